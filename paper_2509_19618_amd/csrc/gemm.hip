@@ -121,17 +121,6 @@ constexpr int GGROUP = 8;          // tile rows per group in the tile order
 #endif
 constexpr int GGROUP2 = MXP_GGROUP2;   // the same for two-segment updates (twice the operand bytes per tile row)
 
-// Direct global->LDS copy of 16 bytes per lane: lane L lands at l + 16 L
-// (l is wave-uniform).  gfx950 global_load_lds_dwordx4.
-MXP_DEV void dma16(const char* g, char* l) {
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)g,
-                                     (void __attribute__((address_space(3)))*)l, 16, 0, 0);
-}
-// s_waitcnt vmcnt(N) (expcnt / lgkmcnt not waited); N < 64
-template <int N> MXP_DEV void wait_vm() {
-    static_assert(N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
-}
 // wait_vm<y NIS + (c ? NC : 0)> for a wave-uniform y <= Y
 template <int NIS, int NC, int Y> MXP_DEV void wait_case(int y, bool c) {
     if constexpr (Y >= 0) {

@@ -10,9 +10,8 @@
 //
 // Right-looking, block size nb (64 or 128).  Per block step k, m = n - k:
 //   without pivoting: the nb x nb diagonal block is factored by one
-//     work-group in LDS (k_diag64); L21 = A21 U11^-1 (k_trsm64_right) and
-//     U12 = L11^-1 A12 (k_trsm64_left) by substitution, one column / row
-//     per thread;
+//     work-group in LDS (k_diag64); L21 = A21 U11^-1 and U12 = L11^-1 A12 by
+//     substitution over 16 x 16 blocks on the matrix cores (k_trsm64);
 //   with pivoting: the m x nb panel is factored by one cooperative launch
 //     (k_panel64_pp): every work-group holds a slice of the panel's rows in
 //     LDS; per column each proposes its largest-magnitude candidate, a grid
@@ -39,72 +38,118 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 // ============================================================== trailing update
 // C (M x N, ldc) -= A (M x K, lda) B (K x N, ldb), all column-major FP64.
 // Work-group tile 128 x 128, four waves of 64 x 64 (4 x 4 blocks of the
-// 16 x 16 MFMA).  Lane l of an MFMA supplies A[l%16][l/16] and B[l/16][l%16]
+// 16 x 16 MFMA).  Lane l of an MFMA supplies P[l%16][l/16] and Q[l/16][l%16]
 // of a 16 x 4 by 4 x 16 step and holds D[l/16 + 4q][l%16], q < 4.  The
-// operands are read straight from memory (the FP64 matrix cores consume
-// 16 bytes per lane per 64 cycles, which the L2 keeps up with); the next
-// step's operands are loaded while the current one is multiplied.
+// product is formed transposed (P = B^T, Q = A^T), so that the 16 lanes of a
+// result row are 16 consecutive rows of C (128 bytes per access).
+//
+// Bound: a k-step of four takes a wave 16 MFMAs of 64 cycles; its operands
+// read straight from memory (32-byte pieces of B, one step ahead) left the
+// matrix cores waiting.  Both operands are staged through LDS instead, 16 of
+// K at a time, the next stage's copies (16 bytes per lane straight into LDS)
+// in flight behind the current one's 64 MFMAs; 69 KB per work-group, so two
+// share a CU and one's C update overlaps the other's products.  A rows stand
+// at a pitch of 144 (the two k of a 32-lane half on different banks), the
+// 16-byte chunks of a B column are XOR-swizzled by the column.  Tiles past an
+// edge, ragged K and columns that are not 16-byte aligned take guarded loads
+// into the same layout.
 constexpr int G64_T = 128;
+constexpr int G64_K = 16;                        // K per stage
+constexpr int G64_PA = 144;                      // doubles between two k of the A stage
+constexpr int G64_SA = G64_K * G64_PA;           // doubles of an A stage
+constexpr int G64_SB = G64_T * G64_K;            // doubles of a B stage
+constexpr size_t G64_LDS = 2 * (size_t)(G64_SA + G64_SB) * 8;
 
-__global__ __launch_bounds__(256) void k_gemm64(double* __restrict__ C, int64_t ldc, const double* __restrict__ A,
-                                                int64_t lda, const double* __restrict__ B, int64_t ldb, int64_t M,
-                                                int64_t N, int K) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+MXP_DEV int g64_key(int col) { return (col >> 1) & 7; }
+// element (k, col) of a B stage
+MXP_DEV int g64_boff(int k, int col) { return col * G64_K + (((k >> 1) ^ g64_key(col)) << 1) + (k & 1); }
+
+__global__ __launch_bounds__(256, 2) void k_gemm64(double* __restrict__ C, int64_t ldc, const double* __restrict__ A,
+                                                   int64_t lda, const double* __restrict__ B, int64_t ldb, int64_t M,
+                                                   int64_t N, int K, int aligned) {
+    extern __shared__ __attribute__((aligned(16))) double gsm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 15, lk = lane >> 4;
-    const int64_t row0 = (int64_t)blockIdx.x * G64_T + wm * 64;
-    const int64_t col0 = (int64_t)blockIdx.y * G64_T + wn * 64;
-    // clamped operand addresses (rows / columns past the edge read a valid
-    // element; their products land in results that are not stored)
-    const double* ap[4];
-    const double* bp[4];
+    const int64_t row0 = (int64_t)blockIdx.x * G64_T, col0 = (int64_t)blockIdx.y * G64_T;
+    const bool inside = aligned && row0 + G64_T <= M && col0 + G64_T <= N;
+    auto stage = [&](int k0, int buf) {
+        double* sA = gsm + buf * (G64_SA + G64_SB);
+        double* sB = sA + G64_SA;
+        if (inside && k0 + G64_K <= K) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        int64_t r = row0 + a * 16 + li;
-        r = r < M ? r : M - 1;
-        ap[a] = A + r + (int64_t)lk * lda;
-    }
+            for (int i = 0; i < 4; ++i) {
+                const int kk = 4 * wave + i;                  // one k: 128 rows, 1 KB
+                dma16((const char*)(A + row0 + 2 * lane + (int64_t)(k0 + kk) * lda), (char*)(sA + kk * G64_PA));
+            }
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        int64_t c = col0 + b * 16 + li;
-        c = c < N ? c : N - 1;
-        bp[b] = B + lk + c * ldb;
-    }
+            for (int i = 0; i < 4; ++i) {
+                const int j = 4 * wave + i;                   // eight columns, 1 KB
+                const int c = 8 * j + (lane >> 3);
+                const int q = (lane & 7) ^ g64_key(c);        // logical chunk kept at this lane's place
+                dma16((const char*)(B + (k0 + 2 * q) + (col0 + c) * ldb), (char*)(sB + j * 128));
+            }
+        } else {
+            double va[8], vb[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e = tid + 256 * i;
+                const int r = e & 127, ka = e >> 7, kb = e & 15, c = e >> 4;
+                va[i] = row0 + r < M && k0 + ka < K ? A[row0 + r + (int64_t)(k0 + ka) * lda] : 0.0;
+                vb[i] = col0 + c < N && k0 + kb < K ? B[k0 + kb + (col0 + c) * ldb] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e = tid + 256 * i;
+                sA[(e >> 7) * G64_PA + (e & 127)] = va[i];
+                sB[g64_boff(e & 15, e >> 4)] = vb[i];
+            }
+        }
+    };
     d4v acc[4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = d4v{0.0, 0.0, 0.0, 0.0};
-    double fa[4], fb[4], na[4], nb_[4];
+    const int nst = (K + G64_K - 1) / G64_K;
+    stage(0, 0);
+    for (int st = 0; st < nst; ++st) {
+        __builtin_amdgcn_s_waitcnt(0);        // this wave's part of stage st is in LDS
+        __syncthreads();                      // everyone's is; stage st - 1's buffer is free
+        if (st + 1 < nst) stage((st + 1) * G64_K, (st + 1) & 1);
+        const double* sA = gsm + (st & 1) * (G64_SA + G64_SB);
+        const double* sB = sA + G64_SA;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) fa[a] = ap[a][0];
+        for (int ks = 0; ks < G64_K / 4; ++ks) {
+            double fa[4], fb[4];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) fb[b] = bp[b][0];
-    for (int k = 0; k < K; k += 4) {
-        const int kn = k + 4 < K ? k + 4 : k;
+            for (int a = 0; a < 4; ++a) fa[a] = sA[(4 * ks + lk) * G64_PA + wm * 64 + a * 16 + li];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) na[a] = ap[a][(int64_t)kn * lda];
+            for (int b = 0; b < 4; ++b) fb[b] = sB[g64_boff(4 * ks + lk, wn * 64 + b * 16 + li)];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) nb_[b] = bp[b][kn];
+            for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) fa[a] = na[a];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) fb[b] = nb_[b];
+                for (int b = 0; b < 4; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[b], fa[a], acc[a][b], 0, 0, 0);
+        }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t c = col0 + b * 16 + li;
-            if (c >= N) continue;
+        for (int a = 0; a < 4; ++a) {
+            const int64_t r = row0 + wm * 64 + a * 16 + li;
+            const int64_t c0 = col0 + wn * 64 + b * 16 + lk;
+            if (inside) {
+                double* p = C + r + c0 * ldc;
+                double x[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t r = row0 + a * 16 + lk + 4 * q;
-                if (r < M) C[r + c * ldc] -= acc[a][b][q];
+                for (int q = 0; q < 4; ++q) x[q] = p[(int64_t)(4 * q) * ldc];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) p[(int64_t)(4 * q) * ldc] = x[q] - acc[a][b][q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (r < M && c0 + 4 * q < N) C[r + (c0 + 4 * q) * ldc] -= acc[a][b][q];
             }
         }
 }
@@ -114,8 +159,13 @@ hipError_t gemm64(double* C, int64_t ldc, const double* A, int64_t lda, const do
     if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
     if (K % 4) return hipErrorInvalidValue;
     dim3 g((unsigned)((M + G64_T - 1) / G64_T), (unsigned)((N + G64_T - 1) / G64_T));
+    static const hipError_t attr =
+        hipFuncSetAttribute((const void*)k_gemm64, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G64_LDS);
+    if (attr) return attr;
     hipEvent_t pt = prof::begin(prof::GEMM64, s);
-    k_gemm64<<<g, 256, 0, s>>>(C, ldc, A, lda, B, ldb, M, N, K);
+    // 16-byte copies need even leading dimensions and 16-byte aligned operands
+    const int aligned = lda % 2 == 0 && ldb % 2 == 0 && ((uintptr_t)A | (uintptr_t)B) % 16 == 0;
+    k_gemm64<<<g, 256, G64_LDS, s>>>(C, ldc, A, lda, B, ldb, M, N, K, aligned);
     prof::end(pt, prof::GEMM64, s, 2.0 * M * (double)N * K, 16.0 * M * (double)N + 8.0 * (M + N) * K);
     return hipGetLastError();
 }
@@ -146,81 +196,258 @@ hipError_t gemm64_rocblas(double* C, int64_t ldc, const double* A, int64_t lda, 
     return st == rocblas_status_success ? hipSuccess : hipErrorUnknown;
 }
 
+// ============================================================== block triangles
+// The triangular solves of a block step run on the matrix cores: the nb x nb
+// triangle is cut into 16 x 16 blocks, its diagonal blocks replaced by their
+// inverses, and the blocks of the lower triangle (of L11, and of U11
+// transposed) kept as MFMA operands: block (i, j), i >= j, k-step ks of lane l
+// at 256 (i (i + 1) / 2 + j) + 64 ks + l = M[16 i + l % 16][16 j + 4 ks + l / 16].
+constexpr int TB = 16;                              // triangle block
+constexpr int TRI_MAX = 8 * 9 / 2 * 256;            // doubles of one packed triangle (nb = 128)
+MXP_DEV int tri_off(int i, int j) { return (i * (i + 1) / 2 + j) * 256; }
+
+// lane J of each 16-lane row to the whole row
+template <int J> MXP_DEV double row_bcast(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + J, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + J, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// step J of the LU of a 16 x 16 block, row r in the lanes r + 16 g, columns
+// in registers; a zero or non-finite pivot is recorded and its column left
+template <int J> MXP_DEV void leaf64(double (&x)[TB], int r, int& bad) {
+    if constexpr (J < TB) {
+        const double pv = row_bcast<J>(x[J]);
+        const bool ok = pv != 0.0 && isfinite(pv);
+        if (!ok && bad < 0) bad = J;
+        const double rp = 1.0 / pv;
+        const double l = (ok && r > J) ? x[J] * rp : 0.0;
+        if (ok && r > J) x[J] = l;
+#pragma unroll
+        for (int c = J + 1; c < TB; ++c) x[c] = fma(-l, row_bcast<J>(x[c]), x[c]);
+        leaf64<J + 1>(x, r, bad);
+    }
+}
+
+// step S of the inverse of a lower triangle, row r in lane r: m its row
+// (diagonal not read), dinv the reciprocal of its diagonal entry
+template <int S> MXP_DEV void tinv64(double (&X)[TB], const double (&m)[TB], double dinv, int r) {
+    if constexpr (S < TB) {
+        const double sc = r == S ? dinv : 1.0, w = r > S ? m[S] : 0.0;
+#pragma unroll
+        for (int c = 0; c <= S; ++c) {
+            X[c] *= sc;
+            X[c] = fma(-w, row_bcast<S>(X[c]), X[c]);
+        }
+        tinv64<S + 1>(X, m, dinv, r);
+    }
+}
+
+// inverse of the lower triangle M of one 16 x 16 block (lane row r; one wave,
+// groups of 16 lanes independent): m(c) = M[r][c] for c < r, dinv = 1 / M[r][r];
+// written as MFMA operand into dst (lanes of one group: w set) and to s
+// (s[c * 18 + r])
+MXP_DEV void tri_inverse(const double (&m)[TB], double dinv, int r, bool w, double* dst, double* s) {
+    double X[TB];
+#pragma unroll
+    for (int c = 0; c < TB; ++c) X[c] = c == r ? 1.0 : 0.0;
+    tinv64<0>(X, m, dinv, r);
+    if (w) {
+#pragma unroll
+        for (int c = 0; c < TB; ++c) {
+            dst[64 * (c >> 2) + 16 * (c & 3) + r] = X[c];
+            if (s) s[c * 18 + r] = X[c];
+        }
+    }
+}
+
 // ============================================================== diagonal block (no pivoting)
-// Unblocked right-looking LU of the kb x kb block at A[k, k] in LDS (kb <=
-// 128: 128 KB), one work-group; a zero or non-finite pivot sets *info.
-__global__ __launch_bounds__(256) void k_diag64(double* A, int64_t lda, int64_t k, int kb,
+// LU of the kb x kb block at A[k, k] (kb <= 128) by one work-group: the block
+// in LDS (padded with the identity to a multiple of 16, pitch D64P), right-
+// looking over 16 x 16 blocks.  Per step, wave 0 factors the diagonal block
+// in registers (one row per lane, the pivot row broadcast along a 16-lane row
+// by DPP) and forms both triangles' inverses in the same instructions (L in
+// one 16-lane row, U transposed in another); the waves then form the strips
+// as products with the inverses and update the rest on the FP64 matrix cores,
+// wave 0 taking the next diagonal block first and going on to its LU.  The
+// chain is what bounds it: about 3 us per step, where the column-by-column
+// elimination took two work-group barriers and an LDS pass per column.
+// A zero / non-finite pivot sets *info; the packed triangles of L11 and
+// U11^T go to PL and PU.
+constexpr int D64P = 130;
+constexpr size_t D64_LDS = (size_t)(128 * D64P + 2 * TB * 18) * 8;
+
+__global__ __launch_bounds__(512) void k_diag64(double* A, int64_t lda, int64_t k, int kb, double* PL, double* PU,
                                                 unsigned long long* info) {
-    extern __shared__ double D[];   // column-major, ld kb
-    const int t = threadIdx.x;
-    for (int e = t; e < kb * kb; e += 256) D[e] = A[(k + e % kb) + (k + e / kb) * lda];
+    extern __shared__ __attribute__((aligned(16))) double gsm[];
+    double* D = gsm;                                  // D[c * D64P + r]
+    double* sIL = gsm + 128 * D64P;                   // L^-1 of the step's block
+    double* sIU = sIL + TB * 18;                      // U^-T
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int P = (kb + TB - 1) / TB, kp = P * TB;
+    for (int e = tid; e < 128 * kp; e += 512) {
+        const int r = e & 127, c = e >> 7;
+        if (r < kp) D[c * D64P + r] = r < kb && c < kb ? A[(k + r) + (k + c) * lda] : (r == c ? 1.0 : 0.0);
+    }
     __syncthreads();
-    for (int j = 0; j < kb; ++j) {
-        const double piv = D[j + j * kb];
-        const bool ok = piv != 0.0 && isfinite(piv);
-        if (!ok && t == 0) atomicMin(info, (unsigned long long)(k + j + 1));
-        if (ok) {
-            const double rp = 1.0 / piv;
-            for (int i = j + 1 + t; i < kb; i += 256) D[i + j * kb] *= rp;
+    // C(i,j) -= L(i,t) U(t,j)
+    auto update = [&](int i, int j, int t) {
+        d4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(D[(TB * t + 4 * ks + lk) * D64P + TB * i + li],
+                                                       D[(TB * j + li) * D64P + TB * t + 4 * ks + lk], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D[(TB * j + li) * D64P + TB * i + lk + 4 * q] -= acc[q];
+    };
+    for (int t = 0; t < P; ++t) {
+        if (wave == 0) {
+            if (t > 0) update(t, t, t - 1);
+            const int o = TB * t;
+            asm volatile("" ::: "memory");
+            double x[TB], m[TB];
+#pragma unroll
+            for (int c = 0; c < TB; ++c) x[c] = D[(o + c) * D64P + o + li];
+            int bad = -1;
+            leaf64<0>(x, li, bad);
+            if (bad >= 0 && lane == 0) atomicMin(info, (unsigned long long)(k + o + bad + 1));
+            if (lk == 0) {
+#pragma unroll
+                for (int c = 0; c < TB; ++c) D[(o + c) * D64P + o + li] = x[c];
+            }
+            asm volatile("" ::: "memory");
+            // lanes 0-15: L^-1; lanes 16-31: U^-T (row li of U^T is column li of U)
+            double dg = 1.0;
+#pragma unroll
+            for (int c = 0; c < TB; ++c) {
+                const double u = D[(o + li) * D64P + o + c];
+                m[c] = (lk & 1) ? u : x[c];
+                if (c == li) dg = u;
+            }
+            const double dinv = (lk & 1) ? 1.0 / dg : 1.0;
+            tri_inverse(m, dinv, li, lk < 2, ((lk & 1) ? PU : PL) + tri_off(t, t), sIL + (lk & 1) * TB * 18);
+        } else if (t > 0) {
+            // the rest of update t - 1
+            const int w = P - t;
+            for (int u = wave; u < w * w; u += 7) update(t + u % w, t + u / w, t - 1);
         }
         __syncthreads();
-        if (ok) {
-            const int w = kb - j - 1;
-            for (int e = t; e < w * w; e += 256) {
-                const int i = j + 1 + e % w, c = j + 1 + e / w;
-                D[i + c * kb] -= D[i + j * kb] * D[j + c * kb];
+        const int w = P - 1 - t;
+        for (int u = wave; u < 2 * w; u += 8) {
+            d4v acc = {0.0, 0.0, 0.0, 0.0};
+            if (u < w) {
+                // block (i,t) transposed: U_tt^-T block^T
+                const int i = t + 1 + u;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sIU[(4 * ks + lk) * 18 + li],
+                                                               D[(TB * t + 4 * ks + lk) * D64P + TB * i + li], acc, 0,
+                                                               0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) D[(TB * t + lk + 4 * q) * D64P + TB * i + li] = acc[q];
+            } else {
+                const int j = t + 1 + u - w;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sIL[(4 * ks + lk) * 18 + li],
+                                                               D[(TB * j + li) * D64P + TB * t + 4 * ks + lk], acc, 0,
+                                                               0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) D[(TB * j + li) * D64P + TB * t + lk + 4 * q] = acc[q];
             }
         }
         __syncthreads();
     }
-    for (int e = t; e < kb * kb; e += 256) A[(k + e % kb) + (k + e / kb) * lda] = D[e];
+    for (int e = tid; e < 128 * kb; e += 512) {
+        const int r = e & 127, c = e >> 7;
+        if (r < kb) A[(k + r) + (k + c) * lda] = D[c * D64P + r];
+    }
+    // the blocks below the diagonal as operands
+    for (int u = wave; u < P * (P - 1) / 2; u += 8) {
+        int i = 1, v = u;
+        while (v >= i) v -= i++;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            PL[tri_off(i, v) + 64 * ks + lane] = D[(TB * v + 4 * ks + lk) * D64P + TB * i + li];
+            PU[tri_off(i, v) + 64 * ks + lane] = D[(TB * i + li) * D64P + TB * v + 4 * ks + lk];
+        }
+    }
+}
+
+// the packed triangle of L11 from a factored nb x nb block (pivoted panels):
+// wave t the inverse of diagonal block t, then every wave its share of the
+// blocks below
+__global__ __launch_bounds__(512) void k_pack64(const double* __restrict__ A, int64_t lda, int64_t k, int nb,
+                                                double* __restrict__ PL) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int P = nb / TB;
+    const double* B = A + k + k * lda;
+    if (wave < P) {
+        double m[TB];
+#pragma unroll
+        for (int c = 0; c < TB; ++c) m[c] = B[TB * wave + li + (int64_t)(TB * wave + c) * lda];
+        tri_inverse(m, 1.0, li, lk == 0, PL + tri_off(wave, wave), nullptr);
+    }
+    for (int u = wave; u < P * (P - 1) / 2; u += 8) {
+        int i = 1, v = u;
+        while (v >= i) v -= i++;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            PL[tri_off(i, v) + 64 * ks + lane] = B[TB * i + li + (int64_t)(TB * v + 4 * ks + lk) * lda];
+    }
 }
 
 // ============================================================== triangular solves of a block step
-// U12 = L11^-1 A12: one thread per column of A12 (nb values in LDS), forward
-// substitution with the unit-lower L11 read as wave-uniform values.
-constexpr int TW = 64;   // columns (rows) per work-group of the substitution kernels
-
-__global__ __launch_bounds__(TW) void k_trsm64_left(double* A, int64_t lda, int64_t k, int nb, int64_t c_begin,
-                                                    int64_t c_end) {
-    extern __shared__ double X[];   // X[i * TW + t]
-    const int t = threadIdx.x;
-    const int64_t c0 = c_begin + (int64_t)blockIdx.x * TW;
-    const int cols = (int)(c_end - c0 < TW ? c_end - c0 : TW);
-    // coalesced load: the wave reads one column at a time
-    for (int cc = 0; cc < cols; ++cc)
-        for (int i = t; i < nb; i += TW) X[i * TW + cc] = A[(k + i) + (c0 + cc) * lda];
-    __syncthreads();
-    if (t < cols) {
-        for (int i = 1; i < nb; ++i) {
-            const double* Lrow = A + (k + i) + k * lda;   // L[i][p] = Lrow[p * lda]
-            double s = X[i * TW + t];
-            for (int p = 0; p < i; ++p) s -= Lrow[(int64_t)p * lda] * X[p * TW + t];
-            X[i * TW + t] = s;
-        }
+// L21 = A21 U11^-1 (as U11^T X = A21^T) and U12 = L11^-1 A12 in one launch:
+// a wave takes 16 rows of A21 (work-groups [0, wgr)) or 16 columns of A12 (the
+// rest) and holds all nb entries of each in registers, in the MFMA result
+// layout, whose registers are also the operands of the next product.  Per
+// 16-block i: acc = M(i, 0..i-1) X(0..i-1) - X(i), X(i) = -M(i,i)^-1 acc, the
+// packed triangle's operands read as whole 512-byte lines.  A wave is a chain
+// of 144 MFMAs of 64 cycles (nb = 128: 3.8 us); one thread per row or column
+// with its entries in LDS was a chain of nb^2/2 dependent LDS reads.
+template <int P>
+__global__ __launch_bounds__(256) void k_trsm64(double* A, int64_t lda, int64_t n, int64_t k, int wgr,
+                                                const double* __restrict__ PL, const double* __restrict__ PU) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const bool right = (int)blockIdx.x < wgr;              // rows of A21
+    const int64_t wg = right ? blockIdx.x : blockIdx.x - wgr;
+    const int64_t o0 = k + TB * P + (wg * 4 + wave) * TB;  // first row / column of the wave
+    if (o0 >= n) return;
+    const bool in = o0 + li < n;
+    const int64_t o = in ? o0 + li : n - 1;
+    // entry e of this lane's row / column: base + (4 q + 16 i) step
+    double* base = right ? A + o + (k + lk) * lda : A + (k + lk) + o * lda;
+    const int64_t step = right ? lda : 1;
+    const double* __restrict__ M = right ? PU : PL;
+    d4v X[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[i][q] = base[(int64_t)(TB * i + 4 * q) * step];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        d4v acc = -X[i];
+#pragma unroll
+        for (int j = 0; j < i; ++j)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(M[tri_off(i, j) + 64 * ks + lane], X[j][ks], acc, 0, 0, 0);
+        d4v y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(M[tri_off(i, i) + 64 * ks + lane], -acc[ks], y, 0, 0, 0);
+        X[i] = y;
     }
-    __syncthreads();
-    for (int cc = 0; cc < cols; ++cc)
-        for (int i = t; i < nb; i += TW) A[(k + i) + (c0 + cc) * lda] = X[i * TW + cc];
-}
-
-// L21 = A21 U11^-1: one thread per row of A21, substitution against U11 by
-// columns: x[j] = (a[j] - sum_{p<j} x[p] U[p][j]) / U[j][j].
-__global__ __launch_bounds__(TW) void k_trsm64_right(double* A, int64_t lda, int64_t k, int nb, int64_t r_begin,
-                                                     int64_t r_end) {
-    extern __shared__ double X[];   // X[j * TW + t]
-    const int t = threadIdx.x;
-    const int64_t r0 = r_begin + (int64_t)blockIdx.x * TW;
-    const int rows = (int)(r_end - r0 < TW ? r_end - r0 : TW);
-    for (int j = 0; j < nb; ++j) X[j * TW + t] = (t < rows) ? A[(r0 + t) + (k + j) * lda] : 0.0;
-    if (t < rows) {
-        for (int j = 0; j < nb; ++j) {
-            const double* Ucol = A + k + (k + j) * lda;   // U[p][j] = Ucol[p]
-            double s = X[j * TW + t];
-            for (int p = 0; p < j; ++p) s -= X[p * TW + t] * Ucol[p];
-            X[j * TW + t] = s / Ucol[j];
-        }
-        for (int j = 0; j < nb; ++j) A[(r0 + t) + (k + j) * lda] = X[j * TW + t];
+    if (in) {
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) base[(int64_t)(TB * i + 4 * q) * step] = X[i][q];
     }
 }
 
@@ -442,26 +669,22 @@ int lu64_block(int64_t n) {
     return rpw <= 128 ? 128 : 64;
 }
 
-size_t lu64_work_bytes(int64_t n) {
+// candidates and top rows of the pivoted panel, its barrier and error words
+static size_t lu64_panel_bytes(int64_t n) {
     const int nb = lu64_block(n);
-    return (size_t)2 * 256 * (nb + 2) * 8 + (size_t)2 * nb * 8 + 256 + 64;
+    return ((size_t)2 * 256 * (nb + 2) * 8 + (size_t)2 * nb * 8 + 256 + 63) / 64 * 64;
 }
+
+size_t lu64_work_bytes(int64_t n) { return lu64_panel_bytes(n) + (size_t)2 * TRI_MAX * 8; }
 
 hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* work, unsigned long long* info_dev,
                        int use_rocblas, hipStream_t s) {
     const int nb = lu64_block(n);
     static const hipError_t attr = []() {
         hipError_t e;
-        if ((e = hipFuncSetAttribute((const void*)k_diag64, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8)))
+        if ((e = hipFuncSetAttribute((const void*)k_diag64, hipFuncAttributeMaxDynamicSharedMemorySize, (int)D64_LDS)))
             return e;
-        if ((e = hipFuncSetAttribute((const void*)k_panel64_pp, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     128 * 1024)))
-            return e;
-        if ((e = hipFuncSetAttribute((const void*)k_trsm64_left, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     128 * TW * 8)))
-            return e;
-        return hipFuncSetAttribute((const void*)k_trsm64_right, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   128 * TW * 8);
+        return hipFuncSetAttribute((const void*)k_panel64_pp, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     }();
     if (attr) return attr;
     char* wb = (char*)work;
@@ -469,6 +692,8 @@ hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* w
     double* top = cand + 2 * 256 * (nb + 2);
     unsigned* bar = (unsigned*)(top + 2 * nb);
     int* err = (int*)(bar + 2);
+    double* PL = (double*)(wb + lu64_panel_bytes(n));
+    double* PU = PL + TRI_MAX;
     hipError_t e;
     if ((e = fill_u64(info_dev, 1, ~0ull, s))) return e;
     if ((e = fill_u64(bar, 2, 0ull, s))) return e;   // bar[0..1] and err
@@ -491,16 +716,16 @@ hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* w
             if (k > 0) k_laswp64<<<(unsigned)((k + 255) / 256), 256, 0, s>>>(A, lda, ipiv, k, kb, 0, k);
             if (k + kb < n)
                 k_laswp64<<<(unsigned)((n - k - kb + 255) / 256), 256, 0, s>>>(A, lda, ipiv, k, kb, k + kb, n);
+            if (k + kb < n) k_pack64<<<1, 512, 0, s>>>(A, lda, k, kb, PL);
         } else {
-            k_diag64<<<1, 256, (size_t)kb * kb * 8, s>>>(A, lda, k, kb, info_dev);
-            if (k + kb < n)
-                k_trsm64_right<<<(unsigned)((n - k - kb + TW - 1) / TW), TW, (size_t)kb * TW * 8, s>>>(
-                    A, lda, k, kb, k + kb, n);
+            k_diag64<<<1, 512, D64_LDS, s>>>(A, lda, k, kb, PL, PU, info_dev);
         }
         if ((e = hipGetLastError())) return e;
         if (k + kb < n) {
-            k_trsm64_left<<<(unsigned)((n - k - kb + TW - 1) / TW), TW, (size_t)kb * TW * 8, s>>>(A, lda, k, kb,
-                                                                                              k + kb, n);
+            // every block but the last is a full one (kb = nb)
+            const int wg = (int)((n - k - kb + 63) / 64), wgr = ipiv ? 0 : wg;
+            if (kb == 128) k_trsm64<8><<<wg + wgr, 256, 0, s>>>(A, lda, n, k, wgr, PL, PU);
+            else k_trsm64<4><<<wg + wgr, 256, 0, s>>>(A, lda, n, k, wgr, PL, PU);
             if ((e = hipGetLastError())) return e;
             auto g64 = use_rocblas ? gemm64_rocblas : gemm64;
             if ((e = g64(A + (k + kb) + (k + kb) * lda, lda, A + (k + kb) + k * lda, lda, A + k + (k + kb) * lda, lda,
