@@ -601,65 +601,200 @@ __global__ __launch_bounds__(256) void k_laswp64(double* A, int64_t lda, const i
 }
 
 // ============================================================== solve
-// x <- P x (the swaps in order), then unit-lower forward and upper backward
-// substitution, blocked by 64 rows: per block one work-group solves the
-// triangle (the block's 64 x 64 diagonal block in LDS), then every row
-// below (above) subtracts the block's contribution (one thread per row).
-__global__ void k_apply_pivots(double* x, int64_t ldx, int nr, const int64_t* __restrict__ ipiv, int64_t n) {
-    const int r = threadIdx.x;
-    if (r >= nr) return;
-    double* v = x + r * ldx;
-    for (int64_t k = 0; k < n; ++k) {
-        const int64_t p = ipiv[k];
-        if (p != k) {
-            const double a = v[k];
-            v[k] = v[p];
-            v[p] = a;
-        }
-    }
-}
+// x <- P x, then unit-lower forward and upper backward substitution over
+// blocks of 128 rows, one launch per block: every work-group subtracts the
+// previous block's contribution from its 128 rows, and the one that holds
+// the next block solves it in the same launch.  Launches and the solve's
+// chain bound it (about 7 us per block); blocks of 64 with the triangle solved
+// by one lane per right-hand side from memory took 80 us per block.
 
-constexpr int SB = 64;
-
-template <bool LOWER>
-__global__ __launch_bounds__(64) void k_trsv64_block(const double* __restrict__ A, int64_t lda, int64_t n,
-                                                     int64_t b0, double* x, int64_t ldx, int nr) {
-    __shared__ double D[SB * SB];
-    const int t = threadIdx.x;
-    const int kb = (int)(n - b0 < SB ? n - b0 : SB);
-    for (int c = 0; c < kb; ++c)
-        if (t < kb) D[t + c * SB] = A[(b0 + t) + (b0 + c) * lda];
+// the n swaps in order, one work-group per right-hand side: x in LDS when it
+// fits (lds_n = n), the swap rows read ahead 64 at a time
+__global__ __launch_bounds__(256) void k_apply_pivots(double* x, int64_t ldx, const int64_t* __restrict__ ipiv,
+                                                      int64_t n, int lds_n) {
+    extern __shared__ __attribute__((aligned(16))) double gsm[];
+    double* g = x + (int64_t)blockIdx.x * ldx;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < lds_n; i += 256) gsm[i] = g[i];
     __syncthreads();
-    if (t < nr) {
-        double* v = x + t * ldx + b0;
-        if (LOWER) {
-            for (int i = 1; i < kb; ++i) {
-                double s = v[i];
-                for (int p = 0; p < i; ++p) s -= D[i + p * SB] * v[p];
-                v[i] = s;
-            }
-        } else {
-            for (int i = kb - 1; i >= 0; --i) {
-                double s = v[i];
-                for (int p = i + 1; p < kb; ++p) s -= D[i + p * SB] * v[p];
-                v[i] = s / D[i + i * SB];
+    if (tid < 64) {
+        for (int64_t k0 = 0; k0 < n; k0 += 64) {
+            const int m = (int)(n - k0 < 64 ? n - k0 : 64);
+            const int pv = tid < m ? (int)ipiv[k0 + tid] : 0;
+            for (int j = 0; j < m; ++j) {
+                const int64_t k = k0 + j, p = __builtin_amdgcn_readlane(pv, j);
+                if (p != k && tid == 0) {
+                    double* v = lds_n ? gsm : g;
+                    const double a = v[k];
+                    v[k] = v[p];
+                    v[p] = a;
+                }
             }
         }
     }
+    __syncthreads();
+    for (int i = tid; i < lds_n; i += 256) g[i] = gsm[i];
 }
 
-// rows [r_begin, r_end) -= A[rows, b0 : b0+kb] x[b0 : b0+kb]
-__global__ __launch_bounds__(256) void k_gemv64_update(const double* __restrict__ A, int64_t lda, int64_t b0, int kb,
-                                                       int64_t r_begin, int64_t r_end, double* x, int64_t ldx,
-                                                       int nr) {
-    const int64_t r = r_begin + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= r_end) return;
-    for (int q = 0; q < nr; ++q) {
-        const double* v = x + q * ldx + b0;
-        double s = 0.0;
-        for (int c = 0; c < kb; ++c) s += A[r + (b0 + c) * lda] * v[c];
-        x[q * ldx + r] -= s;
+constexpr int SVB = 128;     // rows of a block step
+
+MXP_DEV double rl64(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// One wave solves a 64 x 64 triangle, row r in lane r: d[s] = T[r][s], zero
+// outside the strict triangle, dg its diagonal (1 for the unit-lower); NR
+// right-hand sides side by side.  The quotient by the diagonal is the product
+// with its reciprocal and one residual correction.
+template <bool LOWER, int NR> MXP_DEV void tri_solve64(double (&x)[NR], const double (&d)[64], double dg) {
+    const double ri = LOWER ? 1.0 : 1.0 / dg;
+#pragma unroll
+    for (int s2 = 0; s2 < 64; ++s2) {
+        const int s = LOWER ? s2 : 63 - s2;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            double q = x[r];
+            if (!LOWER) {
+                q = x[r] * ri;
+                q = fma(fma(-dg, q, x[r]), ri, q);
+            }
+            x[r] = fma(-d[s], rl64(q, s), x[r]);
+        }
     }
+    if (!LOWER)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const double q = x[r] * ri;
+            x[r] = fma(fma(-dg, q, x[r]), ri, q);
+        }
+}
+
+// Block step: the block [b0, b0 + kb) and the rows beyond it (above it for
+// the upper triangle) lose A[., p0 : p0 + pkb] x[p0 : p0 + pkb]; work-group 0
+// then solves the block's triangle.  512 threads: 128 rows x 4 column groups.
+template <bool LOWER, int NR>
+__global__ __launch_bounds__(512) void k_trsv64_step(const double* __restrict__ A, int64_t lda, int64_t n, int64_t b0,
+                                                     int kb, int64_t p0, int pkb, double* x, int64_t ldx) {
+    __shared__ double sx[NR][SVB];
+    __shared__ double part[NR][4][SVB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = tid & 127, cg = tid >> 7;
+    const bool solver = blockIdx.x == 0;
+    // first row of this work-group, end of its rows
+    const int64_t r0 = solver ? b0 : LOWER ? b0 + kb + (int64_t)(blockIdx.x - 1) * SVB
+                                           : (int64_t)(blockIdx.x - 1) * SVB;
+    const int64_t rend = solver ? b0 + kb : LOWER ? n : b0;
+    const int64_t i = r0 + row < rend ? r0 + row : rend - 1;
+    const bool in = r0 + row < rend;
+    // the triangle's rows of the solver's waves: wave 0 the first 64 rows,
+    // wave 1 the rest (d), waves 2-5 the block between them (16 columns each)
+    double d[64], dg = 1.0;
+    const int h0 = kb < 64 ? kb : 64, h1 = kb - h0;         // rows of the two halves
+    if (solver && wave < 2) {
+        const int64_t o = b0 + 64 * wave;
+        const int m = wave ? h1 : h0;
+#pragma unroll
+        for (int c = 0; c < 64; ++c) {
+            const bool strict = lane < m && c < m && (LOWER ? c < lane : c > lane);
+            const double v = A[strict ? (o + lane) + (o + c) * lda : b0 + b0 * lda];
+            d[c] = strict ? v : 0.0;
+        }
+        if (!LOWER && lane < m) dg = A[(o + lane) + (o + lane) * lda];
+    }
+    if (pkb > 0) {
+        for (int e = tid; e < NR * SVB; e += 512) {
+            const int r = e / SVB, c = e % SVB;
+            sx[r][c] = c < pkb ? x[r * ldx + p0 + c] : 0.0;
+        }
+        __syncthreads();
+        double acc[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) acc[r] = 0.0;
+        const double* ap = A + i + p0 * lda;
+#pragma unroll
+        for (int c0 = 0; c0 < 32; c0 += 16) {
+            double a[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                const int cc = 32 * cg + c0 + c;
+                a[c] = ap[(int64_t)(cc < pkb ? cc : 0) * lda];
+            }
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                const int cc = 32 * cg + c0 + c;
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (cc < pkb) acc[r] = fma(a[c], sx[r][cc], acc[r]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r) part[r][cg][row] = acc[r];
+        __syncthreads();
+    }
+    if (cg == 0) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            double v = x[r * ldx + i];
+            if (pkb > 0) v -= (part[r][0][row] + part[r][1][row]) + (part[r][2][row] + part[r][3][row]);
+            if (solver) sx[r][row] = v;
+            else if (in && pkb > 0) x[r * ldx + i] = v;
+        }
+    }
+    if (!solver) return;
+    __syncthreads();
+    // the half solved first (rows 0-63 of L, 64-127 of U), its contribution to
+    // the other half, the other half
+    const int first = LOWER ? 0 : 1;
+    auto half = [&](int w, int m) {
+        if (wave == w && m > 0) {
+            double v[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) v[r] = lane < m ? sx[r][64 * w + lane] : 0.0;
+            tri_solve64<LOWER, NR>(v, d, dg);
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (lane < m) {
+                    sx[r][64 * w + lane] = v[r];
+                    x[r * ldx + b0 + 64 * w + lane] = v[r];
+                }
+        }
+    };
+    half(first, first ? h1 : h0);
+    if (h1 > 0) {
+        // rows of the half still to be solved, 16 columns of the solved half per wave
+        const int mo = first ? h0 : h1, ms = first ? h1 : h0;
+        double a[16];
+        if (wave >= 2 && wave < 6) {
+            const int64_t ro = b0 + (first ? 0 : 64) + (lane < mo ? lane : 0);
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                const int cc = 16 * (wave - 2) + c;
+                a[c] = A[ro + (b0 + 64 * first + (cc < ms ? cc : 0)) * lda];
+            }
+        }
+        __syncthreads();
+        if (wave >= 2 && wave < 6) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                double t = 0.0;
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    const int cc = 16 * (wave - 2) + c;
+                    if (cc < ms) t = fma(a[c], sx[r][64 * first + cc], t);
+                }
+                part[r][wave - 2][lane] = t;
+            }
+        }
+        __syncthreads();
+        if (wave == 1 - first)
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                sx[r][64 * (1 - first) + lane] -=
+                    (part[r][0][lane] + part[r][1][lane]) + (part[r][2][lane] + part[r][3][lane]);
+    }
+    half(1 - first, first ? h0 : h1);
 }
 
 // ============================================================== drivers
@@ -743,24 +878,41 @@ int* lu64_err_word(void* work, int64_t n) {
     return (int*)((unsigned*)(top + 2 * nb) + 2);
 }
 
+template <int NR>
+static void lu64_solve_nr(int64_t n, const double* A, int64_t lda, double* X, int64_t ldx, hipStream_t s) {
+    const int64_t last = (n - 1) / SVB * SVB;
+    auto wgs = [](int64_t rows) { return (unsigned)(1 + (rows + SVB - 1) / SVB); };
+    for (int64_t b0 = 0; b0 < n; b0 += SVB) {
+        const int kb = (int)(n - b0 < SVB ? n - b0 : SVB);
+        k_trsv64_step<true, NR><<<b0 ? wgs(n - b0 - kb) : 1u, 512, 0, s>>>(A, lda, n, b0, kb, b0 - SVB, b0 ? SVB : 0,
+                                                                       X, ldx);
+    }
+    for (int64_t b0 = last; b0 >= 0; b0 -= SVB) {
+        const int kb = (int)(n - b0 < SVB ? n - b0 : SVB);
+        const int pkb = b0 == last ? 0 : (int)(n - b0 - SVB < SVB ? n - b0 - SVB : SVB);
+        k_trsv64_step<false, NR><<<pkb ? wgs(b0) : 1u, 512, 0, s>>>(A, lda, n, b0, kb, b0 + SVB, pkb, X, ldx);
+    }
+}
+
 hipError_t lu64_solve(int64_t n, const double* A, int64_t lda, const int64_t* ipiv, double* X, int64_t ldx, int nr,
                       hipStream_t s) {
     hipError_t e;
     if (ipiv) {
-        k_apply_pivots<<<1, 64, 0, s>>>(X, ldx, nr, ipiv, n);
+        constexpr int LDS_N = 20000;                  // 160 KB of LDS
+        static const hipError_t attr = hipFuncSetAttribute((const void*)k_apply_pivots,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS_N * 8);
+        if (attr) return attr;
+        const int lds_n = n <= LDS_N ? (int)n : 0;
+        k_apply_pivots<<<nr, 256, (size_t)lds_n * 8, s>>>(X, ldx, ipiv, n, lds_n);
         if ((e = hipGetLastError())) return e;
     }
-    for (int64_t b0 = 0; b0 < n; b0 += SB) {
-        const int kb = (int)(n - b0 < SB ? n - b0 : SB);
-        k_trsv64_block<true><<<1, 64, 0, s>>>(A, lda, n, b0, X, ldx, nr);
-        if (b0 + kb < n)
-            k_gemv64_update<<<(unsigned)((n - b0 - kb + 255) / 256), 256, 0, s>>>(A, lda, b0, kb, b0 + kb, n, X, ldx,
-                                                                                  nr);
-    }
-    for (int64_t b0 = (n - 1) / SB * SB; b0 >= 0; b0 -= SB) {
-        const int kb = (int)(n - b0 < SB ? n - b0 : SB);
-        k_trsv64_block<false><<<1, 64, 0, s>>>(A, lda, n, b0, X, ldx, nr);
-        if (b0 > 0) k_gemv64_update<<<(unsigned)((b0 + 255) / 256), 256, 0, s>>>(A, lda, b0, kb, 0, b0, X, ldx, nr);
+    for (int r = 0; r < nr;) {
+        const int w = nr - r >= 4 ? 4 : nr - r >= 2 ? 2 : 1;
+        double* x = X + r * ldx;
+        if (w == 4) lu64_solve_nr<4>(n, A, lda, x, ldx, s);
+        else if (w == 2) lu64_solve_nr<2>(n, A, lda, x, ldx, s);
+        else lu64_solve_nr<1>(n, A, lda, x, ldx, s);
+        r += w;
     }
     return hipGetLastError();
 }
