@@ -53,7 +53,7 @@ struct FactorPlan {
     void* binv;      // 2 x 3 x nb x nb 16-bit parts of the current block's inverses (U11^-1, L11^-1)
     float* binv_sc;  // 2 x nb reciprocal line scales of those parts
     unsigned long long* info;  // 1
-    int* dsync;      // nblk x diag_sync_words(): phase counters of the diagonal-block LUs (zeroed per factorisation)
+    int* dsync;      // nblk x diag_sync_words(nb): task counters of the diagonal-block LUs (zeroed per factorisation)
     int gemm_tile = 0;  // work-group tile of the trailing update (GEMM_TILE_*)
 };
 
@@ -107,10 +107,10 @@ hipError_t gemm_group(int update, int store, int tile, const GemmCall* calls, in
 // FP32 LU of the diagonal block A[k:k+kb, k:k+kb] (padded to kbp, a multiple
 // of 64, with the identity) by a few cooperating work-groups: T/Trm (ld ldt)
 // get L\U column- and row-major, linv/uinv the 64x64 sub-block inverses, A
-// the factored block.  sync: diag_sync_words() zeroed ints for this call.  A
+// the factored block.  sync: diag_sync_words(nb) zeroed ints for this call.  A
 // zero / non-finite pivot sets *info (atomic min) to its 1-based column; an
 // expired wait sets it to 2^62.
-size_t diag_sync_words();
+size_t diag_sync_words(int64_t nb);
 struct DiagCall {
     void* A;
     int64_t lda, k;

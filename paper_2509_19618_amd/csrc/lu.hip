@@ -5,7 +5,7 @@
 // the input allowed).
 //
 // Per block step k (block size nb):
-//   1. diagonal block A11 -> FP32, LU in FP32 by up to 24 cooperating
+//   1. diagonal block A11 -> FP32, LU in FP32 by up to 32 cooperating
 //      work-groups over 32x32 tiles (diag.hip); inverses of the 64x64
 //      diagonal sub-blocks of L11 and U11 kept;
 //   2. L21 = A21 U11^-1 and U12 = L11^-1 A12 by blocked substitution in
@@ -66,7 +66,7 @@ WorkLayout work_layout(int64_t n, int64_t nb, int update) {
     W.inv_sa = off; off = al256(off + 4 * (size_t)(rows / 32) * 4);
     W.inv_sb = off; off = al256(off + 4 * (size_t)(rows / 32) * 4);
     W.info = off; off = al256(off + 8);
-    W.dsync = off; off = al256(off + (size_t)((n + nb - 1) / nb) * diag_sync_words() * 4);
+    W.dsync = off; off = al256(off + (size_t)((n + nb - 1) / nb) * diag_sync_words(nb) * 4);
     W.pairw = off;
     if (prec_block(nb) == 2 * nb) off = al256(off + (size_t)((n + 2 * nb - 1) / (2 * nb)) * nb * nb * 4);
     W.binv = off; off = al256(off + (size_t)2 * 3 * nb * nb * 2);
@@ -1001,7 +1001,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         float* uinv = p.uinv + blk * nb * 64;
         hipEvent_t pt = prof::begin(prof::DIAG, st);
         hipError_t e2 = diag_lu(ST, A, lda, k, kb, kbp, T, p.Trm + blk * nb * nb, nb, linv, uinv,
-                                p.dsync + blk * diag_sync_words(), p.info, st);
+                                p.dsync + blk * diag_sync_words(nb), p.info, st);
         if (e2) return e2;
         prof::end(pt, prof::DIAG, st, 2.0 / 3.0 * kb * (double)kb * kb, 2.0 * kb * (double)kb * sizeof(ST_T));
         if ((e2 = hipGetLastError())) return e2;
@@ -1078,7 +1078,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
 
     if ((e = fill_u64(p.info, 1, ~0ull, s))) return e;
     {
-        const int64_t words = ((n + nb - 1) / nb) * (int64_t)diag_sync_words();
+        const int64_t words = ((n + nb - 1) / nb) * (int64_t)diag_sync_words(nb);
         if ((e = fill_u64(p.dsync, (words + 1) / 2, 0ull, s))) return e;
     }
     // panels 0 and 1 (block column and row 1 updated by step 0 alone)
@@ -1171,7 +1171,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
         const FactorPlan& p = P[g];
         if ((e = fill_u64(p.info, 1, ~0ull, s))) return e;
         const int64_t nblk = (p.n + p.nb - 1) / p.nb;
-        const int64_t words = nblk * (int64_t)diag_sync_words();
+        const int64_t words = nblk * (int64_t)diag_sync_words(p.nb);
         if ((e = fill_u64(p.dsync, (words + 1) / 2, 0ull, s))) return e;
         steps = nblk > steps ? nblk : steps;
     }
@@ -1189,7 +1189,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
             const int kb = (int)(p.n - k < nb ? p.n - k : nb);
             const int64_t blk = k / nb, m = p.n - k - kb;
             dc[nd++] = DiagCall{p.A, p.lda, k, kb, (int)rup(kb, 64), nb, p.T + blk * nb * nb, p.Trm + blk * nb * nb,
-                                p.linv + blk * nb * 64, p.uinv + blk * nb * 64, p.dsync + blk * diag_sync_words(),
+                                p.linv + blk * nb * 64, p.uinv + blk * nb * 64, p.dsync + blk * diag_sync_words(nb),
                                 p.info};
             if (NP && inverse_path(p, k)) {
                 pg.g[np++].nb = nb;                       // descriptors filled below (tile rows need nbmax)

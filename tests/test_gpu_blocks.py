@@ -1,0 +1,90 @@
+"""GPU tests of the block kernels at the sizes where their tilings change.
+
+* The FP32 diagonal-block LU (one block, n <= nb): L U against the stored
+  matrix in FP64, elementwise within the error of an FP32 elimination
+  (2 (kb + 32) 2^-24 |L||U|: kb sums and the reciprocal's two roundings per
+  element), the row-major copy and the stored block equal to it, and the
+  64 x 64 sub-block inverses within the same relative error.
+* The FP64 LU and solve: L U against P A within 8 n eps |L||U|, |L| <= 1 with
+  pivoting, the solution's HPL scaled residual below 16.
+"""
+import pytest
+import torch
+
+import paper_2509_19618_amd as mxp
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -53
+
+
+# one tile, a tile and a row, whole 64s, tiles at every distance from the
+# diagonal (from 4 tiles on), ragged ends, the largest block; then a zero pivot
+@pytest.mark.parametrize("n,nb,store", [(1, 64, "f32"), (33, 64, "f16"), (64, 64, "bf16"), (96, 128, "f32"),
+                                        (128, 128, "f16"), (161, 256, "bf16"), (512, 512, "f32"),
+                                        (501, 512, "f16"), (1000, 1024, "bf16"), (1024, 1024, "f32")])
+def test_diagonal_block(n, nb, store):
+    print("diag", n, nb, store, flush=True)
+    prob = mxp.mxp_generate(n, 1, 11 + n, store=store, kind=mxp.GEN_SQRTN, gamma=1.0)
+    A = mxp.as_matrix(prob.A, n).double().clone()
+    fac = mxp.mxp_factor(prob, nb, store)
+    assert fac.info == 0
+    lay = mxp.factor_layout(n, nb, store)
+
+    def f32(off, shape):
+        cnt = shape[0] * shape[1]
+        return fac.aux[off:off + 4 * cnt].view(torch.float32).view(shape)
+
+    T = f32(lay.T, (nb, nb)).t()[:n, :n]
+    assert torch.equal(T, f32(lay.Trm, (nb, nb))[:n, :n])
+    stored = mxp.as_matrix(fac.LU, n)
+    assert torch.equal(stored, T.to(stored.dtype))
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    L, U = torch.tril(T.double(), -1) + eye, torch.triu(T.double())
+    bound = 2 * (n + 32) * 2.0 ** -24
+    assert bool(((L @ U - A).abs() <= bound * (L.abs() @ U.abs())).all())
+    for b in range(n // 64):
+        s = slice(64 * b, 64 * b + 64)
+        Li = f32(lay.linv + b * 16384, (64, 64)).t().double()
+        Ui = f32(lay.uinv + b * 16384, (64, 64)).double()
+        e = eye[s, s]
+        assert bool(((Li @ L[s, s] - e).abs() <= bound * (Li.abs() @ L[s, s].abs())).all())
+        assert bool(((Ui @ U[s, s] - e).abs() <= bound * (Ui.abs() @ U[s, s].abs())).all())
+
+
+@pytest.mark.parametrize("n,nb,col", [(64, 64, 0), (130, 256, 37), (600, 512, 290), (600, 128, 599)])
+def test_first_zero_pivot_is_reported(n, nb, col):
+    print("zero pivot", n, nb, col, flush=True)
+    prob = mxp.mxp_generate(n, 1, 5, store="f32")
+    A = mxp.as_matrix(prob.A, n)
+    A.copy_(torch.eye(n, device="cuda"))
+    A[col, col] = 0.0
+    assert mxp.mxp_factor(prob, nb, "f32").info == col + 1
+
+
+# unpivoted: 16-wide tiles, the 128 block; pivoted also the widths of the
+# one-work-group panel (16 columns to 2048 rows, 8 to 4096, 4 to 8192) and the
+# device-wide one beyond
+@pytest.mark.parametrize("n,pivot,nrhs", [(1, False, 1), (15, False, 3), (17, True, 1), (128, False, 4),
+                                          (129, True, 5), (257, False, 7), (300, True, 2), (2049, True, 1),
+                                          (4100, True, 1), (8200, True, 1)])
+def test_lu64_and_solve(n, pivot, nrhs):
+    print("lu64", n, pivot, nrhs, flush=True)
+    prob = mxp.mxp_generate(n, nrhs, 3 + n, store="f64", kind=mxp.GEN_UNIFORM if pivot else mxp.GEN_DOMINANT)
+    A = mxp.as_matrix(prob.A, n).clone()
+    fac = mxp.mxp_lu64_factor(prob.A, n, prob.lda, pivot)
+    assert fac.info == 0
+    X = mxp.mxp_lu64_solve(fac, prob.B)
+    r = prob.B - X @ A.t()
+    den = (A.abs().sum(1).max() * X.abs().amax(1) + prob.B.abs().amax(1)) * n * EPS
+    assert bool((r.abs().amax(1) / den < 16).all())
+    LU = mxp.as_matrix(fac.LU, n)
+    L, U = torch.tril(LU, -1), torch.triu(LU)
+    if pivot:
+        assert float(L.abs().max()) <= 1.0 + 2 * EPS
+        perm = list(range(n))
+        for k, p in enumerate(fac.ipiv.tolist()):
+            assert k <= p < n
+            perm[k], perm[p] = perm[p], perm[k]
+        A = A[torch.tensor(perm, device="cuda")]
+    L = L + torch.eye(n, dtype=torch.float64, device="cuda")
+    assert bool(((L @ U - A).abs() <= 8 * n * EPS * (L.abs() @ U.abs())).all())
