@@ -188,24 +188,31 @@ __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const t
         return (unsigned)((kb + TS - 1) / TS);
     };
     if (tid < TS) w[tid] = (tid < rows) ? rhs[r0 + tid] : 0.0;
-    const bool vload = vec && rows == TS;
+    // The ragged last strip takes the same 16-byte loads: with 16-byte aligned
+    // columns the rows up to lda may be read (its panel columns lie before the
+    // last one), the lanes past lda re-read the strip's first rows, and the
+    // sums of rows past n are dropped.  (Element loads, waited for one by one,
+    // made that one strip the end of the forward solve: n = 20001 FP16 846 us
+    // per solve against 312 us.)
+    const bool vload = vec;
     const int rg = lane % RG, cl = lane / RG;
+    const int64_t rl = r0 + RPL * rg < lda ? r0 + RPL * rg : r0;   // first row this lane reads
     constexpr int PF = 16;                     // panel loads issued before the dependency's flag is awaited
     // The factor panels do not depend on the flags: the panel of the next
     // dependency block is loaded while the current one is awaited and applied
     // (two buffers, the loop taken two blocks at a time).  The loads carry no
     // condition (a column past the range reads column 0 and is weighted zero
     // below): a load under a branch ends in a wait for every load in flight,
-    // which would serialise them (the ragged last strip, which takes element
-    // loads below, reads the 16-byte aligned inverse array instead and
-    // ignores the values).
+    // which would serialise them (unaligned columns, which take element loads
+    // below, read the 16-byte aligned inverse array instead and ignore the
+    // values).
     const int64_t istep = LOWER ? 1 : -1;
     auto in_range = [&](int64_t i) { return LOWER ? (i < first) : (i > last); };
     auto issue = [&](int64_t i, uint4* dst) {
         const int64_t c0 = i * nb;
         const int kbi = (int)(n - c0 < nb ? n - c0 : nb);
         const int q = (kbi + 3) / 4, cb = wv * q, ce = (cb + q < kbi) ? cb + q : kbi;
-        const T* base = A + r0 + RPL * rg + c0 * lda;
+        const T* base = A + rl + c0 * lda;
 #pragma unroll
         for (int m = 0; m < PF; ++m) {
             const int c = cb + cl + m * CPI;
@@ -219,7 +226,7 @@ __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const t
         const int64_t c0 = i * nb;
         const int kbi = (int)(n - c0 < nb ? n - c0 : nb);
         const int q = (kbi + 3) / 4, cb = wv * q, ce = (cb + q < kbi) ? cb + q : kbi;
-        const T* base = A + r0 + RPL * rg + c0 * lda;
+        const T* base = A + rl + c0 * lda;
         if (in_range(i + istep)) issue(i + istep, nxt);
         if (!wait_flag(&ready[i / gb], strips_of(i / gb), err, &s_abort)) return false;
 #pragma unroll

@@ -88,3 +88,18 @@ def test_lu64_and_solve(n, pivot, nrhs):
         A = A[torch.tensor(perm, device="cuda")]
     L = L + torch.eye(n, dtype=torch.float64, device="cuda")
     assert bool(((L @ U - A).abs() <= 8 * n * EPS * (L.abs() @ U.abs())).all())
+
+
+# a last strip of 1 to 63 rows, lda ending inside it or past it: the 16-byte
+# loads (padding rows filled with NaN) against the element loads of an odd lda
+@pytest.mark.parametrize("n,nb,store,lda", [(321, 64, "f16", 384), (600, 128, "bf16", 640), (1000, 128, "f16", 1000),
+                                            (1087, 256, "f32", 1088)])
+def test_ragged_last_strip_of_the_substitution(n, nb, store, lda):
+    print("ragged strip", n, nb, store, lda, flush=True)
+    out = []
+    for ld in (lda, n + 1 - n % 2):
+        prob = mxp.mxp_generate(n, 3, 21, store=store, lda=ld)
+        fac = mxp.mxp_factor(prob, nb, store)
+        fac.LU[:, n:] = float("nan")
+        out.append(mxp.mxp_apply_prec(fac, prob.B))
+    assert torch.equal(out[0], out[1])
