@@ -26,39 +26,86 @@ hipError_t fill_u64(void* p, int64_t count, uint64_t v, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- generation
-// Thread (row i, column quad q): one Philox call gives A[i, 4q..4q+3].
-// Each thread also accumulates sum_j |k(i,j) - 2^31| exactly in 64-bit
-// integers; the per-row sums are combined with integer atomics, which are
-// exact and order independent.  Entries are s 2^-32 (s = k - 2^31) for the
-// matrices with entries in [-1/2, 1/2), s 2^-31 for those in [-1, 1).
-constexpr int GEN_QUADS = 64;  // column quads per thread
+// Thread: GEN_R consecutive rows by a run of column quads; one Philox call
+// gives A[i, 4q..4q+3].  Each thread also accumulates sum_j |k(i,j) - 2^31|
+// exactly in 64-bit integers; the per-row sums are combined with integer
+// atomics, which are exact and order independent.  Entries are s 2^-32 (s = k -
+// 2^31) for the matrices with entries in [-1/2, 1/2), s 2^-31 for those in
+// [-1, 1).
+//
+// Bound: the stores at large n (16-bit: 2 n^2 bytes) and the Philox rounds
+// (shared with the regenerating product, 0.36 ms at n = 32768).  Each entry was
+// rounded through FP64 bits (about 40 integer instructions) and stored alone:
+// 1.61 ms at n = 32768 FP16, 72 us at n = 600, where 64 quads per thread left
+// 9 work-groups.  Four rows per thread make the stores 8 bytes (16-bit
+// formats), the rounding below is a few instructions, and the quads per thread
+// follow from n.
+constexpr int GEN_R = 4;       // rows per thread
+
+// s unit (unit a power of two) rounded once to the storage format.  Beyond 24
+// bits the draw is first rounded to a multiple of 256 by rounding to odd (its
+// 24-bit FP32 value is then exact, and keeps at least 17 bits with the
+// discarded ones' presence in the last, so that the second rounding is the
+// only one).
+template <int ST> MXP_DEV typename Store<ST>::T gen_value(int32_t s, float unit) {
+    if constexpr (ST == F64) return (double)s * (double)unit;
+    else if constexpr (ST == F32) return (float)s * unit;    // v_cvt_f32_i32: RNE
+    else {
+        const int32_t odd = ((s & 0xFF) ? (s | 0x100) : s) & ~0xFF;
+        const bool wide = (uint32_t)s + (1u << 24) > (2u << 24);
+        return Store<ST>::from_f32((float)(wide ? odd : s) * unit);
+    }
+}
 
 template <int ST>
-__global__ __launch_bounds__(256) void k_gen_matrix(int64_t n, uint64_t seed, double scale,
-                                                    typename Store<ST>::T* A, int64_t lda,
+__global__ __launch_bounds__(256) void k_gen_matrix(int64_t n, uint64_t seed, float unit, typename Store<ST>::T* A,
+                                                    int64_t lda, int vec, int64_t quads,
                                                     unsigned long long* rowsum) {
+    typedef typename Store<ST>::T T;
+    typedef T TV __attribute__((ext_vector_type(GEN_R)));
     uint32_t k0[10], k1[10];
     philox_keys(seed, k0, k1);
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * GEN_R;
     if (i >= n) return;
-    int64_t q0 = (int64_t)blockIdx.y * GEN_QUADS;
-    int64_t nq = (n + 3) / 4;
-    int64_t q1 = q0 + GEN_QUADS < nq ? q0 + GEN_QUADS : nq;
-    unsigned long long acc = 0;
+    const int64_t nq = (n + 3) / 4;
+    const int64_t q0 = (int64_t)blockIdx.y * quads, q1 = q0 + quads < nq ? q0 + quads : nq;
+    unsigned long long acc[GEN_R] = {};
+    const bool whole = vec && i + GEN_R <= n;
     for (int64_t q = q0; q < q1; ++q) {
-        uint32_t w[4];
-        philox4((uint32_t)i, (uint32_t)q, 0u, k0, k1, w);
+        uint32_t w[GEN_R][4];
+#pragma unroll
+        for (int r = 0; r < GEN_R; ++r) philox4((uint32_t)(i + r), (uint32_t)q, 0u, k0, k1, w[r]);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            int64_t j = 4 * q + t;
-            if (j < n) {
-                int32_t s = draw_offset(w[t]);
-                acc += (unsigned long long)(s < 0 ? -(int64_t)s : (int64_t)s);
-                if (A) A[i + j * lda] = Store<ST>::from_f64((double)s * scale);
+            const int64_t j = 4 * q + t;
+            if (j >= n) break;
+            TV v;
+#pragma unroll
+            for (int r = 0; r < GEN_R; ++r) {
+                const int32_t s = draw_offset(w[r][t]);
+                acc[r] += (uint32_t)(s < 0 ? 0u - (uint32_t)s : (uint32_t)s);
+                v[r] = gen_value<ST>(s, unit);
+            }
+            if (!A) continue;
+            if (whole) {
+                *(TV*)(A + i + j * lda) = v;
+            } else {
+#pragma unroll
+                for (int r = 0; r < GEN_R; ++r)
+                    if (i + r < n) A[i + r + j * lda] = v[r];
             }
         }
     }
-    atomicAdd(&rowsum[i], acc);
+#pragma unroll
+    for (int r = 0; r < GEN_R; ++r)
+        if (i + r < n) atomicAdd(&rowsum[i + r], acc[r]);
+}
+
+// row sums and the norm cleared
+__global__ __launch_bounds__(256) void k_gen_clear(unsigned long long* rowsum, int64_t n, unsigned long long* amax) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) rowsum[i] = 0;
+    if (i == 0) *amax = 0;
 }
 
 // The diagonal and the row 1-norms from the integer row sums S (held in the
@@ -69,7 +116,8 @@ __global__ __launch_bounds__(256) void k_gen_matrix(int64_t n, uint64_t seed, do
 //             host), ||A_i||_1 = (S - |s_ii|) 2^-32 + |A_ii|;
 //   uniform:  A_ii = s_ii 2^-31, ||A_i||_1 = S 2^-31.
 // ||A||_inf is the largest row norm: a maximum over the bit patterns of
-// non-negative doubles, which order like the values.
+// non-negative doubles, which order like the values (a_inf holds the pattern,
+// that is the value).
 template <int ST>
 __global__ __launch_bounds__(256) void k_gen_finalize(int64_t n, uint64_t seed, int kind, double shift,
                                                       typename Store<ST>::T* A, int64_t lda, double* diag,
@@ -100,11 +148,6 @@ __global__ __launch_bounds__(256) void k_gen_finalize(int64_t n, uint64_t seed, 
     atomicMax(amax, (unsigned long long)__double_as_longlong(l1));
 }
 
-__global__ void k_gen_anorm(double* a_inf) {
-    unsigned long long m = *(unsigned long long*)a_inf;
-    *a_inf = __longlong_as_double((long long)m);
-}
-
 __global__ __launch_bounds__(256) void k_gen_rhs(int64_t n, int64_t nrhs, uint64_t seed, double* B, int64_t ldb) {
     uint32_t k0[10], k1[10];
     philox_keys(seed, k0, k1);
@@ -127,16 +170,19 @@ static hipError_t gen_launch(int64_t n, int64_t nrhs, uint64_t seed, int kind, d
                              double* B, int64_t ldb, double* diag, double* row_l1, double* a_inf, hipStream_t s) {
     typedef typename Store<ST>::T T;
     hipError_t e;
-    if ((e = fill_u64(diag, n, 0, s))) return e;
-    if ((e = fill_u64(a_inf, 1, 0, s))) return e;
-    dim3 g((unsigned)((n + 255) / 256), (unsigned)(((n + 3) / 4 + GEN_QUADS - 1) / GEN_QUADS));
-    k_gen_matrix<ST><<<g, dim3(256), 0, s>>>(n, seed, gen_offscale(kind), (T*)A, lda, (unsigned long long*)diag);
+    const unsigned rows = (unsigned)((n + 255) / 256);
+    k_gen_clear<<<rows, 256, 0, s>>>((unsigned long long*)diag, n, (unsigned long long*)a_inf);
     if ((e = hipGetLastError())) return e;
-    k_gen_finalize<ST><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(n, seed, kind, shift, (T*)A, lda,
-                                                                               diag, row_l1,
-                                                                               (unsigned long long*)a_inf);
+    // about 4096 work-groups, 4 to 64 column quads per thread
+    const int64_t nq = (n + 3) / 4, gx = (n + 256 * GEN_R - 1) / (256 * GEN_R);
+    int64_t quads = nq * gx / 4096;
+    quads = quads < 4 ? 4 : quads > 64 ? 64 : quads;
+    const int vec = lda % GEN_R == 0 && (uintptr_t)A % (GEN_R * sizeof(T)) == 0;
+    k_gen_matrix<ST><<<dim3((unsigned)gx, (unsigned)((nq + quads - 1) / quads)), 256, 0, s>>>(
+        n, seed, (float)gen_offscale(kind), (T*)A, lda, vec, quads, (unsigned long long*)diag);
     if ((e = hipGetLastError())) return e;
-    k_gen_anorm<<<1, 1, 0, s>>>(a_inf);
+    k_gen_finalize<ST><<<rows, 256, 0, s>>>(n, seed, kind, shift, (T*)A, lda, diag, row_l1,
+                                            (unsigned long long*)a_inf);
     if ((e = hipGetLastError())) return e;
     if (nrhs > 0 && B) {
         k_gen_rhs<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(n, nrhs, seed, B, ldb);
@@ -226,18 +272,27 @@ __global__ __launch_bounds__(256) void k_regen_gemv(int64_t n, uint64_t seed, do
 }
 
 // R[i,r] = B[i,r] - (diag[i] X[i,r] + sum_c P[c][r][i]) (or without B: R = A X),
-// chunks summed in a fixed order so the result is run-to-run identical.
+// chunks summed in a fixed order so the result is run-to-run identical.  One
+// right-hand side per blockIdx.y, eight loads in flight (one thread taking all
+// eight right-hand sides in turn, a load at a time: 66 us at n = 8192).
 __global__ __launch_bounds__(256) void k_regen_reduce(int64_t n, int nr, int64_t nchunk, const double* __restrict__ P,
                                                       const double* __restrict__ diag, const double* __restrict__ X,
                                                       int64_t ldx, const double* __restrict__ B, int64_t ldb,
                                                       double* __restrict__ R, int64_t ldr) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int r = blockIdx.y;
     if (i >= n) return;
-    for (int r = 0; r < nr; ++r) {
-        double s = diag[i] * X[i + r * ldx];
-        for (int64_t c = 0; c < nchunk; ++c) s += P[(c * nr + r) * n + i];
-        R[i + r * ldr] = B ? B[i + r * ldb] - s : s;
+    double s = diag[i] * X[i + r * ldx];
+    const double* p = P + (int64_t)r * n + i;
+    const int64_t step = (int64_t)nr * n;
+    for (int64_t c = 0; c < nchunk; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(c + u < nchunk ? c + u : c) * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s = c + u < nchunk ? s + v[u] : s;
     }
+    R[i + r * ldr] = B ? B[i + r * ldb] - s : s;
 }
 
 int64_t regen_chunk_cols(int64_t n) {
@@ -246,8 +301,11 @@ int64_t regen_chunk_cols(int64_t n) {
     int64_t want = (2048 + row_tiles - 1) / row_tiles;
     int64_t cc = (n + want - 1) / want;
     cc = (cc + 63) / 64 * 64;
-    if (cc < 256) cc = 256;
-    return cc;
+    // small sizes take shorter chunks, or too few work-groups are left (n =
+    // 600: 9 of 256 columns, 20 us); from n = 4096 on 256 columns and fewer
+    // partial sums
+    const int64_t least = n < 2048 ? 64 : n < 4096 ? 128 : 256;
+    return cc < least ? least : cc;
 }
 
 size_t regen_partial_bytes(int64_t n, int nr) {
@@ -275,7 +333,7 @@ hipError_t regen_matvec(int64_t n, uint64_t seed, int kind, const double* diag, 
         }
         hipError_t e = hipGetLastError();
         if (e) return e;
-        k_regen_reduce<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(
+        k_regen_reduce<<<dim3((unsigned)((n + 255) / 256), w), dim3(256), 0, s>>>(
             n, w, nchunk, P, diag, X + r0 * ldx, ldx, B ? B + r0 * ldb : nullptr, ldb, R + r0 * ldr, ldr);
         if ((e = hipGetLastError())) return e;
         r0 += w;
