@@ -302,6 +302,7 @@ static int solve_batch(int64_t n, uint64_t seed, int kind, const PrecPlan& pp, c
     int status[RHS_BATCH], done[RHS_BATCH] = {}, a[RHS_BATCH], kd[RHS_BATCH];
     double eta[RHS_BATCH] = {};
     for (int r = 0; r < R; ++r) status[r] = MXP_OK;
+    HIPCHK(prec_reset(Wp, n, R, s));
     HIPCHK(prec_apply(pp, B, ldb, X, ldx, R, Wp, s));   // x0 = M^-1 b
     for (;;) {
         HIPCHK(regen_matvec(n, seed, kind, diag, X, ldx, R, B, ldb, Rr, n, P, s));
@@ -341,8 +342,7 @@ static int solve_batch(int64_t n, uint64_t seed, int kind, const PrecPlan& pp, c
             // w = M^-1 A v_j for every right-hand side
             HIPCHK(regen_matvec(n, seed, kind, diag, V + (int64_t)j * R * n, n, R, nullptr, n, W, n, P, s));
             HIPCHK(prec_apply(pp, W, n, W, n, R, Wp, s));
-            HIPCHK(gm_arnoldi(n, R, V, j, W, part, H, ldh, act, s));
-            HIPCHK(gm_givens(R, j, H, ldh, cs, sn, g, xnorm, 1, tau, flag, act, s));
+            HIPCHK(gm_arnoldi(n, R, V, j, W, part, H, ldh, cs, sn, g, xnorm, 1, tau, flag, act, s));
             int fl[RHS_BATCH];
             HIPCHK(hipMemcpyAsync(fl, flag, (size_t)R * 4, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
@@ -357,7 +357,9 @@ static int solve_batch(int64_t n, uint64_t seed, int kind, const PrecPlan& pp, c
             if (kd[r] == 0) { status[r] = MXP_ENOCONV; done[r] = 1; }
         }
     }
-    int worst = MXP_OK;
+    int worst = MXP_OK, perr = 0;
+    HIPCHK(prec_err_read(Wp, n, R, &perr, s));
+    if (perr) return set_err(MXP_EHIP, "mxp_solve_ir: a wait of the block substitution expired%s", "");
     for (int r = 0; r < R; ++r) {
         if (status[r] == MXP_OK && !(eta[r] < tol)) status[r] = MXP_ECRITERION;
         rep[r].iters = it[r];
@@ -382,9 +384,6 @@ extern "C" int mxp_solve_ir(int64_t n, int64_t nb, int update, int store, uint64
     if (work_bytes < L.total) return set_err(MXP_EWORKSPACE, "mxp_solve_ir: work buffer too small%s", "");
     hipStream_t s = (hipStream_t)stream;
     PrecPlan pp = make_prec(n, nb, store, LU, lda, aux);
-    const int Rmax = (int)std::min<int64_t>(nrhs, RHS_BATCH);
-    double* Wp = (double*)((char*)work + L.Wp);
-    HIPCHK(prec_err_reset(Wp, n, Rmax, s));
     int worst = MXP_OK;
     for (int64_t r0 = 0; r0 < nrhs; r0 += RHS_BATCH) {
         const int R = (int)std::min<int64_t>(nrhs - r0, RHS_BATCH);
@@ -393,9 +392,6 @@ extern "C" int mxp_solve_ir(int64_t n, int64_t nb, int update, int store, uint64
         if (rc < 0) return rc;
         if (rc > worst) worst = rc;
     }
-    int perr = 0;
-    HIPCHK(prec_err_read(Wp, n, Rmax, &perr, s));
-    if (perr) return set_err(MXP_EHIP, "mxp_solve_ir: a wait of the block substitution expired%s", "");
     return worst;
 }
 
@@ -447,7 +443,7 @@ extern "C" int mxp_apply_prec(int64_t n, int64_t nb, int update, int store, cons
         return set_err(MXP_EWORKSPACE, "mxp_apply_prec: work buffer too small%s", "");
     PrecPlan pp = make_prec(n, nb, store, LU, lda, aux);
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(prec_err_reset((double*)work, n, (int)nrhs, s));
+    HIPCHK(prec_reset((double*)work, n, (int)nrhs, s));
     HIPCHK(prec_apply(pp, V, ldv, Z, ldz, (int)nrhs, (double*)work, s));
     int perr = 0;
     HIPCHK(prec_err_read((double*)work, n, (int)nrhs, &perr, s));

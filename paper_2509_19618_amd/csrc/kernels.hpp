@@ -207,11 +207,12 @@ struct PrecPlan {
 };
 // Z = U^-1 L^-1 S V for nr columns (V may alias Z); W: prec_work_bytes(n, nr)
 // of scratch.  A wait of the substitution kernels that expires sets an error
-// word in W (cleared by prec_err_reset, read by prec_err_read).
+// word in W (read by prec_err_read); prec_reset clears it and the flags, once
+// before the applies with this n and nr.
 size_t prec_work_bytes(int64_t n, int nr);
 hipError_t prec_apply(const PrecPlan& p, const double* V, int64_t ldv, double* Z, int64_t ldz, int nr, double* W,
                       hipStream_t s);
-hipError_t prec_err_reset(double* W, int64_t n, int nr, hipStream_t s);
+hipError_t prec_reset(double* W, int64_t n, int nr, hipStream_t s);
 hipError_t prec_err_read(double* W, int64_t n, int nr, int* err, hipStream_t s);
 
 // GMRES steps for nr right-hand sides in lockstep (solve.hip).  V holds the
@@ -223,10 +224,10 @@ hipError_t gm_norms(int64_t n, int nr, const double* X, int64_t ldx, double* out
                     const int* act, hipStream_t s);
 hipError_t gm_start(int64_t n, int nr, const double* Z, const double* sc, int sc_stride, double* V, double* g,
                     int ldg, const int* act, hipStream_t s);
-hipError_t gm_arnoldi(int64_t n, int nr, double* V, int k, double* W, double* part, double* H, int ldh,
-                      const int* act, hipStream_t s);
-hipError_t gm_givens(int nr, int k, double* H, int ldh, double* cs, double* sn, double* g, const double* sc,
-                     int sc_stride, double tau, int* flag, const int* act, hipStream_t s);
+// column k: the Arnoldi step and its rotation (flag[r]: the inner stopping test)
+hipError_t gm_arnoldi(int64_t n, int nr, double* V, int k, double* W, double* part, double* H, int ldh, double* cs,
+                      double* sn, double* g, const double* sc, int sc_stride, double tau, int* flag, const int* act,
+                      hipStream_t s);
 hipError_t gm_update(int64_t n, int nr, const double* H, int ldh, const double* g, double* y, const int* kdim,
                      const double* V, double* X, int64_t ldx, hipStream_t s);
 hipError_t set_i32(int* dst, int n, const int* src_dev, hipStream_t s);

@@ -18,13 +18,6 @@ namespace mxp {
 __host__ __device__ static inline int64_t rup(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
 // ================================================================ preconditioner
-__global__ __launch_bounds__(256) void k_scale_rows(int64_t n, const double* __restrict__ S, const double* __restrict__ V,
-                                                    int64_t ldv, double* __restrict__ W, int nr) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    for (int r = 0; r < nr; ++r) W[i + r * n] = S[i] * V[i + r * ldv];
-}
-
 // ---------------------------------------------------------------- block substitution
 // One kernel per triangular solve, every right-hand side at once (each
 // right-hand side with its own flags).  Work-group = one strip of TS rows;
@@ -147,10 +140,10 @@ template <int ST, bool LOWER>
 __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const typename Store<ST>::T* __restrict__ A,
                                               int64_t lda, int vec, const float* __restrict__ inv_all,
                                               const float* __restrict__ lsc, int64_t nstrips32,
-                                              const double* __restrict__ rhs, int64_t ld_rhs,
-                                              double* __restrict__ tbuf, double* __restrict__ out, int64_t ld_out,
-                                              unsigned* flags, int64_t flag_stride, unsigned* ticket,
-                                              int* err) {
+                                              const double* __restrict__ scale, const double* __restrict__ rhs,
+                                              int64_t ld_rhs, double* __restrict__ tbuf, double* __restrict__ out,
+                                              int64_t ld_out, unsigned* flags, unsigned* other, int64_t flag_stride,
+                                              unsigned* ticket, unsigned* other_ticket, int* err) {
     typedef typename Store<ST>::T T;
     constexpr int RPL = 16 / (int)sizeof(T);   // rows per lane: one 16-byte load
     constexpr int RG = TS / RPL;               // lanes per column
@@ -173,6 +166,14 @@ __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const t
     out += py * ld_out;
     tbuf += py * n;
     flags += py * flag_stride;
+    other += py * flag_stride;
+    // the flags and the counter of the other triangular solve, which is not
+    // running, cleared for its next launch
+    if (tid == 0) {
+        __hip_atomic_store(other + px, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (px < J) __hip_atomic_store(other + S + px, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (pos == 0) __hip_atomic_store(other_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     // the substitution's diagonal blocks (size db, a multiple of nb: gb factor
     // blocks each) are the dataflow's steps; the off-diagonal products go by
     // factor block (each with its own strip factors)
@@ -187,7 +188,8 @@ __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const t
         const int64_t kb = n - b * db < db ? n - b * db : db;
         return (unsigned)((kb + TS - 1) / TS);
     };
-    if (tid < TS) w[tid] = (tid < rows) ? rhs[r0 + tid] : 0.0;
+    // the forward solve starts from S v (row scaling)
+    if (tid < TS) w[tid] = (tid < rows) ? (LOWER ? scale[r0 + tid] * rhs[r0 + tid] : rhs[r0 + tid]) : 0.0;
     // The ragged last strip takes the same 16-byte loads: with 16-byte aligned
     // columns the rows up to lda may be read (its panel columns lie before the
     // last one), the lanes past lda re-read the strip's first rows, and the
@@ -409,16 +411,19 @@ static int64_t trsv_flag_words(int64_t n) {
 }
 
 size_t prec_work_bytes(int64_t n, int nr) {
-    // S V, forward solution, block right-hand sides (n x nr each), flags, error word
-    return (size_t)(3 * n * nr) * 8 + (size_t)(trsv_flag_words(n) * nr) * 4 + 256;
+    // forward solution, block right-hand sides (n x nr each), flags, error word
+    return (size_t)(2 * n * nr) * 8 + (size_t)(trsv_flag_words(n) * nr) * 4 + 256;
 }
 
 static int* prec_err_word(double* W, int64_t n, int nr) {
-    return (int*)((unsigned*)(W + 3 * n * nr) + trsv_flag_words(n) * nr);
+    return (int*)((unsigned*)(W + 2 * n * nr) + trsv_flag_words(n) * nr);
 }
 
-hipError_t prec_err_reset(double* W, int64_t n, int nr, hipStream_t s) {
-    k_zero_u32<<<1, 256, 0, s>>>((unsigned*)prec_err_word(W, n, nr), 1);
+// flags, counters and the error word: once before the applies with this n, nr
+// (each solve then clears the other's)
+hipError_t prec_reset(double* W, int64_t n, int nr, hipStream_t s) {
+    const int64_t words = trsv_flag_words(n) * nr + 1;
+    k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>((unsigned*)(W + 2 * n * nr), words);
     return hipGetLastError();
 }
 
@@ -436,24 +441,20 @@ static hipError_t prec_typed(const PrecPlan& p, const double* V, int64_t ldv, do
     const int64_t J = (n + nb - 1) / nb;
     const int64_t nstrips32 = (n + 31) / 32;
     const int64_t S = (n + TS - 1) / TS;
-    double* R = W;                 // S V, nr columns (ld n)
-    double* Y = W + n * nr;        // forward solutions
+    double* Y = W;                 // forward solutions, nr columns (ld n)
     double* Tb = Y + n * nr;       // block right-hand sides
     unsigned* flags = (unsigned*)(Tb + n * nr);
     const int64_t fw = trsv_flag_words(n);
     int* err = prec_err_word(W, n, nr);
     const int vec = ((p.lda * (int64_t)sizeof(T)) % 16 == 0 && ((uintptr_t)p.A) % 16 == 0) ? 1 : 0;
-    hipEvent_t pt = prof::begin(prof::PREC, s);
-    k_scale_rows<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, p.rowscale, V, ldv, R, nr);
-    k_zero_u32<<<(unsigned)((fw * nr + 255) / 256), 256, 0, s>>>(flags, fw * nr);
+    unsigned *fl = flags, *fu = flags + S + J, *tk = flags + 2 * (S + J);
     const int db = (int)prec_block(nb);
-    k_trsv<ST, true><<<dim3((unsigned)S, (unsigned)nr), 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec,
-                                                                     p.linv_full, p.lsc, nstrips32, R, n, Tb, Y, n,
-                                                                     flags, fw, flags + 2 * (S + J), err);
-    k_trsv<ST, false><<<dim3((unsigned)S, (unsigned)nr), 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec,
-                                                                      p.uinv_full, nullptr, nstrips32, Y, n, Tb, Z,
-                                                                      ldz, flags + S + J, fw, flags + 2 * (S + J) + 1,
-                                                                      err);
+    const dim3 grid((unsigned)S, (unsigned)nr);
+    hipEvent_t pt = prof::begin(prof::PREC, s);
+    k_trsv<ST, true><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec, p.linv_full, p.lsc, nstrips32,
+                                          p.rowscale, V, ldv, Tb, Y, n, fl, fu, fw, tk, tk + 1, err);
+    k_trsv<ST, false><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec, p.uinv_full, nullptr, nstrips32,
+                                           nullptr, Y, n, Tb, Z, ldz, fu, fl, fw, tk + 1, tk, err);
     prof::end(pt, prof::PREC, s, 2.0 * n * (double)n * nr, (double)n * n * sizeof(T) + 8.0 * n * nb);
     return hipGetLastError();
 }
@@ -579,10 +580,8 @@ __global__ __launch_bounds__(256) void k_start_basis(int64_t n, const double* __
 // Column k of each active H_r (column-major, ldh = m + 1): apply rotations
 // 0..k-1, form rotation k that zeroes H[k+1][k], rotate g.  flag[r] = 1 when
 // |g[k+1]| <= tau ||x_r|| or H[k+1][k] was 0 (exact breakdown).
-__global__ void k_givens(int nr, int k, double* H, int ldh, double* cs, double* sn, double* g,
-                         const double* sc, int sc_stride, double tau, int* flag, const int* __restrict__ act) {
-    const int r = threadIdx.x;
-    if (r >= nr || !act[r]) return;
+MXP_DEV void givens_column(int r, int k, double* H, int ldh, double* cs, double* sn, double* g, const double* sc,
+                           int sc_stride, double tau, int* flag) {
     double* h = H + (int64_t)r * ldh * (ldh - 1) + (int64_t)k * ldh;
     double* c_ = cs + r * ldh;
     double* s_ = sn + r * ldh;
@@ -605,6 +604,62 @@ __global__ void k_givens(int nr, int k, double* H, int ldh, double* cs, double* 
     gr[k] = c * gk;
     const double xnorm = sc[r * sc_stride];
     flag[r] = (fabs(gr[k + 1]) <= tau * xnorm || hsub == 0.0) ? 1 : 0;
+}
+
+__global__ void k_givens(int nr, int k, double* H, int ldh, double* cs, double* sn, double* g,
+                         const double* sc, int sc_stride, double tau, int* flag, const int* __restrict__ act) {
+    const int r = threadIdx.x;
+    if (r < nr && act[r]) givens_column(r, k, H, ldh, cs, sn, g, sc, sc_stride, tau, flag);
+}
+
+// A whole Arnoldi step and its rotation for sizes whose sums are one block's
+// (n <= 4096): k_dot_part, the k_mgs, k_normalize and k_givens of column k in
+// one launch, the new vector in registers (same order of every sum).  At these
+// sizes a launch (4-5 us) costs more than its work: n = 600, 100 us per step
+// in k + 4 launches before.
+constexpr int ONE_U = 16;      // elements per thread
+__global__ __launch_bounds__(256) void k_arnoldi_one(int64_t n, int nr, double* __restrict__ V, int k,
+                                                     const double* __restrict__ W, double* H, int ldh, double* cs,
+                                                     double* sn, double* g, const double* sc, int sc_stride,
+                                                     double tau, int* flag, const int* __restrict__ act) {
+    __shared__ double red[4];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    if (!act[r]) return;
+    double* Hk = H + (int64_t)r * ldh * (ldh - 1) + (int64_t)k * ldh;
+    const double* w = W + (int64_t)r * n;
+    auto vec = [&](int j) -> double* { return V + ((int64_t)j * nr + r) * n; };
+    double x[ONE_U], v[ONE_U], sum = 0.0;
+    auto load = [&](const double* p, double (&d)[ONE_U]) {
+#pragma unroll
+        for (int u = 0; u < ONE_U; ++u) {
+            const int i = tid + 256 * u;
+            d[u] = i < n ? p[i] : 0.0;
+        }
+    };
+    load(w, x);
+    load(vec(0), v);
+#pragma unroll
+    for (int u = 0; u < ONE_U; ++u) sum += v[u] * x[u];
+    double h = block_sum(sum, red);
+    for (int j = 0; j <= k; ++j) {
+        if (tid == 0) Hk[j] = h;
+#pragma unroll
+        for (int u = 0; u < ONE_U; ++u) x[u] -= h * v[u];
+        if (j < k) load(vec(j + 1), v);
+        sum = 0.0;
+#pragma unroll
+        for (int u = 0; u < ONE_U; ++u) sum += (j < k ? v[u] : x[u]) * x[u];
+        h = block_sum(sum, red);
+    }
+    h = sqrt(h);
+    if (tid == 0) Hk[k + 1] = h;
+    double* vk = vec(k + 1);
+#pragma unroll
+    for (int u = 0; u < ONE_U; ++u) {
+        const int i = tid + 256 * u;
+        if (i < n) vk[i] = (h > 0.0) ? x[u] / h : 0.0;
+    }
+    if (tid == 0) givens_column(r, k, H, ldh, cs, sn, g, sc, sc_stride, tau, flag);
 }
 
 // y_r = R_r^-1 g_r (R_r = rotated H_r[0:k_r, 0:k_r]), k_r = kdim[r]
@@ -656,9 +711,14 @@ hipError_t gm_start(int64_t n, int nr, const double* Z, const double* sc, int sc
     return hipGetLastError();
 }
 
-hipError_t gm_arnoldi(int64_t n, int nr, double* V, int k, double* W, double* part, double* H, int ldh,
-                      const int* act, hipStream_t s) {
+hipError_t gm_arnoldi(int64_t n, int nr, double* V, int k, double* W, double* part, double* H, int ldh, double* cs,
+                      double* sn, double* g, const double* sc, int sc_stride, double tau, int* flag, const int* act,
+                      hipStream_t s) {
     const int nbk = red_blocks(n);
+    if (nbk == 1 && n <= 256 * ONE_U) {
+        k_arnoldi_one<<<nr, 256, 0, s>>>(n, nr, V, k, W, H, ldh, cs, sn, g, sc, sc_stride, tau, flag, act);
+        return hipGetLastError();
+    }
     const int64_t chunk = (n + nbk - 1) / nbk;
     k_dot_part<<<dim3(nbk, nr), 256, 0, s>>>(n, chunk, V, n, W, n, part, act);
     for (int j = 0; j <= k; ++j) {
@@ -667,11 +727,6 @@ hipError_t gm_arnoldi(int64_t n, int nr, double* V, int k, double* W, double* pa
         k_mgs<<<dim3(nbk, nr), 256, 0, s>>>(n, chunk, nr, V, j, j == k, W, pin, pout, H, ldh, k, act);
     }
     k_normalize<<<dim3(nbk, nr), 256, 0, s>>>(n, chunk, nr, part + ((k + 1) & 1) * 256 * nr, W, V, k, H, ldh, act);
-    return hipGetLastError();
-}
-
-hipError_t gm_givens(int nr, int k, double* H, int ldh, double* cs, double* sn, double* g, const double* sc,
-                     int sc_stride, double tau, int* flag, const int* act, hipStream_t s) {
     k_givens<<<1, 64, 0, s>>>(nr, k, H, ldh, cs, sn, g, sc, sc_stride, tau, flag, act);
     return hipGetLastError();
 }

@@ -103,3 +103,30 @@ def test_ragged_last_strip_of_the_substitution(n, nb, store, lda):
         fac.LU[:, n:] = float("nan")
         out.append(mxp.mxp_apply_prec(fac, prob.B))
     assert torch.equal(out[0], out[1])
+
+
+# rows in groups of four per thread: whole, ragged, and columns that are not
+# aligned for the group's store give the same entries, row norms and diagonal
+@pytest.mark.parametrize("n", [1, 3, 130, 1027])
+@pytest.mark.parametrize("store", ["f16", "bf16", "f32", "f64"])
+def test_generator_does_not_depend_on_the_leading_dimension(n, store):
+    print("generate", n, store, flush=True)
+    a = mxp.mxp_generate(n, 1, 77, store=store, kind=mxp.GEN_UNIFORM)
+    b = mxp.mxp_generate(n, 1, 77, store=store, kind=mxp.GEN_UNIFORM, lda=n + 1 - n % 2)
+    assert torch.equal(mxp.as_matrix(a.A, n), mxp.as_matrix(b.A, n))
+    assert torch.equal(a.diag, b.diag) and torch.equal(a.row_l1, b.row_l1)
+    assert float(a.a_inf) == float(a.row_l1.max())
+
+
+# more right-hand sides than one pass takes (16 and 4), at a size whose sums
+# are one block's and one where they are not; each solution as if alone
+@pytest.mark.parametrize("n", [700, 4100])
+def test_many_right_hand_sides(n):
+    print("rhs batches", n, flush=True)
+    prob = mxp.mxp_generate(n, 20, 31, store="bf16")
+    fac = mxp.mxp_factor(prob, 128, "bf16")
+    res = mxp.mxp_solve_ir(prob, fac)
+    assert res.code == 0 and all(e < 16 for e in res.eta)
+    for r in (0, 15, 16, 19):
+        one = mxp.mxp_solve_ir(prob, fac, B=prob.B[r:r + 1].contiguous())
+        assert float((res.X[r] - one.X[0]).abs().max()) <= 1e-12 * float(one.X[0].abs().max())
