@@ -20,6 +20,8 @@
 // Work-groups are dispatched round-robin over the 8 XCDs; the tile order
 // gives every XCD a contiguous range of tiles, walked in groups of 8 tile
 // rows so that the operand panels in flight on an XCD fit its L2.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -109,10 +111,7 @@ template <> struct Quad<BF16> {
 // MFMA loop; TMv = 128 gives twice as many tiles for small trailing matrices.
 constexpr int TN = 128;
 constexpr int GBK = 64;            // K bytes per stage
-#ifndef MXP_NBUF
-#define MXP_NBUF 3
-#endif
-constexpr int NBUF = MXP_NBUF;     // stages in LDS: two copies in flight while one is read
+constexpr int NBUF = 3;             // stages in LDS: two copies in flight while one is read
 constexpr int GCH = GBK / 16;      // 16-byte chunks per operand row
 constexpr int SB = TN * GBK;       // bytes of one B stage
 constexpr int GGROUP = 8;          // tile rows per group in the tile order
@@ -121,18 +120,13 @@ constexpr int GGROUP = 8;          // tile rows per group in the tile order
 #endif
 constexpr int GGROUP2 = MXP_GGROUP2;   // the same for two-segment updates (twice the operand bytes per tile row)
 
-// wait_vm<y NIS + (c ? NC : 0)> for a wave-uniform y <= Y
-template <int NIS, int NC, int Y> MXP_DEV void wait_case(int y, bool c) {
-    if constexpr (Y >= 0) {
-        if (y == Y) {
-            if (c) wait_vm<Y * NIS + NC>();
-            else wait_vm<Y * NIS>();
-            return;
-        }
-        wait_case<NIS, NC, Y - 1>(y, c);
-    }
+// a work-group barrier after this wave's LDS reads; copies into LDS may be in flight
+MXP_DEV void stage_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x3 << 14));   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
-
 
 // c - a d with d a power of two (a d exact): one rounding to FP32; the
 // rounding to the storage format stays a separate step in every epilogue
@@ -211,11 +205,16 @@ struct GemmGroup {
 // k-step reads its fragments from LDS (the other work-group on the SIMD
 // covers their latency).  Epilogue, full tiles with 16-bit C: the freed LDS
 // holds the C tile (read and written with coalesced 16-byte accesses, TMv*2
-// bytes per column), updated in place in the MFMA layout; the first half of
-// the tile is loaded into registers at the first stage, so that its HBM
-// reads overlap the MFMA loop (the whole tile would not fit beside the
-// accumulators), the second half in the epilogue.  Other tiles update C
-// directly with guarded accesses.
+// bytes per column), updated in place in the MFMA layout; the tile is loaded
+// into registers behind the last two stages.  Other tiles update C directly
+// with guarded accesses.
+//
+// Bound: C traffic plus products; doubling K from 1024 to 2048 adds 421 us at
+// 16384 x 16384 (1300 TFLOP/s), the remaining 230 us of the 652 us at K = 512 +
+// 512 are what its 1 GB of C takes at the 4.8 TB/s of a large copy.  Measured
+// against the pipeline that waited for every copy at each stage: 16384 x 16384,
+// K = 512 + 512, FP16 771 -> 842 TFLOP/s, BF16 754 -> 806, FP8 1385 -> 1439;
+// 31744 x 31744 FP16 756 -> 816.
 template <int OP, int ST, int TMv>
 __global__ __launch_bounds__(256, 2) void k_gemm_update(const GemmGroup grp) {
     typedef typename Store<ST>::T CT;
@@ -232,7 +231,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_update(const GemmGroup grp) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* sA = lds;
     char* sB = lds + NBUF * SA;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     // work-group j of XCD x (x = blockIdx % 8) takes tile x*per_xcd + j of its XCD's contiguous range
     const int xcd = (int)(blockIdx.x % 8);
@@ -264,29 +263,36 @@ __global__ __launch_bounds__(256, 2) void k_gemm_update(const GemmGroup grp) {
     const char* gB2 = G.K2 ? G.Bq2 + col0 * Kb2 : gB1;
     const int nst1 = (int)(Kb1 / GBK);
     const int nst = nst1 + (int)(Kb2 / GBK);
+    static_assert(NBUF >= 2, "a stage is copied while another is read");
     const int lr = lane & 31, lh = lane >> 5;
     const int l_row = lane / GCH, l_pch = lane % GCH;
-    auto issue = [&](int st) {
-        const int buf = st % NBUF;
-        const bool s2 = st >= nst1;                           // wave-uniform
-        const char* gA = s2 ? gA2 : gA1;
-        const char* gB = s2 ? gB2 : gB1;
-        const int64_t Kbytes = s2 ? Kb2 : Kb1;
-        const int64_t ko = (int64_t)(s2 ? st - nst1 : st) * GBK;
+    // this lane's offset, in the operand rows of the tile, of every copy
+    // instruction of a stage: row j RPI + l_row of the slice, logical chunk
+    // l_pch ^ key (the one kept at this lane's slot); the stage's first byte
+    // is wave-uniform
+    uint32_t off[NIS];
+    auto offsets = [&](int Kbytes) {
 #pragma unroll
-        for (int i = 0; i < NIA; ++i) {
-            const int j = wave * NIA + i;                     // 1 KB slice of the stage
-            const int row = j * RPI + l_row;
-            const int lch = l_pch ^ swz_key(row);            // logical chunk stored at this lane's slot
-            dma16(gA + (int64_t)row * Kbytes + ko + lch * 16, sA + buf * SA + j * 1024);
+        for (int i = 0; i < NIS; ++i) {
+            const int row = (i < NIA ? wave * NIA + i : wave * NIB + i - NIA) * RPI + l_row;
+            off[i] = (uint32_t)(row * Kbytes + (l_pch ^ swz_key(row)) * 16);
+        }
+    };
+    offsets((int)Kb1);
+    const char *cA = gA1, *cB = gB1;
+    // the copies of stage st (stages in order), into buffer buf
+    auto issue = [&](int st, int buf) {
+        if (st == nst1) {
+            cA = gA2;
+            cB = gB2;
+            offsets((int)Kb2);
         }
 #pragma unroll
-        for (int i = 0; i < NIB; ++i) {
-            const int j = wave * NIB + i;
-            const int row = j * RPI + l_row;
-            const int lch = l_pch ^ swz_key(row);
-            dma16(gB + (int64_t)row * Kbytes + ko + lch * 16, sB + buf * SB + j * 1024);
-        }
+        for (int i = 0; i < NIA; ++i) dma16(cA + off[i], sA + buf * SA + (wave * NIA + i) * 1024);
+#pragma unroll
+        for (int i = 0; i < NIB; ++i) dma16(cB + off[NIA + i], sB + buf * SB + (wave * NIB + i) * 1024);
+        cA += GBK;
+        cB += GBK;
     };
     f16v acc[NA][2];
 #pragma unroll
@@ -304,42 +310,34 @@ __global__ __launch_bounds__(256, 2) void k_gemm_update(const GemmGroup grp) {
     constexpr int NIT = TN / 4 / CPI;      // instructions per wave
     const int lc = lane / LPC, lo = (lane % LPC) * 16;
     i4v xv[NIT];                           // the C tile, 16 bytes per register quad
+    // loaded behind the last stages' products; half of it in the epilogue for
+    // FP8, whose fragments take twice the registers
+    constexpr int NIT1 = OP == F8 ? NIT / 2 : NIT;
+    auto load_c = [&](auto I0, auto I1) {
 #pragma unroll
-    for (int st = 0; st < NBUF - 1; ++st)
-        if (st < nst) issue(st);
-    for (int st = 0; st < nst; ++st) {
-        // stage st has landed when at most the younger stages' copies are
-        // outstanding, and the C loads while they are younger than stage st
-        // (issued at stage 0, after the copies of stages up to NBUF - 1)
-        const int younger = (NBUF - 2) < (nst - 1 - st) ? (NBUF - 2) : (nst - 1 - st);
-        const bool cy = cpre && st > 0 && st <= NBUF - 1;
-        wait_case<NIS, NIT / 2, NBUF - 2>(younger, cy);
-        __syncthreads();                  // stage st visible to all; stage st-1's buffer free
-        if (st + NBUF - 1 < nst) issue(st + NBUF - 1);
-        if (cpre && st == 0) {
+        for (int it = decltype(I0)::value; it < decltype(I1)::value; ++it) {
+            const int c = (wave * NIT + it) * CPI + lc;
+            xv[it] = __builtin_nontemporal_load((const i4v*)((const char*)(C + row0 + (col0 + c) * ldc) + lo));
+        }
+    };
+    // first stage of the second segment: the first segment's sums to its scale
+    auto rescale = [&]() {
 #pragma unroll
-            for (int it = 0; it < NIT / 2; ++it) {
-                const int c = (wave * NIT + it) * CPI + lc;
-                xv[it] = __builtin_nontemporal_load((const i4v*)((const char*)(C + row0 + (col0 + c) * ldc) + lo));
+        for (int a = 0; a < NA; ++a) {
+            const int64_t ra = (row0 + wm * WR + a * 32) / 32;
+            const float fa = G.inv_sa[ra] / G.inv_sa2[ra];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int64_t cb = (col0 + wn * 64 + b * 32) / 32;
+                const float f = fa * (G.inv_sb[cb] / G.inv_sb2[cb]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][b][r] *= f;
             }
         }
-        if (st == nst1 && st > 0) {
-            // first stage of the second segment: the first segment's sums to its scale
-#pragma unroll
-            for (int a = 0; a < NA; ++a) {
-                const int64_t ra = (row0 + wm * WR + a * 32) / 32;
-                const float fa = G.inv_sa[ra] / G.inv_sa2[ra];
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const int64_t cb = (col0 + wn * 64 + b * 32) / 32;
-                    const float f = fa * (G.inv_sb[cb] / G.inv_sb2[cb]);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[a][b][r] *= f;
-                }
-            }
-        }
-        const char* A0 = sA + (st % NBUF) * SA;
-        const char* B0 = sB + (st % NBUF) * SB;
+    };
+    auto compute = [&](int buf) {
+        const char* A0 = sA + buf * SA;
+        const char* B0 = sB + buf * SB;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             FT ac[NA], bc[2];
@@ -353,15 +351,49 @@ __global__ __launch_bounds__(256, 2) void k_gemm_update(const GemmGroup grp) {
 #pragma unroll
                 for (int b = 0; b < 2; ++b) acc[a][b] = Frag<OP>::mma(ac[a], bc[b], acc[a][b]);
         }
+    };
+    // Stage st: its copies have landed (the next stage's NIS may be in flight),
+    // everyone is past stage st - 1, whose buffer takes the copies of stage
+    // st + 2.  stage_barrier is not __syncthreads: before that the compiler
+    // puts a wait for every copy in flight, which left the later stage's no
+    // time.
+    static_assert(NBUF == 3, "two stages are in flight while one is read");
+    issue(0, 0);
+    if (nst > 1) issue(1, 1);
+    int buf = 0, st = 0;                   // stage st is in buffer buf
+    for (; st + 2 < nst; ++st) {
+        wait_vm<NIS>();
+        stage_barrier();
+        issue(st + 2, buf == 0 ? 2 : buf - 1);
+        if (st == nst1) rescale();
+        compute(buf);
+        buf = buf == 2 ? 0 : buf + 1;
     }
+    // The last two stages issue no copies; the C tile is loaded here, behind
+    // their products (at the first stage its loads would be waited for with
+    // the copies issued after them)
+    if (nst > 1) {
+        wait_vm<NIS>();
+        stage_barrier();
+        if (cpre) load_c(std::integral_constant<int, 0>(), std::integral_constant<int, NIT1>());
+        if (st == nst1) rescale();
+        compute(buf);
+        buf = buf == 2 ? 0 : buf + 1;
+        ++st;
+    }
+    if (cpre && nst > 1) {
+        wait_vm<NIT1>();
+    } else {
+        wait_vm<0>();
+    }
+    stage_barrier();
+    if (cpre && nst == 1) load_c(std::integral_constant<int, 0>(), std::integral_constant<int, NIT1>());
+    if (st == nst1) rescale();
+    compute(buf);
     if constexpr (sizeof(CT) == 2) {
         if (full) {
-            __syncthreads();                       // operand buffers no longer read
-#pragma unroll
-            for (int it = NIT / 2; it < NIT; ++it) {
-                const int c = (wave * NIT + it) * CPI + lc;
-                xv[it] = __builtin_nontemporal_load((const i4v*)((const char*)(C + row0 + (col0 + c) * ldc) + lo));
-            }
+            load_c(std::integral_constant<int, NIT1>(), std::integral_constant<int, NIT>());
+            stage_barrier();                       // operand buffers no longer read
 #pragma unroll
             for (int it = 0; it < NIT; ++it) {
                 const int c = (wave * NIT + it) * CPI + lc;
