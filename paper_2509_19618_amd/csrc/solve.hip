@@ -9,6 +9,8 @@
 // their power-of-two factor); one dataflow kernel per triangular solve.
 // Modified Gram-Schmidt, Givens rotations, the least-squares solve and the
 // basis update are deterministic (fixed reduction orders).
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "prof.hpp"
@@ -60,107 +62,89 @@ MXP_DEV double get_shared(const double* p) { return __hip_atomic_load(p, __ATOMI
 // v, treated as written at this point: arithmetic on prefetched registers
 // cannot move above it (the compiler would otherwise unpack a load's result
 // right after issuing it, which waits for the load)
-MXP_DEV void pin4(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
-MXP_DEV void pin4f(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+MXP_DEV void pin4(u32x4v& v) { asm volatile("" : "+v"(v)); }
+MXP_DEV void pin4f(f32x4v& v) { asm volatile("" : "+v"(v)); }
 
 // element k of a 16-byte vector of storage values, taken from its 32-bit
 // words (no access through a cast pointer, which would split the vector at
 // its load)
-template <int ST> MXP_DEV float u4_elem(const uint4& v, int k);
-template <> MXP_DEV float u4_elem<F32>(const uint4& v, int k) {
+template <int ST> MXP_DEV float u4_elem(const u32x4v& v, int k);
+template <> MXP_DEV float u4_elem<F32>(const u32x4v& v, int k) {
     const unsigned w[4] = {v.x, v.y, v.z, v.w};
     return __uint_as_float(w[k]);
 }
-template <> MXP_DEV float u4_elem<F16>(const uint4& v, int k) {
+template <> MXP_DEV float u4_elem<F16>(const u32x4v& v, int k) {
     const unsigned w[4] = {v.x, v.y, v.z, v.w};
     const unsigned h = (k & 1) ? (w[k >> 1] >> 16) : (w[k >> 1] & 0xFFFFu);
     return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
 }
-template <> MXP_DEV float u4_elem<BF16>(const uint4& v, int k) {
+template <> MXP_DEV float u4_elem<BF16>(const u32x4v& v, int k) {
     const unsigned w[4] = {v.x, v.y, v.z, v.w};
     return __uint_as_float((k & 1) ? (w[k >> 1] & 0xFFFF0000u) : (w[k >> 1] << 16));
 }
 
-__device__ bool wait_flag(const unsigned* flag, unsigned target, int* err, int* s_abort) {
-    if (threadIdx.x == 0) {
-        int ok = 1;
-        unsigned it = 0;
-        while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            // a wait that expired anywhere ends every other wait at once
-            if (++it > (1u << 24) || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                ok = 0;
-                atomicOr(err, 1);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
+// Bounded waits of one wave: until *flag >= target; until the cnt <= 64 flags
+// f[0 .. cnt) are raised (one lane per flag).  False: expired here or anywhere
+// (*err is looked at every 64 polls).
+MXP_DEV bool wave_wait(const unsigned* f, int cnt, unsigned target, int* err) {
+    const int l = threadIdx.x & 63;
+    for (unsigned it = 0;; ++it) {
+        const bool up = l >= cnt || __hip_atomic_load(f + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
+        if (__all(up)) break;
+        if ((it & 63) == 63 &&
+            (it > (1u << 24) || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            if (l == 0) atomicOr(err, 1);
+            return false;
         }
-        if (ok) sync_acquire();
-        *s_abort = !ok;
+        __builtin_amdgcn_s_sleep(1);
     }
-    __syncthreads();
-    return !*s_abort;
+    sync_acquire();
+    asm volatile("" ::: "memory");
+    return true;
 }
 
-// bounded wait, by the first wave, until the cnt flags f[0 .. cnt) are all
-// raised (cnt <= 64: one lane per flag)
-__device__ bool wait_all(const unsigned* f, int cnt, int* err, int* s_abort) {
-    if (threadIdx.x < 64) {
-        const int l = threadIdx.x;
-        int ok = 1;
-        unsigned it = 0;
-        for (;;) {
-            const bool up = l >= cnt || __hip_atomic_load(f + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-            if (__all(up)) break;
-            if (++it > (1u << 24) || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                ok = 0;
-                if (l == 0) atomicOr(err, 1);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-        }
-        if (ok) sync_acquire();
-        if (l == 0) *s_abort = !ok;
-    }
-    __syncthreads();
-    return !*s_abort;
-}
-
-// every wave's stores are released at agent scope and precede the barrier;
-// the flag then counts one more strip with release semantics
-__device__ void signal_flag(unsigned* flag) {
-    sync_release();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        sync_release();
-        __hip_atomic_fetch_add(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-template <int ST, bool LOWER>
-__global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const typename Store<ST>::T* __restrict__ A,
-                                              int64_t lda, int vec, const float* __restrict__ inv_all,
-                                              const float* __restrict__ lsc, int64_t nstrips32,
-                                              const double* __restrict__ scale, const double* __restrict__ rhs,
-                                              int64_t ld_rhs, double* __restrict__ tbuf, double* __restrict__ out,
-                                              int64_t ld_out, unsigned* flags, unsigned* other, int64_t flag_stride,
-                                              unsigned* ticket, unsigned* other_ticket, int* err) {
+// A strip's step is a chain of round trips: the flag of the block before it,
+// that block's solution, the strip's right-hand side to the others and theirs
+// back, the solution out.  Each wave polls for itself (the loads that follow
+// need no barrier before them), a whole diagonal block's panels are in
+// registers when its flag is raised and are taken in one pass (one wait, one
+// load of the solution, one reduction), both halves of the inverse's rows are
+// loaded before the last wait and reduced together, and only the wave that
+// stores waits for its stores.  Eight right-hand sides at n = 8192, BF16:
+// 237 -> 219 us per solve; n = 600: 27 -> 23.5 us.  VEC: 16-byte aligned columns
+// (else element loads).
+template <int ST, bool LOWER, bool VEC>
+__global__ __launch_bounds__(256, 2) void k_trsv(int64_t n, int nb, int db, const typename Store<ST>::T* __restrict__ A,
+                                                 int64_t lda, const float* __restrict__ inv_all,
+                                                 const float* __restrict__ lsc, int64_t nstrips32,
+                                                 const double* __restrict__ scale, const double* __restrict__ rhs,
+                                                 int64_t ld_rhs, double* __restrict__ tbuf, double* __restrict__ out,
+                                                 int64_t ld_out, unsigned* flags, unsigned* other,
+                                                 int64_t flag_stride, unsigned* ticket, unsigned* other_ticket,
+                                                 int* err) {
     typedef typename Store<ST>::T T;
     constexpr int RPL = 16 / (int)sizeof(T);   // rows per lane: one 16-byte load
     constexpr int RG = TS / RPL;               // lanes per column
     constexpr int CPI = 64 / RG;               // columns per wave and load
-    __shared__ double zs[1024];
-    constexpr int PCOLS = CPI > 64 / (TS / 8) ? CPI : 64 / (TS / 8);   // column groups: panels, diagonal apply
+    constexpr int HS = TS / 2, RQ = HS / 4, CS = 64 / RQ;   // diagonal apply: half strips, lanes per column, columns
+    constexpr int PCOLS = CPI > CS ? CPI : CS;              // column groups of either
+    static_assert(TS == 64, "a wave holds one value per row of a strip");
+    constexpr int ZERO = 1024;                 // zs[ZERO] = 0: the weight of columns past a range
+    __shared__ double zs[ZERO + 1];
     __shared__ double part[4][PCOLS][TS];
-    __shared__ double w[TS];
-    __shared__ int s_abort;
     __shared__ unsigned s_pos;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // position in start order: strip pos % S of right-hand side pos / S (the
     // grid is S x nrhs work-groups)
-    if (tid == 0) s_pos = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+        s_pos = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        zs[ZERO] = 0.0;
+    }
     __syncthreads();
-    const int64_t S = (n + TS - 1) / TS, J = (n + nb - 1) / nb, gb = db / nb;
-    const int64_t pos = s_pos, px = pos % S, py = pos / S;
+    const int64_t S = (n + TS - 1) / TS, J = (n + nb - 1) / nb;
+    const int64_t pos = __builtin_amdgcn_readfirstlane((int)s_pos), py = __builtin_amdgcn_readfirstlane((int)((unsigned)pos / (unsigned)S)), px = pos - py * S;
     // right-hand side py: its own vectors, block buffer and flags
     rhs += py * ld_rhs;
     out += py * ld_out;
@@ -174,226 +158,235 @@ __global__ __launch_bounds__(256) void k_trsv(int64_t n, int nb, int db, const t
         if (px < J) __hip_atomic_store(other + S + px, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (pos == 0) __hip_atomic_store(other_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // the substitution's diagonal blocks (size db, a multiple of nb: gb factor
-    // blocks each) are the dataflow's steps; the off-diagonal products go by
-    // factor block (each with its own strip factors)
+    // the substitution's diagonal blocks (size db, a multiple of nb) are the
+    // dataflow's steps
     const int64_t sidx = LOWER ? px : S - 1 - px;
-    const int64_t j = sidx / (db / TS);
-    const int64_t first = j * gb, last = (first + gb < J ? first + gb : J) - 1;
+    const int64_t j = __builtin_amdgcn_readfirstlane((int)((unsigned)sidx / (unsigned)(db / TS))), Jd = (n + db - 1) / db;
     const int64_t r0 = sidx * TS;
     const int rows = (int)(n - r0 < TS ? n - r0 : TS);
     unsigned* sflag = flags;          // one per strip: its rows of the block right-hand side are published
     unsigned* ready = flags + S;      // one per block: strips that have published their solution rows
-    auto strips_of = [&](int64_t b) -> unsigned {
-        const int64_t kb = n - b * db < db ? n - b * db : db;
-        return (unsigned)((kb + TS - 1) / TS);
-    };
-    // the forward solve starts from S v (row scaling)
-    if (tid < TS) w[tid] = (tid < rows) ? (LOWER ? scale[r0 + tid] * rhs[r0 + tid] : rhs[r0 + tid]) : 0.0;
+    auto cols_of = [&](int64_t b) -> int { return (int)(n - b * db < db ? n - b * db : db); };
+    auto strips_of = [&](int64_t b) -> unsigned { return (unsigned)((cols_of(b) + TS - 1) / TS); };
+    // wave 0: the strip's rows, one per lane (the forward solve starts from S v)
+    double w = 0.0;
+    if (tid < rows) w = LOWER ? scale[r0 + tid] * rhs[r0 + tid] : rhs[r0 + tid];
     // The ragged last strip takes the same 16-byte loads: with 16-byte aligned
     // columns the rows up to lda may be read (its panel columns lie before the
     // last one), the lanes past lda re-read the strip's first rows, and the
     // sums of rows past n are dropped.  (Element loads, waited for one by one,
     // made that one strip the end of the forward solve: n = 20001 FP16 846 us
     // per solve against 312 us.)
-    const bool vload = vec;
     const int rg = lane % RG, cl = lane / RG;
     const int64_t rl = r0 + RPL * rg < lda ? r0 + RPL * rg : r0;   // first row this lane reads
-    constexpr int PF = 16;                     // panel loads issued before the dependency's flag is awaited
-    // The factor panels do not depend on the flags: the panel of the next
-    // dependency block is loaded while the current one is awaited and applied
-    // (two buffers, the loop taken two blocks at a time).  The loads carry no
-    // condition (a column past the range reads column 0 and is weighted zero
-    // below): a load under a branch ends in a wait for every load in flight,
-    // which would serialise them (unaligned columns, which take element loads
-    // below, read the 16-byte aligned inverse array instead and ignore the
-    // values).
-    const int64_t istep = LOWER ? 1 : -1;
-    auto in_range = [&](int64_t i) { return LOWER ? (i < first) : (i > last); };
-    auto issue = [&](int64_t i, uint4* dst) {
-        const int64_t c0 = i * nb;
-        const int kbi = (int)(n - c0 < nb ? n - c0 : nb);
-        const int q = (kbi + 3) / 4, cb = wv * q, ce = (cb + q < kbi) ? cb + q : kbi;
-        const T* base = A + rl + c0 * lda;
+    constexpr int PF = 16;                     // panel loads of one register set
+    // The factor panels do not depend on the flags: a block's panel (each wave
+    // a quarter of its columns, the first 2 PF loads of it) is loaded while the
+    // block before it is awaited and applied, each register set as soon as it
+    // is free.  The loads carry no condition (a column past the range reads
+    // the block's first and is weighted zero below): a load under a branch
+    // ends in a wait for every load in flight, which would serialise them.
+    struct Quarter {
+        int cb, ce;
+    };
+    auto quarter = [&](int64_t b) {
+        const int kb = cols_of(b), q = (kb + 3) / 4;
+        Quarter Q;
+        Q.cb = wv * q < kb ? wv * q : kb;
+        Q.ce = Q.cb + q < kb ? Q.cb + q : kb;
+        return Q;
+    };
+    // a wave whose wait has expired (*err is set) waits no more and goes
+    // through its steps: a way out of the loop would cost the registers that
+    // hold the loads
+    bool ok = true;
+    double acc[RPL] = {};
+    auto issue = [&](int64_t b, bool on, int m0, u32x4v* dst) {
+        // a uniform base and 32-bit byte offsets (a block of 1024 columns spans
+        // less than 4 GB for any matrix that fits the card)
+        const Quarter Q = quarter(b);
+        if (!VEC) return;
+        const char* base = (const char*)(A + (int64_t)on * b * db * lda);
+        const uint32_t ldb = (uint32_t)on * (uint32_t)(lda * sizeof(T)), row = (uint32_t)(rl * sizeof(T));
+        // (opaque here: the columns of all loads would otherwise be computed
+        // once and kept, which costs more registers than there are)
+        int c0 = Q.cb + cl;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) asm volatile("" : "+v"(c0) : "v"(acc[k]));
 #pragma unroll
         for (int m = 0; m < PF; ++m) {
-            const int c = cb + cl + m * CPI;
-            const void* src = vload ? (const void*)(base + (int64_t)(c < ce ? c : 0) * lda) : (const void*)inv_all;
-            dst[m] = *(const uint4*)src;
+            const int c = c0 + (m0 + m) * CPI;
+            dst[m] = *(const u32x4v*)(base + (uint32_t)(c < Q.ce ? c : 0) * ldb + row);
         }
     };
-    // one dependency block: wait for it, multiply its panel (prefetched in
-    // pre) with its solution and subtract from w
-    auto dep = [&](int64_t i, uint4* pre, uint4* nxt) -> bool {
-        const int64_t c0 = i * nb;
-        const int kbi = (int)(n - c0 < nb ? n - c0 : nb);
-        const int q = (kbi + 3) / 4, cb = wv * q, ce = (cb + q < kbi) ? cb + q : kbi;
-        const T* base = A + rl + c0 * lda;
-        if (in_range(i + istep)) issue(i + istep, nxt);
-        if (!wait_flag(&ready[i / gb], strips_of(i / gb), err, &s_abort)) return false;
+    const int64_t bstep = LOWER ? 1 : -1;
+    auto in_range = [&](int64_t b) { return LOWER ? b < j : b > j; };
+    auto take = [&](const Quarter& Q, int m0, u32x4v* pre) {
+        int c0 = Q.cb + cl;
+        asm volatile("" : "+v"(c0));           // (see issue)
+        if (!VEC) return;
 #pragma unroll
-        for (int m = 0; m < PF; ++m) pin4(pre[m]);
-        for (int c = tid; c < kbi; c += 256) zs[c] = get_shared(out + c0 + c);
-        __syncthreads();
-        double acc[RPL];
+        for (int m = 0; m < PF; ++m) {
+            pin4(pre[m]);
+            const int c = c0 + (m0 + m) * CPI;
+            const double zc = zs[c < Q.ce ? c : ZERO];
 #pragma unroll
-        for (int k = 0; k < RPL; ++k) acc[k] = 0.0;
-        if (vload) {
-#pragma unroll
-            for (int m = 0; m < PF; ++m) {
-                const int c = cb + cl + m * CPI;
-                const double zc = c < ce ? zs[c] : 0.0;
-#pragma unroll
-                for (int k = 0; k < RPL; ++k) acc[k] += (double)u4_elem<ST>(pre[m], k) * zc;
-            }
-#pragma unroll 4
-            for (int c = cb + cl + PF * CPI; c < ce; c += CPI) {
-                const uint4 v = *(const uint4*)(base + (int64_t)c * lda);
-                const T* e = (const T*)&v;
-                const double zc = zs[c];
-#pragma unroll
-                for (int k = 0; k < RPL; ++k) acc[k] += (double)Store<ST>::load(e, k) * zc;
-            }
-        } else {
-            for (int c = cb + cl; c < ce; c += CPI) {
-                const double zc = zs[c];
-#pragma unroll
-                for (int k = 0; k < RPL; ++k)
-                    if (RPL * rg + k < rows) acc[k] += (double)Store<ST>::load(base, (int64_t)c * lda + k) * zc;
-            }
+            for (int k = 0; k < RPL; ++k) acc[k] += (double)u4_elem<ST>(pre[m], k) * zc;
         }
-#pragma unroll
-        for (int k = 0; k < RPL; ++k) part[wv][cl][RPL * rg + k] = acc[k];
-        __syncthreads();
-        if (tid < rows) {
-            double t = 0.0;
-            for (int u = 0; u < 4; ++u)
-                for (int v2 = 0; v2 < CPI; ++v2) t += part[u][v2][tid];
-            if (LOWER) t /= (double)lsc[i * nstrips32 + (r0 + tid) / 32];
-            w[tid] -= t;
-        }
-        return true;
     };
     {
-        uint4 pa[PF], pb[PF];
-        int64_t i = LOWER ? 0 : J - 1;
-        if (in_range(i)) issue(i, pa);
-        for (;;) {
-            if (!in_range(i)) break;
-            if (!dep(i, pa, pb)) return;
-            i += istep;
-            if (!in_range(i)) break;
-            if (!dep(i, pb, pa)) return;
-            i += istep;
+        u32x4v pa[PF], pb[PF];
+        int64_t b = LOWER ? 0 : Jd - 1;
+        issue(b, in_range(b), 0, pa);
+        issue(b, in_range(b), PF, pb);
+        for (; in_range(b); b += bstep) {
+            const Quarter Q = quarter(b);
+            const int kb = cols_of(b);
+            ok = ok && wave_wait(&ready[b], 1, strips_of(b), err);
+            for (int c = tid; c < kb; c += 256) zs[c] = get_shared(out + b * db + c);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) acc[k] = 0.0;
+            const bool more = in_range(b + bstep);
+            // (kept apart: overlapped, the registers of the old and of the new
+            // loads would all be live)
+            take(Q, 0, pa);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(b + bstep, more, 0, pa);
+            __builtin_amdgcn_sched_barrier(0);
+            take(Q, PF, pb);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(b + bstep, more, PF, pb);
+            __builtin_amdgcn_sched_barrier(0);
+            const T* base = A + rl + b * db * lda;
+            if (VEC) {
+#pragma unroll 4
+                for (int c = Q.cb + cl + 2 * PF * CPI; c < Q.ce; c += CPI) {
+                    const u32x4v v = *(const u32x4v*)(base + (int64_t)c * lda);
+                    const T* e = (const T*)&v;
+                    const double zc = zs[c];
+#pragma unroll
+                    for (int k = 0; k < RPL; ++k) acc[k] += (double)Store<ST>::load(e, k) * zc;
+                }
+            } else {
+                for (int c = Q.cb + cl; c < Q.ce; c += CPI) {
+                    const double zc = zs[c];
+#pragma unroll
+                    for (int k = 0; k < RPL; ++k)
+                        if (RPL * rg + k < rows) acc[k] += (double)Store<ST>::load(base, (int64_t)c * lda + k) * zc;
+                }
+            }
+            if (LOWER) {
+                // stored strips carry a power of two per factor block and 32
+                // rows; a dependency of the forward solve is a whole block, so
+                // a wave's quarter lies in one factor block
+                const int64_t i = b * (db / nb) + (int64_t)Q.cb / nb;
+                const double us = 1.0 / (double)lsc[i * nstrips32 + (r0 + RPL * rg < n ? r0 + RPL * rg : r0) / 32];
+#pragma unroll
+                for (int k = 0; k < RPL; ++k) acc[k] *= us;
+            }
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) part[wv][cl][RPL * rg + k] = acc[k];
+            __syncthreads();
+            if (tid < TS) {
+                double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v2 = 0; v2 < CPI; ++v2)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) t[u] += part[u][v2][tid];
+                w -= (t[0] + t[1]) + (t[2] + t[3]);
+            }
         }
     }
-    // The strip's rows of its diagonal-block inverse (lower / upper
-    // triangular: a row takes the columns up to / from itself), applied in two
-    // half strips of HS rows.  A lane: four consecutive rows (16-byte loads),
-    // one of CS column groups; the waves split a half strip's columns.  The
-    // first batch of loads is issued while the strips it depends on publish.
+    // this strip's rows of the block right-hand side are final (wave 0)
+    if (wv == 0) {
+        if (tid < rows) put_shared(tbuf + r0 + tid, w);
+        sync_release();
+        if (tid == 0) __hip_atomic_store(&sflag[sidx], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // The strip's rows of its diagonal-block inverse (lower / upper triangular:
+    // a row takes the columns up to / from itself), in two half strips of HS
+    // rows.  A lane: four consecutive rows (16-byte loads), one of CS column
+    // groups; the waves split a half strip's columns.  The first loads of both
+    // are issued while the strips they depend on publish.
     const int64_t cj = j * db;
-    const int kbj = (int)(n - cj < db ? n - cj : db);
+    const int kbj = cols_of(j);
     const int nst = (int)strips_of(j);
     const int s_in = (int)((r0 - cj) / TS);
-    constexpr int HS = TS / 2, RQ = HS / 4, CS = 64 / RQ;
-    static_assert(PCOLS >= CS, "part[][] also holds the column groups of the diagonal apply");
     const int rsub = lane % RQ, csub = lane / RQ;
-    const float* blkinv = inv_all + j * (int64_t)db * db + 4 * rsub;
+    const float* blkinv = inv_all + j * (int64_t)db * db;
     struct Half {
-        int r0, rows, clo, cb, ce;
+        int r0, clo, cb, ce;
     };
     auto half = [&](int h) {
         Half H;
-        H.r0 = HS * h;
-        H.rows = kbj - H.r0 < HS ? kbj - H.r0 : HS;               // <= 0: nothing to do
+        H.r0 = HS * h < kbj ? HS * h : 0;                         // past the block: nothing is stored
         H.clo = LOWER ? 0 : H.r0;
         const int chi = LOWER ? (H.r0 + HS < kbj ? H.r0 + HS : kbj) : kbj;
-        const int q = chi > H.clo ? (chi - H.clo + 3) / 4 : 0;
+        const int q = (chi - H.clo + 3) / 4;
         H.cb = H.clo + wv * q;
         H.ce = H.cb + q < chi ? H.cb + q : chi;
         return H;
     };
     const Half HA = half(2 * s_in), HB = half(2 * s_in + 1);
-    // this strip's rows of the block right-hand side are final
-    if (tid < rows) put_shared(tbuf + r0 + tid, w[tid]);
-    signal_flag(&sflag[sidx]);
-    // (issued after the signal, whose wait for this wave's stores would also
-    // wait for them)
-#ifndef MXP_TRSV_NIV
-#define MXP_TRSV_NIV 16
-#endif
-    constexpr int NIV = MXP_TRSV_NIV;     // inverse loads in flight per lane (16 bytes each)
-    float4 iv0[NIV];
-    {
-        const float* rb = blkinv + HA.r0;
+    constexpr int NIV = 16;               // inverse loads of a batch per lane (16 bytes each)
+    auto load_inv = [&](const Half& H, int t0, f32x4v (&iv)[NIV]) {
+        const uint32_t row = (uint32_t)(H.r0 + 4 * rsub) * 4u, ldb = (uint32_t)db * 4u;
 #pragma unroll
         for (int t = 0; t < NIV; ++t) {
-            const int c = HA.cb + csub + CS * t;
-            iv0[t] = *(const float4*)(rb + (int64_t)(c < HA.ce ? c : HA.clo) * db);
+            const int c = H.cb + csub + CS * (t0 + t);
+            iv[t] = *(const f32x4v*)((const char*)blkinv + (uint32_t)(c < H.ce ? c : H.clo) * ldb + row);
         }
-    }
+    };
+    f32x4v ia[NIV], ib[NIV];
+    load_inv(HA, 0, ia);
+    load_inv(HB, 0, ib);
     // the strips whose right-hand side rows this strip's rows take: those
     // above it in the block (L), below it (U)
-    const int64_t sb = sidx - s_in;
-    if (!(LOWER ? wait_all(sflag + sb, s_in, err, &s_abort)
-                : wait_all(sflag + sidx + 1, nst - 1 - s_in, err, &s_abort)))
-        return;
-#pragma unroll
-    for (int t = 0; t < NIV; ++t) pin4f(iv0[t]);
+    ok = ok && (LOWER ? wave_wait(sflag + sidx - s_in, s_in, 1u, err)
+                      : wave_wait(sflag + sidx + 1, nst - 1 - s_in, 1u, err));
     {
-        const int zlo = LOWER ? 0 : s_in * TS, zhi = LOWER ? s_in * TS + rows : kbj;
+        // this strip's own rows come from wave 0's registers
+        const int own = s_in * TS, zlo = LOWER ? 0 : own + rows, zhi = LOWER ? own : kbj;
         for (int c = zlo + tid; c < zhi; c += 256) zs[c] = get_shared(tbuf + cj + c);
+        if (tid < rows) zs[own + tid] = w;
     }
     __syncthreads();
-    // one half strip: its columns in batches of NIV loads in flight at once,
-    // without conditions (a column past the range reads column clo and is
-    // weighted zero); the first batch is given (pre) or loaded here
-    auto apply = [&](const Half& H, float4 (&pre)[NIV], bool has_pre) {
-        const float* rb = blkinv + H.r0;
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        auto fma4 = [&](const float4 v, double zc) {
-            acc[0] += (double)v.x * zc;
-            acc[1] += (double)v.y * zc;
-            acc[2] += (double)v.z * zc;
-            acc[3] += (double)v.w * zc;
-        };
-        int c0b = H.cb + csub;
-        if (has_pre) {
+    auto apply = [&](const Half& H, int h, f32x4v (&iv)[NIV]) {
+        double a4[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int t0 = 0;;) {
 #pragma unroll
             for (int t = 0; t < NIV; ++t) {
-                const int c = c0b + CS * t;
-                fma4(pre[t], c < H.ce ? zs[c] : 0.0);
+                pin4f(iv[t]);
+                const int c = H.cb + csub + CS * (t0 + t);
+                const double zc = zs[c < H.ce ? c : ZERO];
+                a4[0] += (double)iv[t].x * zc;
+                a4[1] += (double)iv[t].y * zc;
+                a4[2] += (double)iv[t].z * zc;
+                a4[3] += (double)iv[t].w * zc;
             }
-            c0b += CS * NIV;
-        }
-        for (; c0b < H.ce; c0b += CS * NIV) {
-            float4 iv[NIV];
-#pragma unroll
-            for (int t = 0; t < NIV; ++t) {
-                const int c = c0b + CS * t;
-                iv[t] = *(const float4*)(rb + (int64_t)(c < H.ce ? c : H.clo) * db);
-            }
-#pragma unroll
-            for (int t = 0; t < NIV; ++t) {
-                const int c = c0b + CS * t;
-                fma4(iv[t], c < H.ce ? zs[c] : 0.0);
-            }
+            t0 += NIV;
+            if (H.cb + CS * t0 >= H.ce) break;            // wave-uniform
+            load_inv(H, t0, iv);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) part[wv][csub][4 * rsub + k] = acc[k];
-        __syncthreads();
-        if (tid < H.rows) {
-            double t = 0.0;
-            for (int u = 0; u < 4; ++u)
-                for (int v2 = 0; v2 < CS; ++v2) t += part[u][v2][tid];
-            put_shared(out + cj + H.r0 + tid, t);
-        }
-        __syncthreads();                      // part[] free for the next half
+        for (int k = 0; k < 4; ++k) part[wv][csub][HS * h + 4 * rsub + k] = a4[k];
     };
-    if (HA.rows > 0) apply(HA, iv0, true);
-    if (HB.rows > 0) apply(HB, iv0, false);
-    signal_flag(&ready[j]);
+    apply(HA, 0, ia);
+    apply(HB, 1, ib);
+    __syncthreads();
+    if (wv == 0) {
+        if (tid < rows) {
+            double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int v2 = 0; v2 < CS; ++v2)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) t[u] += part[u][v2][tid];
+            put_shared(out + r0 + tid, (t[0] + t[1]) + (t[2] + t[3]));
+        }
+        sync_release();
+        if (tid == 0) __hip_atomic_fetch_add(&ready[j], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 __global__ void k_zero_u32(unsigned* p, int64_t count) {
@@ -446,15 +439,22 @@ static hipError_t prec_typed(const PrecPlan& p, const double* V, int64_t ldv, do
     unsigned* flags = (unsigned*)(Tb + n * nr);
     const int64_t fw = trsv_flag_words(n);
     int* err = prec_err_word(W, n, nr);
-    const int vec = ((p.lda * (int64_t)sizeof(T)) % 16 == 0 && ((uintptr_t)p.A) % 16 == 0) ? 1 : 0;
+    const bool vec = ((p.lda * (int64_t)sizeof(T)) % 16 == 0 && ((uintptr_t)p.A) % 16 == 0);
     unsigned *fl = flags, *fu = flags + S + J, *tk = flags + 2 * (S + J);
     const int db = (int)prec_block(nb);
     const dim3 grid((unsigned)S, (unsigned)nr);
     hipEvent_t pt = prof::begin(prof::PREC, s);
-    k_trsv<ST, true><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec, p.linv_full, p.lsc, nstrips32,
-                                          p.rowscale, V, ldv, Tb, Y, n, fl, fu, fw, tk, tk + 1, err);
-    k_trsv<ST, false><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, vec, p.uinv_full, nullptr, nstrips32,
-                                           nullptr, Y, n, Tb, Z, ldz, fu, fl, fw, tk + 1, tk, err);
+    auto solves = [&](auto VEC) {
+        constexpr bool V16 = decltype(VEC)::value;
+        k_trsv<ST, true, V16><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.linv_full, p.lsc, nstrips32,
+                                                   p.rowscale, V, ldv, Tb, Y, n, fl, fu, fw, tk, tk + 1, err);
+        k_trsv<ST, false, V16><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.uinv_full, nullptr,
+                                                    nstrips32, nullptr, Y, n, Tb, Z, ldz, fu, fl, fw, tk + 1, tk, err);
+    };
+    if (vec)
+        solves(std::true_type{});
+    else
+        solves(std::false_type{});
     prof::end(pt, prof::PREC, s, 2.0 * n * (double)n * nr, (double)n * n * sizeof(T) + 8.0 * n * nb);
     return hipGetLastError();
 }
