@@ -207,7 +207,7 @@ struct PrecPlan {
 };
 // Z = U^-1 L^-1 S V for nr columns (V may alias Z); W: prec_work_bytes(n, nr)
 // of scratch.  A wait of the substitution kernels that expires sets an error
-// word in W (read by prec_err_read); prec_reset clears it and the flags, once
+// word in W (read by prec_err_read); prec_reset clears it and the exchange buffers, once
 // before the applies with this n and nr.
 size_t prec_work_bytes(int64_t n, int nr);
 hipError_t prec_apply(const PrecPlan& p, const double* V, int64_t ldv, double* Z, int64_t ldz, int nr, double* W,

@@ -22,17 +22,16 @@ __host__ __device__ static inline int64_t rup(int64_t a, int64_t b) { return (a 
 // ================================================================ preconditioner
 // ---------------------------------------------------------------- block substitution
 // One kernel per triangular solve, every right-hand side at once (each
-// right-hand side with its own flags).  Work-group = one strip of TS rows;
-// strips are processed as a dataflow: a strip of block j accumulates the
-// products of its rows of the off-diagonal factor with every dependency
-// block's solution as soon as that block is published (flag `ready`),
-// publishes its rows of the block right-hand side (its strip flag), and
-// applies its rows of the FP32 inverse of the diagonal block once the strips
-// those rows depend on have published theirs (the inverse is triangular:
-// the strips above it in the block for L, below it for U); it then counts
-// itself into the block's `ready`.  Forward (L): dependencies are the blocks
-// before j, strips run in increasing order; backward (U): the blocks after
-// j, strips in decreasing order.
+// right-hand side with its own exchange buffers).  Work-group = one strip of
+// TS rows; strips are processed as a dataflow: a strip of block j accumulates
+// the products of its rows of the off-diagonal factor with every dependency
+// block's solution as soon as that is there (`out`), publishes its rows of the
+// block right-hand side (`tbuf`), applies its rows of the FP32 inverse of the
+// diagonal block once the rows they take are there (the inverse is triangular:
+// the strips above it in the block for L, below it for U), and publishes its
+// rows of the solution.  Forward (L): dependencies are the blocks before j,
+// strips run in increasing order; backward (U): the blocks after j, strips in
+// decreasing order.
 //
 // A work-group takes its position (right-hand side, strip) from a counter
 // of the launch when it starts, not from its index, and every wait is on
@@ -42,9 +41,9 @@ __host__ __device__ static inline int64_t rup(int64_t a, int64_t b) { return (a 
 // hardware deals the indices out to the XCDs, each dispatching its share in
 // order, and with other launches on other streams it can hold back a
 // launch's remaining work-groups while that launch's resident ones spin.
-// Each wait is still bounded and on expiry sets *err and lets the
-// work-group exit.  All sums are taken in a fixed order (deterministic
-// results).
+// Each wait is still bounded; on expiry it sets *err and the work-group goes
+// through its remaining steps without waiting.  All sums are taken in a fixed
+// order (deterministic results).
 #ifndef MXP_TRSV_TS
 #define MXP_TRSV_TS 64
 #endif
@@ -52,20 +51,14 @@ constexpr int TS = MXP_TRSV_TS;
 
 // Values exchanged between work-groups (block solutions, block right-hand
 // sides) are written and read with device-scope atomic accesses, which go to
-// the device's coherence point instead of an XCD's L2.  A flag is raised
-// after every wave's stores are released (sync_release) and a work-group
-// barrier; a waiter that sees the flag reads after it (sync_acquire, then
-// the barrier that lets its other threads read); see common.hpp.
-MXP_DEV void put_shared(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// the device's coherence point instead of an XCD's L2.
 MXP_DEV double get_shared(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // v, treated as written at this point: arithmetic on prefetched registers
 // cannot move above it (the compiler would otherwise unpack a load's result
 // right after issuing it, which waits for the load)
 typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
 MXP_DEV void pin4(u32x4v& v) { asm volatile("" : "+v"(v)); }
-MXP_DEV void pin4f(f32x4v& v) { asm volatile("" : "+v"(v)); }
 
 // element k of a 16-byte vector of storage values, taken from its 32-bit
 // words (no access through a cast pointer, which would split the vector at
@@ -85,92 +78,149 @@ template <> MXP_DEV float u4_elem<BF16>(const u32x4v& v, int k) {
     return __uint_as_float((k & 1) ? (w[k >> 1] & 0xFFFF0000u) : (w[k >> 1] << 16));
 }
 
-// Bounded waits of one wave: until *flag >= target; until the cnt <= 64 flags
-// f[0 .. cnt) are raised (one lane per flag).  False: expired here or anywhere
-// (*err is looked at every 64 polls).
-MXP_DEV bool wave_wait(const unsigned* f, int cnt, unsigned target, int* err) {
+// A step of the substitution is a chain of exchanges between work-groups: the
+// block's solution to every strip of the next block, and the strips' right-hand
+// side rows among each other.  A value is its own flag: the exchange buffers
+// hold UNSET (a NaN no computation gives, put_value) until the value is
+// written, so an exchange is one store and one load that sees it, not a store,
+// its acknowledgement, a flag, the flag's load and the value's load.
+constexpr unsigned long long UNSET = 0x7FF8D15EA5EDF1A6ull;
+MXP_DEV void put_value(double* p, double v) {
+    unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    if (u == UNSET) u ^= 1ull;
+    __hip_atomic_store((unsigned long long*)p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+MXP_DEV void put_unset(double* p) {
+    __hip_atomic_store((unsigned long long*)p, UNSET, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+MXP_DEV bool is_set(double v) { return __builtin_bit_cast(unsigned long long, v) != UNSET; }
+
+// Bounded waits of one wave for the values p[c], p[c + 64] of its lanes (those
+// below cnt; the others are given 0).  far: a value several steps away is
+// looked for with one address per wave (the last) before all are.  False:
+// expired here or anywhere (*err is looked at every 64 polls).
+MXP_DEV bool wait_values(const double* p, int cnt, bool far, double& v0, double& v1, int* err) {
     const int l = threadIdx.x & 63;
+    v0 = v1 = 0.0;
+    if (cnt <= 0) return true;
     for (unsigned it = 0;; ++it) {
-        const bool up = l >= cnt || __hip_atomic_load(f + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
-        if (__all(up)) break;
+        bool up = true;
+        if (far) {
+            up = is_set(get_shared(p + cnt - 1));
+            if (__all(up)) { far = false; continue; }
+        } else {
+            if (l < cnt) v0 = get_shared(p + l);
+            if (l + 64 < cnt) v1 = get_shared(p + l + 64);
+            up = is_set(v0) && is_set(v1);
+            if (__all(up)) return true;
+        }
         if ((it & 63) == 63 &&
             (it > (1u << 24) || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
             if (l == 0) atomicOr(err, 1);
             return false;
         }
-        __builtin_amdgcn_s_sleep(1);
+        if (far) __builtin_amdgcn_s_sleep(4);
+        else __builtin_amdgcn_s_sleep(1);
     }
-    sync_acquire();
-    asm volatile("" ::: "memory");
-    return true;
 }
 
-// A strip's step is a chain of round trips: the flag of the block before it,
-// that block's solution, the strip's right-hand side to the others and theirs
-// back, the solution out.  Each wave polls for itself (the loads that follow
-// need no barrier before them), a whole diagonal block's panels are in
-// registers when its flag is raised and are taken in one pass (one wait, one
-// load of the solution, one reduction), both halves of the inverse's rows are
-// loaded before the last wait and reduced together, and only the wave that
-// stores waits for its stores.  Eight right-hand sides at n = 8192, BF16:
-// 237 -> 219 us per solve; n = 600: 27 -> 23.5 us.  VEC: 16-byte aligned columns
-// (else element loads).
+// a wave's LDS stores before its lanes' loads (LDS operations of a wave are in order)
+MXP_DEV void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// x, y of every lane -> lanes below 32: x + x of lane + 32, lanes above: y + y
+// of lane - 32 (fold32); the same between the 16-lane rows of each half
+// (fold16) and the 8-lane halves of each row (fold8): log2 steps of a sum over
+// lanes in which each lane ends with the sums of its own rows
+MXP_DEV double join(unsigned lo, unsigned hi) { return __hiloint2double((int)hi, (int)lo); }
+MXP_DEV double fold32(double x, double y) {
+    const auto a = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return join(a[0], b[0]) + join(a[1], b[1]);
+}
+MXP_DEV double fold16(double x, double y) {
+    const auto a = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return join(a[0], b[0]) + join(a[1], b[1]);
+}
+MXP_DEV double fold8(double x, double y) {
+    const bool up = threadIdx.x & 8;
+    const double keep = up ? y : x, give = up ? x : y;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(give), 0x128, 0xF, 0xF, true);   // row_ror:8
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(give), 0x128, 0xF, 0xF, true);
+    return keep + __hiloint2double(hi, lo);
+}
+
+// What bounds a solve: the chain of exchanges, about 7 us per block of 1024
+// columns at n = 8192; at n = 32768 also the panels' bytes (one factor half,
+// 1.07 GB, in 318 us: 3.4 TB/s).  Eight waves per strip
+// and at most 128 registers: two waves per SIMD also where a CU holds one
+// strip (one wave issues an instruction every 8 cycles at most, two nearly
+// twice as many) and four where it holds two.
+//   a block's panel: each wave an eighth of the columns, in registers before the
+//   block's solution is there (with FP32 storage half of it), taken in one pass;
+//   the next block's loads, at the last block the inverse's, take their place.
+//   A wave waits only for the solution values of its own columns.
+// The loads that fill a set of registers are issued as one group with the
+// panel's scale factor first: a later load in the chain would wait for them all
+// (loads return in order).
+// Per solve, against four waves per strip with a flag per exchange: n = 32768
+// FP16 610 -> 318 us, n = 20001 FP16 312 -> 173, n = 8192 BF16 with eight
+// right-hand sides 219 -> 122, n = 600 BF16 23.5 -> 14.2.
 template <int ST, bool LOWER, bool VEC>
-__global__ __launch_bounds__(256, 2) void k_trsv(int64_t n, int nb, int db, const typename Store<ST>::T* __restrict__ A,
+__global__ __launch_bounds__(512, 4) void k_trsv(int64_t n, int nb, int db, const typename Store<ST>::T* __restrict__ A,
                                                  int64_t lda, const float* __restrict__ inv_all,
                                                  const float* __restrict__ lsc, int64_t nstrips32,
-                                                 const double* __restrict__ scale, const double* __restrict__ rhs,
-                                                 int64_t ld_rhs, double* __restrict__ tbuf, double* __restrict__ out,
-                                                 int64_t ld_out, unsigned* flags, unsigned* other,
-                                                 int64_t flag_stride, unsigned* ticket, unsigned* other_ticket,
+                                                 const double* __restrict__ scale, const double* rhs, int64_t ld_rhs,
+                                                 double* tbuf, double* out, double* other_tbuf, double* other_out,
+                                                 double* zout, int64_t ld_z, unsigned* ticket, unsigned* other_ticket,
                                                  int* err) {
     typedef typename Store<ST>::T T;
     constexpr int RPL = 16 / (int)sizeof(T);   // rows per lane: one 16-byte load
     constexpr int RG = TS / RPL;               // lanes per column
     constexpr int CPI = 64 / RG;               // columns per wave and load
-    constexpr int HS = TS / 2, RQ = HS / 4, CS = 64 / RQ;   // diagonal apply: half strips, lanes per column, columns
-    constexpr int PCOLS = CPI > CS ? CPI : CS;              // column groups of either
-    static_assert(TS == 64, "a wave holds one value per row of a strip");
-    constexpr int ZERO = 1024;                 // zs[ZERO] = 0: the weight of columns past a range
-    __shared__ double zs[ZERO + 1];
-    __shared__ double part[4][PCOLS][TS];
+    constexpr int RQ = TS / 4, CS = 64 / RQ;   // the inverse (FP32): lanes per column, columns per wave and load
+    constexpr int NW = 8, WC = 128;            // waves; columns of a wave at most (blocks have at most 1024)
+    constexpr int PF = 16;                     // loads of one group
+    constexpr int PH = WC / (CPI * PF);        // groups of a panel
+    static_assert(TS == 64 && (RPL == 4 || RPL == 8), "a wave holds one value per row of a strip");
+    __shared__ double zs[NW][WC];              // each wave's weights
+    __shared__ double part[2][NW][TS];
+    __shared__ double own[TS];
     __shared__ unsigned s_pos;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // position in start order: strip pos % S of right-hand side pos / S (the
     // grid is S x nrhs work-groups)
-    if (tid == 0) {
-        s_pos = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        zs[ZERO] = 0.0;
-    }
+    if (tid == 0) s_pos = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const int64_t S = (n + TS - 1) / TS, J = (n + nb - 1) / nb;
-    const int64_t pos = __builtin_amdgcn_readfirstlane((int)s_pos), py = __builtin_amdgcn_readfirstlane((int)((unsigned)pos / (unsigned)S)), px = pos - py * S;
-    // right-hand side py: its own vectors, block buffer and flags
+    const int64_t S = (n + TS - 1) / TS;
+    const int64_t pos = __builtin_amdgcn_readfirstlane((int)s_pos);
+    const int64_t py = __builtin_amdgcn_readfirstlane((int)((unsigned)pos / (unsigned)S)), px = pos - py * S;
+    // right-hand side py: its own vectors and exchange buffers
     rhs += py * ld_rhs;
-    out += py * ld_out;
+    out += py * n;
     tbuf += py * n;
-    flags += py * flag_stride;
-    other += py * flag_stride;
-    // the flags and the counter of the other triangular solve, which is not
-    // running, cleared for its next launch
-    if (tid == 0) {
-        __hip_atomic_store(other + px, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (px < J) __hip_atomic_store(other + S + px, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (pos == 0) __hip_atomic_store(other_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     // the substitution's diagonal blocks (size db, a multiple of nb) are the
     // dataflow's steps
     const int64_t sidx = LOWER ? px : S - 1 - px;
-    const int64_t j = __builtin_amdgcn_readfirstlane((int)((unsigned)sidx / (unsigned)(db / TS))), Jd = (n + db - 1) / db;
-    const int64_t r0 = sidx * TS;
+    const int64_t j = __builtin_amdgcn_readfirstlane((int)((unsigned)sidx / (unsigned)(db / TS)));
+    const int64_t Jd = (n + db - 1) / db, r0 = sidx * TS;
     const int rows = (int)(n - r0 < TS ? n - r0 : TS);
-    unsigned* sflag = flags;          // one per strip: its rows of the block right-hand side are published
-    unsigned* ready = flags + S;      // one per block: strips that have published their solution rows
     auto cols_of = [&](int64_t b) -> int { return (int)(n - b * db < db ? n - b * db : db); };
-    auto strips_of = [&](int64_t b) -> unsigned { return (unsigned)((cols_of(b) + TS - 1) / TS); };
-    // wave 0: the strip's rows, one per lane (the forward solve starts from S v)
+    // wave 0: the strip's rows, one per lane (the forward solve starts from S v).
+    // The buffers of the other triangular solve, which is not running, are
+    // cleared for its next launch (the backward solve's right-hand side is the
+    // forward solve's `out`: read first).
     double w = 0.0;
-    if (tid < rows) w = LOWER ? scale[r0 + tid] * rhs[r0 + tid] : rhs[r0 + tid];
+    if (tid < rows) {
+        w = LOWER ? scale[r0 + tid] * rhs[r0 + tid] : rhs[r0 + tid];
+        asm volatile("" : "+v"(w) : : "memory");
+        put_unset(other_tbuf + py * n + r0 + tid);
+        put_unset(other_out + py * n + r0 + tid);
+    }
+    if (pos == 0 && tid == 0) __hip_atomic_store(other_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // The ragged last strip takes the same 16-byte loads: with 16-byte aligned
     // columns the rows up to lda may be read (its panel columns lie before the
     // last one), the lanes past lda re-read the strip's first rows, and the
@@ -179,249 +229,214 @@ __global__ __launch_bounds__(256, 2) void k_trsv(int64_t n, int nb, int db, cons
     // per solve against 312 us.)
     const int rg = lane % RG, cl = lane / RG;
     const int64_t rl = r0 + RPL * rg < lda ? r0 + RPL * rg : r0;   // first row this lane reads
-    constexpr int PF = 16;                     // panel loads of one register set
-    // The factor panels do not depend on the flags: a block's panel (each wave
-    // a quarter of its columns, the first 2 PF loads of it) is loaded while the
-    // block before it is awaited and applied, each register set as soon as it
-    // is free.  The loads carry no condition (a column past the range reads
-    // the block's first and is weighted zero below): a load under a branch
-    // ends in a wait for every load in flight, which would serialise them.
-    struct Quarter {
-        int cb, ce;
+    const int rsub = lane % RQ, csub = lane / RQ;
+    // the rows whose sums the lane ends with (reduce below)
+    const int prow = RPL == 8 ? 8 * rg + (lane >> 3 & 1) + 2 * (lane >> 4 & 1) + 4 * (lane >> 5)
+                              : 4 * rg + (lane >> 4 & 1) + 2 * (lane >> 5);
+    const int irow = 4 * rsub + (lane >> 4 & 1) + 2 * (lane >> 5);
+    // a wave's columns [cb, cb + cnt) of block b / of the strip's rows of the
+    // diagonal block's inverse (lower / upper triangular: a row takes the
+    // columns up to / from itself)
+    struct Cols {
+        int cb, cnt;
     };
-    auto quarter = [&](int64_t b) {
-        const int kb = cols_of(b), q = (kb + 3) / 4;
-        Quarter Q;
-        Q.cb = wv * q < kb ? wv * q : kb;
-        Q.ce = Q.cb + q < kb ? Q.cb + q : kb;
-        return Q;
+    auto share = [&](int lo, int hi) {
+        const int q = (hi - lo + NW - 1) / NW, cb = lo + wv * q;
+        Cols C;
+        C.cb = cb < hi ? cb : lo;
+        C.cnt = cb < hi ? (cb + q < hi ? q : hi - cb) : 0;
+        return C;
     };
-    // a wave whose wait has expired (*err is set) waits no more and goes
-    // through its steps: a way out of the loop would cost the registers that
-    // hold the loads
-    bool ok = true;
+    const int64_t cj = j * db;
+    const int kbj = cols_of(j), ro = (int)(r0 - cj);      // the strip's first row in its block
+    const Cols CI = LOWER ? share(0, ro + TS < kbj ? ro + TS : kbj) : share(ro, kbj);
+    const float* blkinv = inv_all + j * (int64_t)db * db;
+    // Loads carry no condition (a column past the range re-reads the first and
+    // has the weight zero): a load under a branch ends in a wait for every load
+    // in flight, which would serialise them.  A uniform base and 32-bit byte
+    // offsets (a block of 1024 columns spans less than 4 GB for any matrix that
+    // fits the card).
+    u32x4v pre[PF];
     double acc[RPL] = {};
-    auto issue = [&](int64_t b, bool on, int m0, u32x4v* dst) {
-        // a uniform base and 32-bit byte offsets (a block of 1024 columns spans
-        // less than 4 GB for any matrix that fits the card)
-        const Quarter Q = quarter(b);
-        if (!VEC) return;
-        const char* base = (const char*)(A + (int64_t)on * b * db * lda);
-        const uint32_t ldb = (uint32_t)on * (uint32_t)(lda * sizeof(T)), row = (uint32_t)(rl * sizeof(T));
-        // (opaque here: the columns of all loads would otherwise be computed
-        // once and kept, which costs more registers than there are)
-        int c0 = Q.cb + cl;
+    float us = 1.0f;
+    // (the weights of a whole group at once would not fit the registers either)
+    auto pin_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) asm volatile("" : "+v"(acc[k]));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_group = [&](const char* base, uint32_t ldb, uint32_t row, int c0, int cnt, int step) __attribute__((always_inline)) {
+        // (opaque: the columns of all loads would otherwise be kept, which costs
+        // more registers than there are; and not before acc is final)
 #pragma unroll
         for (int k = 0; k < RPL; ++k) asm volatile("" : "+v"(c0) : "v"(acc[k]));
 #pragma unroll
         for (int m = 0; m < PF; ++m) {
-            const int c = c0 + (m0 + m) * CPI;
-            dst[m] = *(const u32x4v*)(base + (uint32_t)(c < Q.ce ? c : 0) * ldb + row);
+            const int c = c0 + m * step;
+            pre[m] = *(const u32x4v*)(base + (uint32_t)(c < cnt ? c : 0) * ldb + row);
         }
+    };
+    auto load_inverse = [&](int c0) __attribute__((always_inline)) {
+        load_group((const char*)(blkinv + (int64_t)CI.cb * db), (uint32_t)db * 4u, (uint32_t)(ro + 4 * rsub) * 4u,
+                   csub + c0, CI.cnt, CS);
+    };
+    // group ph of block b's panel, or (on false) the first of the inverse:
+    // chosen by value, since a branch around the loads would cost a copy of
+    // their registers
+    auto load_next = [&](int64_t b, bool on, int ph) __attribute__((always_inline)) {
+        const Cols C = share(0, cols_of(on ? b : 0));
+        if (LOWER && ph == 0) {
+            // stored strips carry a power of two per factor block and 32 rows; a
+            // dependency of the forward solve is a whole block, so a wave's
+            // columns lie in one factor block
+            const int64_t i = (on ? b : 0) * (db / nb) + (int64_t)C.cb / nb;
+            us = lsc[i * nstrips32 + (r0 + prow < n ? r0 + prow : r0) / 32];
+        }
+        const bool pan = VEC && on;
+        const int64_t off = pan ? (int64_t)(uintptr_t)(A + (b * db + C.cb) * lda)
+                                : (int64_t)(uintptr_t)(blkinv + (int64_t)CI.cb * db);
+        load_group((const char*)(uintptr_t)off, pan ? (uint32_t)(lda * sizeof(T)) : (uint32_t)db * 4u,
+                   pan ? (uint32_t)(rl * sizeof(T)) : (uint32_t)(ro + 4 * rsub) * 4u,
+                   (pan ? cl : csub) + ph * PF * CPI, pan ? C.cnt : CI.cnt, pan ? CPI : CS);
     };
     const int64_t bstep = LOWER ? 1 : -1;
     auto in_range = [&](int64_t b) { return LOWER ? b < j : b > j; };
-    auto take = [&](const Quarter& Q, int m0, u32x4v* pre) {
-        int c0 = Q.cb + cl;
-        asm volatile("" : "+v"(c0));           // (see issue)
-        if (!VEC) return;
+    // a wave whose wait has expired (*err is set) waits no more and goes
+    // through its steps: a way out of the loop would cost the registers that
+    // hold the loads
+    bool ok = true;
+    int pb = 0;
+    int64_t b = LOWER ? 0 : Jd - 1;
+    load_next(b, in_range(b), 0);
+    for (; in_range(b); b += bstep) {
+        const Cols C = share(0, cols_of(b));
+        const bool more = in_range(b + bstep);
+        double v0 = 0.0, v1 = 0.0;
+        if (ok) ok = wait_values(out + b * db + C.cb, C.cnt, more, v0, v1, err);
+        zs[wv][lane] = v0;
+        zs[wv][lane + 64] = v1;
+        wave_sync();
+        if (!more) __builtin_amdgcn_s_setprio(2);
+        const float usb = us;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) acc[k] = 0.0;
+        if (VEC) {
+#pragma unroll
+            for (int ph = 0; ph < PH; ++ph) {
+#pragma unroll
+                for (int m = 0; m < PF; ++m) {
+                    pin4(pre[m]);
+                    const double zc = zs[wv][cl + (ph * PF + m) * CPI];
+#pragma unroll
+                    for (int k = 0; k < RPL; ++k) acc[k] += (double)u4_elem<ST>(pre[m], k) * zc;
+                    if (m % 4 == 3) pin_sums();
+                }
+                if (ph + 1 < PH) load_next(b, true, ph + 1);
+            }
+        } else {
+            const T* base = A + rl + (b * db + C.cb) * lda;
+            for (int c = cl; c < C.cnt; c += CPI) {
+                const double zc = zs[wv][c];
+#pragma unroll
+                for (int k = 0; k < RPL; ++k)
+                    if (RPL * rg + k < rows) acc[k] += (double)Store<ST>::load(base, (int64_t)c * lda + k) * zc;
+            }
+        }
+        load_next(b + bstep, more, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        double r;
+        if constexpr (RPL == 8)
+            r = fold8(fold16(fold32(acc[0], acc[4]), fold32(acc[2], acc[6])),
+                      fold16(fold32(acc[1], acc[5]), fold32(acc[3], acc[7])));
+        else
+            r = fold16(fold32(acc[0], acc[2]), fold32(acc[1], acc[3]));
+        part[pb][wv][prow] = LOWER ? r * (1.0 / (double)usb) : r;
+        __syncthreads();
+        if (wv == 0) {
+            double t[NW];
+#pragma unroll
+            for (int u = 0; u < NW; ++u) t[u] = part[pb][u][lane];
+            w -= ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        }
+        pb ^= 1;
+    }
+    __builtin_amdgcn_s_setprio(2);
+    // this strip's rows of the block right-hand side are final (wave 0)
+    if (wv == 0) {
+        if (tid < rows) put_value(tbuf + r0 + tid, w);
+        own[tid] = w;
+    }
+    // Its rows of the inverse: each wave waits for the rows of its columns (its
+    // own strip's come from wave 0)
+    {
+        const int lim = LOWER ? ro : ro + rows;           // others' rows: below lim (L), from lim (U)
+        const int lo = LOWER ? CI.cb : (CI.cb > lim ? CI.cb : lim);
+        const int hi = LOWER ? (CI.cb + CI.cnt < lim ? CI.cb + CI.cnt : lim) : CI.cb + CI.cnt;
+        const int off = lo - CI.cb;                       // of the awaited range in the wave's columns
+        double v0 = 0.0, v1 = 0.0;
+        if (ok) ok = wait_values(tbuf + cj + lo, hi - lo, false, v0, v1, err);
+        __syncthreads();
+        // first the columns of its own strip (and zeros), then the awaited ones
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = CI.cb + lane + 64 * u - ro;
+            const bool mine = c >= 0 && c < rows && lane + 64 * u < CI.cnt;
+            zs[wv][lane + 64 * u] = mine ? own[c < 0 ? 0 : (c < TS ? c : 0)] : 0.0;
+        }
+        wave_sync();
+        if (lane < hi - lo) zs[wv][off + lane] = v0;
+        if (lane + 64 < hi - lo) zs[wv][off + lane + 64] = v1;
+        wave_sync();
+    }
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) acc[k] = 0.0;
+    for (int t0 = 0;;) {
 #pragma unroll
         for (int m = 0; m < PF; ++m) {
             pin4(pre[m]);
-            const int c = c0 + (m0 + m) * CPI;
-            const double zc = zs[c < Q.ce ? c : ZERO];
+            const double zc = zs[wv][csub + t0 + CS * m];
 #pragma unroll
-            for (int k = 0; k < RPL; ++k) acc[k] += (double)u4_elem<ST>(pre[m], k) * zc;
+            for (int k = 0; k < 4; ++k) acc[k] += (double)__uint_as_float(pre[m][k]) * zc;
+            if (m % 4 == 3) pin_sums();
         }
-    };
-    {
-        u32x4v pa[PF], pb[PF];
-        int64_t b = LOWER ? 0 : Jd - 1;
-        issue(b, in_range(b), 0, pa);
-        issue(b, in_range(b), PF, pb);
-        for (; in_range(b); b += bstep) {
-            const Quarter Q = quarter(b);
-            const int kb = cols_of(b);
-            ok = ok && wave_wait(&ready[b], 1, strips_of(b), err);
-            for (int c = tid; c < kb; c += 256) zs[c] = get_shared(out + b * db + c);
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) acc[k] = 0.0;
-            const bool more = in_range(b + bstep);
-            // (kept apart: overlapped, the registers of the old and of the new
-            // loads would all be live)
-            take(Q, 0, pa);
-            __builtin_amdgcn_sched_barrier(0);
-            issue(b + bstep, more, 0, pa);
-            __builtin_amdgcn_sched_barrier(0);
-            take(Q, PF, pb);
-            __builtin_amdgcn_sched_barrier(0);
-            issue(b + bstep, more, PF, pb);
-            __builtin_amdgcn_sched_barrier(0);
-            const T* base = A + rl + b * db * lda;
-            if (VEC) {
-#pragma unroll 4
-                for (int c = Q.cb + cl + 2 * PF * CPI; c < Q.ce; c += CPI) {
-                    const u32x4v v = *(const u32x4v*)(base + (int64_t)c * lda);
-                    const T* e = (const T*)&v;
-                    const double zc = zs[c];
-#pragma unroll
-                    for (int k = 0; k < RPL; ++k) acc[k] += (double)Store<ST>::load(e, k) * zc;
-                }
-            } else {
-                for (int c = Q.cb + cl; c < Q.ce; c += CPI) {
-                    const double zc = zs[c];
-#pragma unroll
-                    for (int k = 0; k < RPL; ++k)
-                        if (RPL * rg + k < rows) acc[k] += (double)Store<ST>::load(base, (int64_t)c * lda + k) * zc;
-                }
-            }
-            if (LOWER) {
-                // stored strips carry a power of two per factor block and 32
-                // rows; a dependency of the forward solve is a whole block, so
-                // a wave's quarter lies in one factor block
-                const int64_t i = b * (db / nb) + (int64_t)Q.cb / nb;
-                const double us = 1.0 / (double)lsc[i * nstrips32 + (r0 + RPL * rg < n ? r0 + RPL * rg : r0) / 32];
-#pragma unroll
-                for (int k = 0; k < RPL; ++k) acc[k] *= us;
-            }
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) part[wv][cl][RPL * rg + k] = acc[k];
-            __syncthreads();
-            if (tid < TS) {
-                double t[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int v2 = 0; v2 < CPI; ++v2)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) t[u] += part[u][v2][tid];
-                w -= (t[0] + t[1]) + (t[2] + t[3]);
-            }
-        }
+        t0 += PF * CS;
+        if (t0 >= CI.cnt) break;                          // wave-uniform
+        load_inverse(t0);
     }
-    // this strip's rows of the block right-hand side are final (wave 0)
-    if (wv == 0) {
-        if (tid < rows) put_shared(tbuf + r0 + tid, w);
-        sync_release();
-        if (tid == 0) __hip_atomic_store(&sflag[sidx], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // The strip's rows of its diagonal-block inverse (lower / upper triangular:
-    // a row takes the columns up to / from itself), in two half strips of HS
-    // rows.  A lane: four consecutive rows (16-byte loads), one of CS column
-    // groups; the waves split a half strip's columns.  The first loads of both
-    // are issued while the strips they depend on publish.
-    const int64_t cj = j * db;
-    const int kbj = cols_of(j);
-    const int nst = (int)strips_of(j);
-    const int s_in = (int)((r0 - cj) / TS);
-    const int rsub = lane % RQ, csub = lane / RQ;
-    const float* blkinv = inv_all + j * (int64_t)db * db;
-    struct Half {
-        int r0, clo, cb, ce;
-    };
-    auto half = [&](int h) {
-        Half H;
-        H.r0 = HS * h < kbj ? HS * h : 0;                         // past the block: nothing is stored
-        H.clo = LOWER ? 0 : H.r0;
-        const int chi = LOWER ? (H.r0 + HS < kbj ? H.r0 + HS : kbj) : kbj;
-        const int q = (chi - H.clo + 3) / 4;
-        H.cb = H.clo + wv * q;
-        H.ce = H.cb + q < chi ? H.cb + q : chi;
-        return H;
-    };
-    const Half HA = half(2 * s_in), HB = half(2 * s_in + 1);
-    constexpr int NIV = 16;               // inverse loads of a batch per lane (16 bytes each)
-    auto load_inv = [&](const Half& H, int t0, f32x4v (&iv)[NIV]) {
-        const uint32_t row = (uint32_t)(H.r0 + 4 * rsub) * 4u, ldb = (uint32_t)db * 4u;
-#pragma unroll
-        for (int t = 0; t < NIV; ++t) {
-            const int c = H.cb + csub + CS * (t0 + t);
-            iv[t] = *(const f32x4v*)((const char*)blkinv + (uint32_t)(c < H.ce ? c : H.clo) * ldb + row);
-        }
-    };
-    f32x4v ia[NIV], ib[NIV];
-    load_inv(HA, 0, ia);
-    load_inv(HB, 0, ib);
-    // the strips whose right-hand side rows this strip's rows take: those
-    // above it in the block (L), below it (U)
-    ok = ok && (LOWER ? wave_wait(sflag + sidx - s_in, s_in, 1u, err)
-                      : wave_wait(sflag + sidx + 1, nst - 1 - s_in, 1u, err));
-    {
-        // this strip's own rows come from wave 0's registers
-        const int own = s_in * TS, zlo = LOWER ? 0 : own + rows, zhi = LOWER ? own : kbj;
-        for (int c = zlo + tid; c < zhi; c += 256) zs[c] = get_shared(tbuf + cj + c);
-        if (tid < rows) zs[own + tid] = w;
-    }
+    part[pb][wv][irow] = fold16(fold32(acc[0], acc[2]), fold32(acc[1], acc[3]));
     __syncthreads();
-    auto apply = [&](const Half& H, int h, f32x4v (&iv)[NIV]) {
-        double a4[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int t0 = 0;;) {
+    if (wv == 0 && tid < rows) {
+        double t[NW];
 #pragma unroll
-            for (int t = 0; t < NIV; ++t) {
-                pin4f(iv[t]);
-                const int c = H.cb + csub + CS * (t0 + t);
-                const double zc = zs[c < H.ce ? c : ZERO];
-                a4[0] += (double)iv[t].x * zc;
-                a4[1] += (double)iv[t].y * zc;
-                a4[2] += (double)iv[t].z * zc;
-                a4[3] += (double)iv[t].w * zc;
-            }
-            t0 += NIV;
-            if (H.cb + CS * t0 >= H.ce) break;            // wave-uniform
-            load_inv(H, t0, iv);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) part[wv][csub][HS * h + 4 * rsub + k] = a4[k];
-    };
-    apply(HA, 0, ia);
-    apply(HB, 1, ib);
-    __syncthreads();
-    if (wv == 0) {
-        if (tid < rows) {
-            double t[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int v2 = 0; v2 < CS; ++v2)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) t[u] += part[u][v2][tid];
-            put_shared(out + r0 + tid, (t[0] + t[1]) + (t[2] + t[3]));
-        }
-        sync_release();
-        if (tid == 0) __hip_atomic_fetch_add(&ready[j], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int u = 0; u < NW; ++u) t[u] = part[pb][u][lane];
+        const double z = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        put_value(out + r0 + tid, z);
+        if (!LOWER) zout[py * ld_z + r0 + tid] = z;
     }
 }
 
-__global__ void k_zero_u32(unsigned* p, int64_t count) {
+__global__ void k_prec_reset(double* buf, int64_t count, unsigned* words) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < count) p[i] = 0u;
+    if (i < count) put_unset(buf + i);
+    if (i < 3) words[i] = 0u;
 }
 
-// flag words of one right-hand side: the strip flags (S = ceil(n / TS)) and
-// block flags (J = ceil(n / nb), nb >= 64) of both solves; those of the
-// first right-hand side also hold the two solves' start-order counters
-// (words 2 (S + J) and 2 (S + J) + 1)
-static int64_t trsv_flag_words(int64_t n) {
-    constexpr int64_t u = TS < 64 ? TS : 64;
-    return 4 * (n / u + 2);
-}
+// forward solution and its block right-hand sides, the backward solve's two
+// (n x nr each); the two solves' start-order counters and the error word
+size_t prec_work_bytes(int64_t n, int nr) { return (size_t)(4 * n * nr) * 8 + 256; }
 
-size_t prec_work_bytes(int64_t n, int nr) {
-    // forward solution, block right-hand sides (n x nr each), flags, error word
-    return (size_t)(2 * n * nr) * 8 + (size_t)(trsv_flag_words(n) * nr) * 4 + 256;
-}
+static unsigned* prec_words(double* W, int64_t n, int nr) { return (unsigned*)(W + 4 * n * nr); }
 
-static int* prec_err_word(double* W, int64_t n, int nr) {
-    return (int*)((unsigned*)(W + 2 * n * nr) + trsv_flag_words(n) * nr);
-}
-
-// flags, counters and the error word: once before the applies with this n, nr
-// (each solve then clears the other's)
+// the forward solve's buffers, the counters and the error word: once before the
+// applies with this n, nr (each solve then clears the other's)
 hipError_t prec_reset(double* W, int64_t n, int nr, hipStream_t s) {
-    const int64_t words = trsv_flag_words(n) * nr + 1;
-    k_zero_u32<<<(unsigned)((words + 255) / 256), 256, 0, s>>>((unsigned*)(W + 2 * n * nr), words);
+    const int64_t count = 2 * n * nr;
+    k_prec_reset<<<(unsigned)((count + 255) / 256), 256, 0, s>>>(W, count, prec_words(W, n, nr));
     return hipGetLastError();
 }
 
 hipError_t prec_err_read(double* W, int64_t n, int nr, int* err, hipStream_t s) {
-    hipError_t e = hipMemcpyAsync(err, prec_err_word(W, n, nr), sizeof(int), hipMemcpyDeviceToHost, s);
+    hipError_t e = hipMemcpyAsync(err, prec_words(W, n, nr) + 2, sizeof(int), hipMemcpyDeviceToHost, s);
     if (!e) e = hipStreamSynchronize(s);
     return e;
 }
@@ -431,25 +446,21 @@ static hipError_t prec_typed(const PrecPlan& p, const double* V, int64_t ldv, do
                              double* W, hipStream_t s) {
     typedef typename Store<ST>::T T;
     const int64_t n = p.n, nb = p.nb;
-    const int64_t J = (n + nb - 1) / nb;
     const int64_t nstrips32 = (n + 31) / 32;
     const int64_t S = (n + TS - 1) / TS;
-    double* Y = W;                 // forward solutions, nr columns (ld n)
-    double* Tb = Y + n * nr;       // block right-hand sides
-    unsigned* flags = (unsigned*)(Tb + n * nr);
-    const int64_t fw = trsv_flag_words(n);
-    int* err = prec_err_word(W, n, nr);
+    double *Y = W, *Tf = Y + n * nr, *Xb = Tf + n * nr, *Tb = Xb + n * nr;
+    unsigned* tk = prec_words(W, n, nr);
+    int* err = (int*)(tk + 2);
     const bool vec = ((p.lda * (int64_t)sizeof(T)) % 16 == 0 && ((uintptr_t)p.A) % 16 == 0);
-    unsigned *fl = flags, *fu = flags + S + J, *tk = flags + 2 * (S + J);
     const int db = (int)prec_block(nb);
     const dim3 grid((unsigned)S, (unsigned)nr);
     hipEvent_t pt = prof::begin(prof::PREC, s);
     auto solves = [&](auto VEC) {
         constexpr bool V16 = decltype(VEC)::value;
-        k_trsv<ST, true, V16><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.linv_full, p.lsc, nstrips32,
-                                                   p.rowscale, V, ldv, Tb, Y, n, fl, fu, fw, tk, tk + 1, err);
-        k_trsv<ST, false, V16><<<grid, 256, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.uinv_full, nullptr,
-                                                    nstrips32, nullptr, Y, n, Tb, Z, ldz, fu, fl, fw, tk + 1, tk, err);
+        k_trsv<ST, true, V16><<<grid, 512, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.linv_full, p.lsc, nstrips32,
+                                                   p.rowscale, V, ldv, Tf, Y, Tb, Xb, nullptr, 0, tk, tk + 1, err);
+        k_trsv<ST, false, V16><<<grid, 512, 0, s>>>(n, (int)nb, db, (const T*)p.A, p.lda, p.uinv_full, nullptr,
+                                                    nstrips32, nullptr, Y, n, Tb, Xb, Tf, Y, Z, ldz, tk + 1, tk, err);
     };
     if (vec)
         solves(std::true_type{});

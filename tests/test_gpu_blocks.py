@@ -12,6 +12,7 @@ import pytest
 import torch
 
 import paper_2509_19618_amd as mxp
+from test_gpu_factor import _dense_prec
 
 pytestmark = pytest.mark.gpu
 EPS = 2.0 ** -53
@@ -103,6 +104,28 @@ def test_ragged_last_strip_of_the_substitution(n, nb, store, lda):
         fac.LU[:, n:] = float("nan")
         out.append(mxp.mxp_apply_prec(fac, prob.B))
     assert torch.equal(out[0], out[1])
+
+
+# shares of eight waves that are empty, of one column, ragged or whole; one
+# block, a block of one column behind it, several; FP32 storage (a panel in two
+# groups of loads): against L and U in FP64 within the FP32 error of the inverses
+# (as the apply's own test: 32 D 2^-24, D the substitution's block), the same bits
+# from each right-hand side alone and again
+@pytest.mark.parametrize("n,nb,store", [(1, 64, "f16"), (65, 64, "f32"), (130, 64, "bf16"), (1025, 512, "f32"),
+                                        (1100, 1024, "f16"), (2100, 512, "bf16")])
+def test_substitution_shares(n, nb, store):
+    print("substitution", n, nb, store, flush=True)
+    prob = mxp.mxp_generate(n, 3, 51, store=store)
+    fac = mxp.mxp_factor(prob, nb, store)
+    Z = mxp.mxp_apply_prec(fac, prob.B)
+    L, U = (torch.from_numpy(M) for M in _dense_prec(prob, fac))
+    D = 2 * nb if nb <= 512 else nb
+    for r in range(3):
+        y = torch.linalg.solve_triangular(L, prob.B[r:r + 1, :n].cpu().T, upper=False, unitriangular=True)
+        z = torch.linalg.solve_triangular(U, y, upper=True)[:, 0]
+        assert float((Z[r, :n].cpu() - z).abs().max()) <= 32 * D * 2.0 ** -24 * float(z.abs().max())
+        assert torch.equal(mxp.mxp_apply_prec(fac, prob.B[r:r + 1].contiguous())[0], Z[r])
+    assert torch.equal(mxp.mxp_apply_prec(fac, prob.B), Z)
 
 
 # rows in groups of four per thread: whole, ragged, and columns that are not
