@@ -119,36 +119,27 @@ hipError_t row_equilibrate(const FactorPlan& p, const double* diag, hipStream_t 
 }
 
 // ============================================================== strip TRSMs + rounding
-typedef float f16v_t __attribute__((ext_vector_type(16)));
-MXP_DEV f16v_t mfma2(float a, float b, f16v_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
-
 constexpr int SR = 32;  // rows (columns) per strip of L21 (U12) and per scale
+constexpr int SW = 8;   // waves of a strip's work-group
+constexpr int ST_THREADS = 64 * SW;
 
-// The strip solves run on the FP32 matrix cores (v_mfma_f32_32x32x2f32):
-// lane l holds A[l%32][k0 + l/32] and B[k0 + l/32][l%32]; the 32x32 result
-// sits in 16 registers, register q of lane l being row 8(q/4) + 4(l/32) + q%4,
-// column l%32.  The strip lives in LDS (pitch odd, so the 32 rows / columns
-// a fragment touches fall in distinct banks); the factor blocks stream from
-// L2 straight into operand registers along contiguous runs.
-// v, treated as written here: a batch of LDS reads feeding an MFMA chain
-// completes before the chain (one wait), instead of one wait per product
-MXP_DEV void pin_f(float& v) { asm volatile("" : "+v"(v)); }
-
-// add the other K-half's partial results (waves 2,3 -> waves 0,1) through LDS
-MXP_DEV void khalf_reduce(f16v_t& acc, float* red, int blk, int kh, int lane) {
-    if (kh == 1)
-        for (int q = 0; q < 16; ++q) red[(blk * 16 + q) * 64 + lane] = acc[q];
-    __syncthreads();
-    if (kh == 0)
-        for (int q = 0; q < 16; ++q) acc[q] += red[(blk * 16 + q) * 64 + lane];
-}
-
-// maximum of v over the work-group (red: at least 4 floats of LDS, free)
+// The strip solves run on the FP32 matrix cores (v_mfma_f32_16x16x4f32: lane
+// l = 16 g + c holds A[c][k + g] and B[k + g][c], register q of the result row
+// 4 g + q, column c).  Both solves are one: with the strip's 32 rows (of L21) or
+// columns (of U12) as runs of nb floats in LDS, Y_J = (S_J - sum_{I<J} M_JI S_I)
+// Minv_J^T, where M(j, k) is U11(k, j), read from the column-major copy, or
+// L11(j, k), from the row-major one: k contiguous, so that a lane takes four
+// consecutive k of its run in one 16-byte load of either operand (the order of k
+// is the same for both, and free).  Eight waves: one 16 x 16 tile of the 64 x 32
+// block each, no sum over waves.
+// maximum of v over the work-group (red: SW floats of LDS, free)
 MXP_DEV float strip_max(float v, float* red) {
     v = warp_maxf(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    const float r = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    float r = red[0];
+#pragma unroll
+    for (int u = 1; u < SW; ++u) r = fmaxf(r, red[u]);
     __syncthreads();
     return r;
 }
@@ -158,176 +149,114 @@ template <class T> struct alignas(4 * sizeof(T)) Pack4 {
     T v[4];
 };
 
-// Right solve of a 32-row strip S (row i at S + i*SP): X <- S U^-1 block by
-// block, X_J = (S_J - sum_{I<J} X_I U_IJ) Uinv_J.  Urm: U11 row-major (ld),
-// uinv_rm: the 64x64 diagonal-block inverses, row-major.  The factor blocks
-// do not depend on the strip: block I+1 is loaded while block I is applied,
-// and the first block and the inverse block of step J+1 are loaded while
-// step J finishes (its reductions and inverse product), so that a step
-// never starts with a load latency.
-MXP_DEV float strip_right_solve(float* S, int SP, int nbk, const float* __restrict__ Urm, int ld,
-                                   const float* __restrict__ uinv_rm, float* red) {
-    float m = 0.0f;   // max |x| over this lane's final stores
+// Solve of a strip: run r at S + r SP, Minv the 64 x 64 diagonal-block inverses
+// (element (j, k) at j + 64 k).  The factor does not depend on the strip: two
+// 64 x 64 blocks' loads stay ahead of the products, and a step's inverse is
+// loaded while the step before it runs.  A step has two barriers: before its
+// last product (the run's newest values) and between the right-hand side, kept
+// apart from S (R, pitch 68), and its product with the inverse.  Two sums per
+// tile (alternate sixteens of k) keep consecutive products independent.
+// What bounds it, at nb = 512: 10.5 MFLOP per strip, 17 us of a CU's FP32 matrix
+// rate, and about 2 us of latencies in each of eight steps; 35 us for one strip
+// per CU.  Against four waves of 32 x 32 x 2 products (four-byte operand loads,
+// half of the sum in another wave, four barriers a step), rocprofv3, both sides'
+// strips in one launch: nb = 512 66 -> 64 us (two strips per CU), nb = 256 (a group
+// of six orders of 520 to 5003) 31 -> 24 us, nb = 256 FP32 (n = 2048)
+// 17.1 -> 15.7 us.
+MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M, int ld,
+                          const float* __restrict__ Minv, float* R) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    constexpr int RP = 68;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lr = lane & 31, lh = lane >> 5, blk = wave & 1, kh = wave >> 1;
-    const int k0 = kh * 32 + lh;
-    auto ld_iv = [&](float* v, int J) {
+    const int c = lane & 15, g = lane >> 4, tj = wave & 3, h = wave >> 2;
+    float m = 0.0f;   // max |y| over this lane's final stores
+    // one 64 x 64 block of M: this wave's 16 rows, k = 16 u + 4 g ..
+    auto ld_blk = [&](f4 (&a)[4], int J, int I) {
+        const float* ub = M + (int64_t)(J * 64 + 16 * tj) * ld + I * 64;
+        const int lo = c * ld + 4 * g;
 #pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) v[s2] = uinv_rm[(int64_t)J * 4096 + (k0 + 2 * s2) * 64 + blk * 32 + lr];
+        for (int u = 0; u < 4; ++u) a[u] = *(const f4*)(ub + lo + 16 * u);
     };
-    // a block's sixteen loads: a wave-uniform base (kept in scalar
-    // registers) plus one 32-bit lane offset
-    const int ld2 = 2 * ld;
-    auto ld_blk = [&](float* bv, int I, int J) {
-        const float* ub = Urm + (int64_t)(I * 64 + kh * 32) * ld + J * 64 + blk * 32;
-        const int lo = lh * ld + lr;
+    auto ld_inv = [&](float (&v)[16], int J) {
+        const float* ub = Minv + (int64_t)J * 4096 + 16 * tj;
+        const int lo = c + 256 * g;
 #pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) bv[s2] = ub[s2 * ld2 + lo];
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[4 * u + t] = ub[lo + (16 * u + t) * 64];
     };
-    float iv[16], ivn[16], b0[16], b1[16];
-    ld_iv(iv, 0);
+    float* const Sr = S + (16 * h + c) * SP + 4 * g;             // this lane's run, its k
+    float* const Rr = R + (16 * h + c) * RP + 4 * g;
+    f4 acc0, acc1;
+    auto mul_blk = [&](const f4 (&a)[4], int I) {
+        f4 b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = *(const f4*)(Sr + I * 64 + 16 * u);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][t], b[0][t], acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2][t], b[2][t], acc1, 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][t], b[1][t], acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3][t], b[3][t], acc1, 0, 0, 0);
+        }
+    };
+    float iv[16];
+    f4 m0[4], m1[4];
+    ld_inv(iv, 0);
     for (int J = 0; J < nbk; ++J) {
-        const int jc = J * 64 + blk * 32 + lr;            // this lane's column of the output block
-        f16v_t acc = {};
-        auto mf_blk = [&](const float* bv, int I) {
-            const int kb0 = I * 64 + k0;
-            float av[16];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) av[s2] = S[lr * SP + kb0 + 2 * s2];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) pin_f(av[s2]);
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) acc = mfma2(av[s2], bv[s2], acc);
-        };
-        // b0 holds block (0, J) for J > 0 (loaded during step J - 1)
+        acc0 = acc1 = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        // m0 holds block (J, 0), m1 block (J, 1) (loaded during step J - 1); the
+        // last block of the step takes the values the step before wrote
         int I = 0;
-        for (; I + 1 < J; I += 2) {
-            ld_blk(b1, I + 1, J);
-            mf_blk(b0, I);
-            if (I + 2 < J) ld_blk(b0, I + 2, J);
-            mf_blk(b1, I + 1);
+        for (; I + 2 < J; I += 2) {
+            mul_blk(m0, I);
+            ld_blk(m0, J, I + 2);
+            mul_blk(m1, I + 1);
+            if (I + 3 < J) ld_blk(m1, J, I + 3);
         }
-        if (I < J) mf_blk(b0, I);
+        if (I + 1 < J) mul_blk(m0, I);
+        __syncthreads();
+        if (J > 0) {
+            if (I + 1 < J) mul_blk(m1, I + 1);
+            else mul_blk(m0, I);
+        }
         if (J + 1 < nbk) {
-            ld_blk(b0, 0, J + 1);
-            ld_iv(ivn, J + 1);
+            ld_blk(m0, J + 1, 0);
+            if (J > 0) ld_blk(m1, J + 1, 1);
         }
-        khalf_reduce(acc, red, blk, kh, lane);
-        if (kh == 0)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int i = 8 * (q >> 2) + 4 * lh + (q & 3);
-                S[i * SP + jc] -= acc[q];
-            }
+        // rows 4 g + q of the tile: four consecutive values of the run
+        const int o = J * 64 + 16 * tj;
+        *(f4*)(Rr + 16 * tj) = *(const f4*)(Sr + o) - (acc0 + acc1);
         __syncthreads();
-        f16v_t y = {};
-        {
-            float av[16];
+        f4 b[4];
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) av[s2] = S[lr * SP + J * 64 + k0 + 2 * s2];
+        for (int u = 0; u < 4; ++u) b[u] = *(const f4*)(Rr + 16 * u);
+        acc0 = acc1 = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) pin_f(av[s2]);
+        for (int u = 0; u < 4; u += 2)
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) y = mfma2(av[s2], iv[s2], y);
-        }
-        khalf_reduce(y, red, blk, kh, lane);
-        if (kh == 0)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int i = 8 * (q >> 2) + 4 * lh + (q & 3);
-                S[i * SP + jc] = y[q];
-                m = fmaxf(m, fabsf(y[q]));
+            for (int t = 0; t < 4; ++t) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(iv[4 * u + t], b[u][t], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(iv[4 * u + 4 + t], b[u + 1][t], acc1, 0, 0, 0);
             }
-        __syncthreads();
+        if (J + 1 < nbk) ld_inv(iv, J + 1);
+        const f4 y = acc0 + acc1;
+        *(f4*)(Sr + o) = y;
 #pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) iv[s2] = ivn[s2];
+        for (int q = 0; q < 4; ++q) m = fmaxf(m, fabsf(y[q]));
     }
-    return strip_max(m, red);
+    __syncthreads();
+    return strip_max(m, R);
 }
 
-// Left solve of a 32-column strip S (column j at S + j*SP): Y <- L^-1 S,
-// Y_I = Linv_I (S_I - sum_{J<I} L_IJ Y_J).  T: L11 column-major (ld),
-// linv: the 64x64 diagonal-block inverses, column-major.  Loads are
-// pipelined as in the right solve.
-MXP_DEV float strip_left_solve(float* S, int SP, int nbk, const float* __restrict__ T, int ld,
-                                  const float* __restrict__ linv, float* red) {
-    float m = 0.0f;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lr = lane & 31, lh = lane >> 5, blk = wave & 1, kh = wave >> 1;
-    const int k0 = kh * 32 + lh;
-    auto ld_iv = [&](float* v, int I) {
-#pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) v[s2] = linv[(int64_t)I * 4096 + (blk * 32 + lr) + 64 * (k0 + 2 * s2)];
-    };
-    const int ld2 = 2 * ld;
-    auto ld_blk = [&](float* av, int J, int I) {
-        const float* ub = T + I * 64 + blk * 32 + (int64_t)(J * 64 + kh * 32) * ld;
-        const int lo = lr + lh * ld;
-#pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) av[s2] = ub[s2 * ld2 + lo];
-    };
-    float iv[16], ivn[16], a0[16], a1[16];
-    ld_iv(iv, 0);
-    for (int I = 0; I < nbk; ++I) {
-        f16v_t acc = {};
-        auto mf_blk = [&](const float* av, int J) {
-            const int kb0 = J * 64 + k0;
-            float bv[16];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) bv[s2] = S[lr * SP + kb0 + 2 * s2];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) pin_f(bv[s2]);
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) acc = mfma2(av[s2], bv[s2], acc);
-        };
-        // a0 holds block (I, 0) for I > 0 (loaded during step I - 1)
-        int J = 0;
-        for (; J + 1 < I; J += 2) {
-            ld_blk(a1, J + 1, I);
-            mf_blk(a0, J);
-            if (J + 2 < I) ld_blk(a0, J + 2, I);
-            mf_blk(a1, J + 1);
-        }
-        if (J < I) mf_blk(a0, J);
-        if (I + 1 < nbk) {
-            ld_blk(a0, 0, I + 1);
-            ld_iv(ivn, I + 1);
-        }
-        khalf_reduce(acc, red, blk, kh, lane);
-        if (kh == 0)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int i = I * 64 + blk * 32 + 8 * (q >> 2) + 4 * lh + (q & 3);
-                S[lr * SP + i] -= acc[q];
-            }
-        __syncthreads();
-        f16v_t y = {};
-        {
-            float bv[16];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) bv[s2] = S[lr * SP + I * 64 + k0 + 2 * s2];
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) pin_f(bv[s2]);
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) y = mfma2(iv[s2], bv[s2], y);
-        }
-        khalf_reduce(y, red, blk, kh, lane);
-        if (kh == 0)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int i = I * 64 + blk * 32 + 8 * (q >> 2) + 4 * lh + (q & 3);
-                S[lr * SP + i] = y[q];
-                m = fmaxf(m, fabsf(y[q]));
-            }
-        __syncthreads();
-#pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) iv[s2] = ivn[s2];
-    }
-    return strip_max(m, red);
-}
-
-// LDS of a strip kernel: the strip (32 x (nb+1) floats) and the K-half reduction buffer
-static inline size_t trsm_smem(int nb) { return (size_t)(SR * (nb + 1) + 2 * 16 * 64) * sizeof(float); }
+// LDS of a strip kernel: the strip (32 runs, 16-byte aligned, of pitch nb + 4:
+// the sixteen runs a load touches fall in distinct banks) and a step's right-hand
+// side
+MXP_DEV int strip_pitch(int nb) { return nb + 4; }
+static inline size_t trsm_smem(int nb) { return (size_t)(SR * (nb + 4) + SR * 68) * sizeof(float); }
 
 // L21 strip: X (32 x nb) = A21[rows, :] U11^-1, then amax -> power-of-two
 // scales; writes the operand Lq (K-major, update format, scaled), the stored
@@ -337,11 +266,11 @@ static inline size_t trsm_smem(int nb) { return (size_t)(SR * (nb + 1) + 2 * 16 
 // last strip takes element accesses.
 template <int ST, int OP>
 MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int64_t k, int nb,
-                          const float* __restrict__ Urm, const float* __restrict__ uinv,
+                          const float* __restrict__ T, const float* __restrict__ uinv,
                           typename Operand<OP>::T* Lq, float* inv_sa, float* lsc_blk, float* smem, int w) {
     typedef typename Store<ST>::T STT;
     typedef typename Operand<OP>::T OPT;
-    const int SP = nb + 1;
+    const int SP = strip_pitch(nb);
     float* S = smem;
     float* red = smem + SR * SP;
     const int tid = threadIdx.x;
@@ -349,21 +278,21 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
     int64_t rv = n - r0;
     rv = rv > SR ? SR : (rv < 0 ? 0 : rv);
     const bool vec = rv == SR && (r0 & 3) == 0 && (lda & 3) == 0 && ((uintptr_t)A & 15) == 0;
-    const int rq = tid & 7, cg = tid >> 3;          // vector mapping: rows 4 rq.., column cg + 32 i
+    const int rq = tid & 7, cg = tid >> 3;          // vector mapping: rows 4 rq.., column cg + 64 i
     if (vec) {
         for (int c0 = 0; c0 < nb; c0 += 512) {
             // loads without conditions (a column past nb reads column 0,
             // unused): a load under a branch ends in a wait for every load in
             // flight, which would serialise them
-            Pack4<STT> x[16];
+            Pack4<STT> x[8];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int c = c0 + cg + 32 * i;
+            for (int i = 0; i < 8; ++i) {
+                const int c = c0 + cg + 64 * i;
                 x[i] = *(const Pack4<STT>*)(A + (r0 + 4 * rq) + (k + (c < nb ? c : 0)) * lda);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int c = c0 + cg + 32 * i;
+            for (int i = 0; i < 8; ++i) {
+                const int c = c0 + cg + 64 * i;
                 if (c < nb)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) S[(4 * rq + q) * SP + c] = Store<ST>::load(x[i].v, q);
@@ -371,11 +300,11 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
         }
     } else {
         const int ii = tid & 31;
-        for (int c = tid >> 5; c < nb; c += 8)
+        for (int c = tid >> 5; c < nb; c += ST_THREADS / 32)
             S[ii * SP + c] = (ii < rv) ? Store<ST>::load(A, (r0 + ii) + (k + c) * lda) : 0.0f;
     }
     __syncthreads();
-    const float amax = strip_right_solve(S, SP, nb / 64, Urm, nb, uinv, red);
+    const float amax = strip_solve(S, SP, nb / 64, T, nb, uinv, red);
     const float s_op = Operand<OP>::scaled ? pow2_scale(amax, Operand<OP>::scale_exp) : 1.0f;
     const float s_st = Store<ST>::scaled ? pow2_scale(amax, Store<ST>::scale_exp) : 1.0f;
     if (tid == 0) {
@@ -384,7 +313,7 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
     }
     // operand rows (nb contiguous values each): 4 columns per lane
     OPT* Lw = Lq + (int64_t)SR * w * nb;
-    for (int e = 4 * tid; e < SR * nb; e += 1024) {
+    for (int e = 4 * tid; e < SR * nb; e += 4 * ST_THREADS) {
         const int ii = e / nb, c = e - ii * nb;      // nb is a multiple of 64: a lane's 4 stay in one row
         Pack4<OPT> o;
 #pragma unroll
@@ -392,7 +321,7 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
         *(Pack4<OPT>*)(Lw + e) = o;
     }
     if (vec) {
-        for (int c = cg; c < nb; c += 32) {
+        for (int c = cg; c < nb; c += ST_THREADS / 8) {
             Pack4<STT> o;
 #pragma unroll
             for (int q = 0; q < 4; ++q) o.v[q] = Store<ST>::from_f32(S[(4 * rq + q) * SP + c] * s_st);
@@ -401,7 +330,7 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
     } else {
         const int ii = tid & 31;
         if (ii < rv)
-            for (int c = tid >> 5; c < nb; c += 8) A[(r0 + ii) + (k + c) * lda] = Store<ST>::from_f32(S[ii * SP + c] * s_st);
+            for (int c = tid >> 5; c < nb; c += ST_THREADS / 32) A[(r0 + ii) + (k + c) * lda] = Store<ST>::from_f32(S[ii * SP + c] * s_st);
     }
 }
 
@@ -410,34 +339,34 @@ MXP_DEV void trsm_L_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
 // the L21 strip, a lane taking 4 consecutive rows of one column.
 template <int ST, int OP>
 MXP_DEV void trsm_U_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int64_t k, int nb,
-                          const float* __restrict__ T, const float* __restrict__ linv,
+                          const float* __restrict__ Trm, const float* __restrict__ linv,
                           typename Operand<OP>::T* Uq, float* inv_sb, float* smem, int w) {
     typedef typename Store<ST>::T STT;
     typedef typename Operand<OP>::T OPT;
-    const int SP = nb + 1;
+    const int SP = strip_pitch(nb);
     float* S = smem;
     float* red = smem + SR * SP;
     const int tid = threadIdx.x;
     const int64_t c0 = k + nb + (int64_t)SR * w;
     int64_t cv = n - c0;
     cv = cv > SR ? SR : (cv < 0 ? 0 : cv);
-    // nb divides 1024: a pass covers 1024 / nb columns, a lane 4 rows
+    // nb divides 1024: a load of the work-group covers 2048 / nb columns, a lane 4 rows
     const int qpc = nb >> 2, lq = __builtin_ctz((unsigned)qpc);
-    const int kq = tid & (qpc - 1), cs = tid >> lq, cpp = 256 >> lq;
+    const int kq = tid & (qpc - 1), cs = tid >> lq, cpp = ST_THREADS >> lq;
     const bool vec = (1024 % nb) == 0 && (k & 3) == 0 && (lda & 3) == 0 && ((uintptr_t)A & 15) == 0;
     if (vec) {
-        for (int p0 = 0; p0 < SR; p0 += 16 * cpp) {
+        for (int p0 = 0; p0 < SR; p0 += 8 * cpp) {
             // loads without conditions, as in the L21 strip (a column past the
             // matrix reads column k + nb, unused)
-            Pack4<STT> x[16];
+            Pack4<STT> x[8];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < 8; ++i) {
                 const int cc = p0 + cs + cpp * i;
                 const int64_t col = (cc < SR && cc < cv) ? c0 + cc : k + nb;
                 x[i] = *(const Pack4<STT>*)(A + (k + 4 * kq) + col * lda);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < 8; ++i) {
                 const int cc = p0 + cs + cpp * i;
                 if (cc < SR)
 #pragma unroll
@@ -446,11 +375,11 @@ MXP_DEV void trsm_U_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
         }
     } else {
         for (int cc = 0; cc < SR; ++cc)
-            for (int kk = tid; kk < nb; kk += 256)
+            for (int kk = tid; kk < nb; kk += ST_THREADS)
                 S[cc * SP + kk] = (cc < cv) ? Store<ST>::load(A, (k + kk) + (c0 + cc) * lda) : 0.0f;
     }
     __syncthreads();
-    const float amax = strip_left_solve(S, SP, nb / 64, T, nb, linv, red);
+    const float amax = strip_solve(S, SP, nb / 64, Trm, nb, linv, red);
     const float s_op = Operand<OP>::scaled ? pow2_scale(amax, Operand<OP>::scale_exp) : 1.0f;
     if (tid == 0) inv_sb[w] = 1.0f / s_op;
     OPT* Uw = Uq + (int64_t)SR * w * nb;
@@ -469,7 +398,7 @@ MXP_DEV void trsm_U_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
         }
     } else {
         for (int cc = 0; cc < SR; ++cc)
-            for (int kk = tid; kk < nb; kk += 256) {
+            for (int kk = tid; kk < nb; kk += ST_THREADS) {
                 Uw[(int64_t)cc * nb + kk] = Operand<OP>::from_f32(S[cc * SP + kk] * s_op);
                 if (cc < cv) A[(k + kk) + (c0 + cc) * lda] = Store<ST>::from_f32(S[cc * SP + kk]);
             }
@@ -484,7 +413,7 @@ struct TrsmOne {
     void* A;
     int64_t lda, n, k;
     int nb, nstrip, wg_end, pad;
-    const float *Urm, *uinv, *T, *linv;
+    const float *T, *uinv, *Trm, *linv;
     void* Lq;
     float* inv_sa;
     float* lsc_blk;
@@ -497,7 +426,7 @@ struct TrsmGroup {
 };
 
 template <int ST, int OP>
-__global__ __launch_bounds__(256) void k_trsm(const TrsmGroup grp) {
+__global__ __launch_bounds__(ST_THREADS, 4) void k_trsm(const TrsmGroup grp) {
     extern __shared__ float smem[];
     int d = 0;
     while ((int)blockIdx.x >= grp.g[d].wg_end) ++d;
@@ -505,45 +434,51 @@ __global__ __launch_bounds__(256) void k_trsm(const TrsmGroup grp) {
     const int w = (int)blockIdx.x - (d > 0 ? grp.g[d - 1].wg_end : 0);
     typename Store<ST>::T* A = (typename Store<ST>::T*)G.A;
     if (w < G.nstrip)
-        trsm_L_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.Urm, G.uinv, (typename Operand<OP>::T*)G.Lq, G.inv_sa,
+        trsm_L_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.T, G.uinv, (typename Operand<OP>::T*)G.Lq, G.inv_sa,
                              G.lsc_blk, smem, w);
     else
-        trsm_U_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.T, G.linv, (typename Operand<OP>::T*)G.Uq, G.inv_sb, smem,
+        trsm_U_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.Trm, G.linv, (typename Operand<OP>::T*)G.Uq, G.inv_sb, smem,
                              w - G.nstrip);
 }
 
+// the solve of runs that are zero before their element 64 j0 (and stay so)
+MXP_DEV void strip_solve_from(int j0, float* S, int SP, int nbk, const float* __restrict__ M, int ld,
+                              const float* __restrict__ Minv, float* R) {
+    strip_solve(S + 64 * j0, SP, nbk - j0, M + (int64_t)64 * j0 * (ld + 1), ld, Minv + 4096 * j0, R);
+}
+
 // Full FP32 inverses of a diagonal block (size kbp) by strips of 32:
-// U11^-1 rows r0..r0+31 = I[r0:r0+32, :] U11^-1 (right solve with Trm, the
-// factor row-major), L11^-1 columns c0..c0+31 = L11^-1 I[:, c0:c0+32] (left
-// solve with T, column-major); out: the inverse, column-major, ld D.
-MXP_DEV void inv_upper_strip(int kbp, const float* __restrict__ Trm, int ld, const float* __restrict__ uinv,
+// U11^-1 rows r0..r0+31 = I[r0:r0+32, :] U11^-1 (with T, the factor
+// column-major), L11^-1 columns c0..c0+31 = L11^-1 I[:, c0:c0+32] (with Trm,
+// row-major); out: the inverse, column-major, ld D.
+MXP_DEV void inv_upper_strip(int kbp, const float* __restrict__ T, int ld, const float* __restrict__ uinv,
                              float* __restrict__ out, int64_t D, int r0, float* smem) {
-    const int SP = kbp + 1;
+    const int SP = strip_pitch(kbp);
     float* S = smem;
     float* red = smem + SR * SP;
-    for (int e = threadIdx.x; e < SR * kbp; e += 256) {
+    for (int e = threadIdx.x; e < SR * kbp; e += ST_THREADS) {
         int ii = e % SR, c = e / SR;
         S[ii * SP + c] = (r0 + ii == c) ? 1.0f : 0.0f;
     }
     __syncthreads();
-    strip_right_solve(S, SP, kbp / 64, Trm, ld, uinv, red);
-    for (int e = threadIdx.x; e < SR * kbp; e += 256) {
+    strip_solve_from(r0 / 64, S, SP, kbp / 64, T, ld, uinv, red);
+    for (int e = threadIdx.x; e < SR * kbp; e += ST_THREADS) {
         int ii = e % SR, c = e / SR;
         out[(r0 + ii) + (int64_t)c * D] = S[ii * SP + c];
     }
 }
-MXP_DEV void inv_lower_strip(int kbp, const float* __restrict__ T, int ld, const float* __restrict__ linv,
+MXP_DEV void inv_lower_strip(int kbp, const float* __restrict__ Trm, int ld, const float* __restrict__ linv,
                              float* __restrict__ out, int64_t D, int c0, float* smem) {
-    const int SP = kbp + 1;
+    const int SP = strip_pitch(kbp);
     float* S = smem;
     float* red = smem + SR * SP;
-    for (int e = threadIdx.x; e < SR * kbp; e += 256) {
+    for (int e = threadIdx.x; e < SR * kbp; e += ST_THREADS) {
         int kk = e % kbp, cc = e / kbp;
         S[cc * SP + kk] = (kk == c0 + cc) ? 1.0f : 0.0f;
     }
     __syncthreads();
-    strip_left_solve(S, SP, kbp / 64, T, ld, linv, red);
-    for (int e = threadIdx.x; e < SR * kbp; e += 256) {
+    strip_solve_from(c0 / 64, S, SP, kbp / 64, Trm, ld, linv, red);
+    for (int e = threadIdx.x; e < SR * kbp; e += ST_THREADS) {
         int kk = e % kbp, cc = e / kbp;
         out[kk + (int64_t)(c0 + cc) * D] = S[cc * SP + kk];
     }
@@ -554,7 +489,7 @@ MXP_DEV void inv_lower_strip(int kbp, const float* __restrict__ T, int ld, const
 // solved by substitution otherwise); blockIdx.y = block - blk0, blockIdx.x = strip.  Block blk is
 // diagonal block blk % g of the preconditioner's group blk / g
 // (column-major, ld D).
-__global__ __launch_bounds__(256) void k_inv_upper(int64_t n, int nb, int64_t blk0, const float* __restrict__ Trm_all,
+__global__ __launch_bounds__(ST_THREADS) void k_inv_upper(int64_t n, int nb, int64_t blk0, const float* __restrict__ Tall,
                                                    const float* __restrict__ uinv_all, float* __restrict__ out_all) {
     extern __shared__ float smem[];
     const int64_t blk = blk0 + blockIdx.y;
@@ -564,11 +499,11 @@ __global__ __launch_bounds__(256) void k_inv_upper(int64_t n, int nb, int64_t bl
     const int r0 = SR * blockIdx.x;
     if (r0 >= kbp) return;
     const int64_t D = prec_block(nb), g = D / nb, o = (blk % g) * nb;
-    inv_upper_strip(kbp, Trm_all + blk * nb * nb, nb, uinv_all + blk * nb * 64,
+    inv_upper_strip(kbp, Tall + blk * nb * nb, nb, uinv_all + blk * nb * 64,
                     out_all + (blk / g) * D * D + o + o * D, D, r0, smem);
 }
 
-__global__ __launch_bounds__(256) void k_inv_lower(int64_t n, int nb, int64_t blk0, const float* __restrict__ Tall,
+__global__ __launch_bounds__(ST_THREADS) void k_inv_lower(int64_t n, int nb, int64_t blk0, const float* __restrict__ Trm_all,
                                                    const float* __restrict__ linv_all, float* __restrict__ out_all) {
     extern __shared__ float smem[];
     const int64_t blk = blk0 + blockIdx.y;
@@ -578,7 +513,7 @@ __global__ __launch_bounds__(256) void k_inv_lower(int64_t n, int nb, int64_t bl
     const int c0 = SR * blockIdx.x;
     if (c0 >= kbp) return;
     const int64_t D = prec_block(nb), g = D / nb, o = (blk % g) * nb;
-    inv_lower_strip(kbp, Tall + blk * nb * nb, nb, linv_all + blk * nb * 64,
+    inv_lower_strip(kbp, Trm_all + blk * nb * nb, nb, linv_all + blk * nb * 64,
                     out_all + (blk / g) * D * D + o + o * D, D, c0, smem);
 }
 
@@ -586,15 +521,15 @@ __global__ __launch_bounds__(256) void k_inv_lower(int64_t n, int nb, int64_t bl
 // right after each diagonal-block LU, they serve the strip products and
 // later the preconditioner): work-groups [0, kbp/32) of a descriptor solve
 // the strips of L11^-1, the next kbp/32 those of U11^-1
-__global__ __launch_bounds__(256) void k_block_inv(const PanelGroup grp) {
+__global__ __launch_bounds__(ST_THREADS) void k_block_inv(const PanelGroup grp) {
     extern __shared__ float smem[];
     int d = 0;
     while ((int)blockIdx.x >= grp.g[d].wg_inv) ++d;
     const PanelOne& G = grp.g[d];
     const int w0 = (int)blockIdx.x - (d > 0 ? grp.g[d - 1].wg_inv : 0);
     const int nstr = G.kbp / SR;
-    if (w0 < nstr) inv_lower_strip(G.kbp, G.T, G.nb, G.linv, G.Li, G.ldi, SR * w0, smem);
-    else inv_upper_strip(G.kbp, G.Trm, G.nb, G.uinv, G.Ui, G.ldi, SR * (w0 - nstr), smem);
+    if (w0 < nstr) inv_lower_strip(G.kbp, G.Trm, G.nb, G.linv, G.Li, G.ldi, SR * w0, smem);
+    else inv_upper_strip(G.kbp, G.T, G.nb, G.uinv, G.Ui, G.ldi, SR * (w0 - nstr), smem);
 }
 
 hipError_t block_inverses(const PanelGroup& grp, int wg, int nbmax, hipStream_t s) {
@@ -602,7 +537,7 @@ hipError_t block_inverses(const PanelGroup& grp, int wg, int nbmax, hipStream_t 
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        (int)trsm_smem(1024));
     if (attr) return attr;
-    k_block_inv<<<wg, 256, trsm_smem(nbmax), s>>>(grp);
+    k_block_inv<<<wg, ST_THREADS, trsm_smem(nbmax), s>>>(grp);
     return hipGetLastError();
 }
 
@@ -620,6 +555,8 @@ hipError_t block_inverses(const PanelGroup& grp, int wg, int nbmax, hipStream_t 
 // rows fall on distinct banks); B is written with k running over the lanes
 // (pitch 97, odd: 32 consecutive k rows on distinct banks)
 constexpr int PP_SP = 96, PP_SPB = 97;
+typedef float f16v_t __attribute__((ext_vector_type(16)));
+MXP_DEV f16v_t mfma2(float a, float b, f16v_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
 // acc (wave (wr, wc)'s 32 x 32 part of the 64 x 64 tile) += A[i0.., k] B[k, j0..] over k in [k_lo, k_hi);
 // the next chunk's operands are loaded into registers before this chunk's
@@ -771,8 +708,8 @@ static hipError_t prec_inverses(const FactorPlan& p, float* W, hipStream_t s) {
     dim3 g((unsigned)(nb / SR), (unsigned)(nblk - blk0));
     hipEvent_t pt = prof::begin(prof::DIAG, s);
     if (blk0 < nblk) {
-        k_inv_upper<<<g, 256, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.Trm, p.uinv, p.uinv_full);
-        k_inv_lower<<<g, 256, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.T, p.linv, p.linv_full);
+        k_inv_upper<<<g, ST_THREADS, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.T, p.uinv, p.uinv_full);
+        k_inv_lower<<<g, ST_THREADS, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.Trm, p.linv, p.linv_full);
     }
     double fl = 2.0 / 3.0 * (double)n * nb * nb;
     if (prec_block(nb) == 2 * nb && n > nb) {
@@ -861,7 +798,7 @@ static void trsm_desc(const FactorPlan& p, int64_t k, TrsmOne& g, int wg_begin) 
     g.A = p.A; g.lda = p.lda; g.n = p.n; g.k = k; g.nb = nb; g.nstrip = nstrip;
     g.wg_end = wg_begin + 2 * nstrip;
     g.pad = 0;
-    g.Urm = p.Trm + blk * nb * nb;
+    g.Trm = p.Trm + blk * nb * nb;
     g.uinv = p.uinv + blk * nb * 64;
     g.T = p.T + blk * nb * nb;
     g.linv = p.linv + blk * nb * 64;
@@ -1038,7 +975,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         trsm_desc<ST, OP>(p, k, grp.g[0], 0);
         grp.count = 1;
         hipEvent_t pt = prof::begin(prof::TRSM, st);
-        k_trsm<ST, OP><<<grp.g[0].wg_end, 256, trsm_smem(nb), st>>>(grp);
+        k_trsm<ST, OP><<<grp.g[0].wg_end, ST_THREADS, trsm_smem(nb), st>>>(grp);
         prof::end(pt, prof::TRSM, st, 2.0 * m * (double)nb * nb,
                   4.0 * m * (double)nb * sizeof(ST_T) + 2.0 * m * (double)nb * sizeof(OP_T));
         return hipGetLastError();
@@ -1225,7 +1162,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
         if (!nt) return hipSuccess;
         tg.count = nt;
         hipEvent_t pt = prof::begin(prof::TRSM, s);
-        k_trsm<ST, OP><<<wg, 256, trsm_smem(nbmax), s>>>(tg);
+        k_trsm<ST, OP><<<wg, ST_THREADS, trsm_smem(nbmax), s>>>(tg);
         prof::end(pt, prof::TRSM, s, 0.0, 0.0);
         return hipGetLastError();
     };
