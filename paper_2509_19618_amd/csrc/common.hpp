@@ -266,6 +266,14 @@ MXP_DEV void sync_acquire() {
 #endif
 }
 
+// LDS that a launch of few work-groups asks for so that each gets a CU of its own
+// (two do not fit its 160 KB, one still fits beside a work-group of the trailing
+// update): the hardware fills a CU before it takes the next, also where there
+// are more CUs than work-groups.  Strip solves of one factorisation at
+// nb = 512, at most one strip per CU: 70 -> 48 us.
+constexpr size_t OWN_CU_LDS = 82 * 1024;
+constexpr int NUM_CU = 256;
+
 // ------------------------------------------------------------------ copies into LDS
 // Direct global->LDS copy of 16 bytes per lane: lane L lands at l + 16 L
 // (l is wave-uniform).  gfx950 global_load_lds_dwordx4.

@@ -777,7 +777,10 @@ __global__ __launch_bounds__(DT, 4) void k_diag_lu(const DiagGroup grp) {
     }
 }
 
-size_t diag_lu_smem() { return (size_t)(O_END > DW * FAC_F ? O_END : DW * FAC_F) * sizeof(float); }
+size_t diag_lu_smem() {
+    const size_t need = (size_t)(O_END > DW * FAC_F ? O_END : DW * FAC_F) * sizeof(float);
+    return need < OWN_CU_LDS ? OWN_CU_LDS : need;
+}
 
 // most work-groups cooperating on one diagonal block
 #ifndef MXP_DIAG_WGS

@@ -131,8 +131,8 @@ struct DiagCall {
 struct PanelOne {
     void* A;
     int64_t lda, n, k, ldi;
-    int nb, kbp, ntile, pad;                 // ntile: output tiles of panel_rows(launch nb) per side
-    int wg_inv, wg_split, wg_trsm, pad2;
+    int nb, kbp, tile0, ntile;               // output tiles of panel_rows(launch nb) per side: tile0 ..
+    int wg_inv, wg_split, wg_trsm, pad;
     const float *T, *Trm, *linv, *uinv;      // the block's FP32 factor and 64x64 sub-block inverses
     float *Li, *Ui;                          // the block's FP32 inverses (column-major, ld ldi)
     void *lb, *ub;                           // their 16-bit parts
@@ -157,16 +157,19 @@ hipError_t diag_lu_group(int store, const DiagCall* calls, int count, hipStream_
 hipError_t diag_lu(int store, void* A, int64_t lda, int64_t k, int kb, int kbp, float* T, float* Trm, int ldt,
                    float* linv, float* uinv, int* sync, unsigned long long* info, hipStream_t s);
 hipError_t row_equilibrate(const FactorPlan& p, const double* diag, hipStream_t s);
-// Side stream and events of the look-ahead (default stream priority): the
-// side stream carries the chain of a factorisation (diagonal-block update,
-// LU, strip TRSMs, the next block column and row by one step); the events
-// order it against the caller's stream, which runs the merged updates
-// (ev_upd: the last part of a pair's update, ev_cross / ev_next: its first
-// two parts, ev_panel: the panels of the next pair).  A factorisation uses
-// the caller's context, or one from a per-device pool if la is NULL.
+// Streams and events of the look-ahead (default stream priority): the chain
+// stream carries what the next diagonal block waits for (diagonal-block
+// updates and LUs, the strips next to them), the side stream the other strips
+// and the next block column and row by one step; the events order them against
+// the caller's stream, which runs the merged updates (ev_upd: the last part of
+// a pair's update, ev_cross: its first part, ev_diag: a diagonal block's LU,
+// ev_first: the strips next to it, ev_panel and ev_side: what the two streams have of the panels
+// of a pair).  A factorisation uses the caller's context,
+// or one from a per-device pool if la is NULL.
 struct Lookahead {
-    hipStream_t side = nullptr;
-    hipEvent_t ev_upd = nullptr, ev_cross = nullptr, ev_next = nullptr, ev_panel = nullptr;
+    hipStream_t side = nullptr, chain = nullptr;
+    hipEvent_t ev_upd = nullptr, ev_cross = nullptr, ev_diag = nullptr, ev_first = nullptr,
+               ev_panel = nullptr, ev_side = nullptr;
 };
 hipError_t lookahead_create(Lookahead* la);
 void lookahead_destroy(Lookahead* la);

@@ -257,6 +257,9 @@ MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M
 // side
 MXP_DEV int strip_pitch(int nb) { return nb + 4; }
 static inline size_t trsm_smem(int nb) { return (size_t)(SR * (nb + 4) + SR * 68) * sizeof(float); }
+static inline size_t trsm_smem(int nb, int wgs) {
+    return wgs <= NUM_CU && trsm_smem(nb) < OWN_CU_LDS ? OWN_CU_LDS : trsm_smem(nb);
+}
 
 // L21 strip: X (32 x nb) = A21[rows, :] U11^-1, then amax -> power-of-two
 // scales; writes the operand Lq (K-major, update format, scaled), the stored
@@ -405,14 +408,14 @@ MXP_DEV void trsm_U_strip(typename Store<ST>::T* A, int64_t lda, int64_t n, int6
     }
 }
 
-// Both strip solves of one block step in one launch: work-groups [0, nstrip)
-// solve the L21 strips, [nstrip, 2 nstrip) the U12 strips (independent).  One
+// Both strip solves of one block step in one launch: the first nstrip
+// work-groups solve L21 strips, the next nstrip U12 strips (independent).  One
 // launch serves a group of factorisations (one per request of the solve
 // server, or a single one): their work-groups are numbered one after another.
 struct TrsmOne {
     void* A;
     int64_t lda, n, k;
-    int nb, nstrip, wg_end, pad;
+    int nb, s0, nstrip, wg_end;              // strips s0 .. s0 + nstrip - 1 of each side
     const float *T, *uinv, *Trm, *linv;
     void* Lq;
     float* inv_sa;
@@ -435,10 +438,10 @@ __global__ __launch_bounds__(ST_THREADS, 4) void k_trsm(const TrsmGroup grp) {
     typename Store<ST>::T* A = (typename Store<ST>::T*)G.A;
     if (w < G.nstrip)
         trsm_L_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.T, G.uinv, (typename Operand<OP>::T*)G.Lq, G.inv_sa,
-                             G.lsc_blk, smem, w);
+                             G.lsc_blk, smem, G.s0 + w);
     else
         trsm_U_strip<ST, OP>(A, G.lda, G.n, G.k, G.nb, G.Trm, G.linv, (typename Operand<OP>::T*)G.Uq, G.inv_sb, smem,
-                             w - G.nstrip);
+                             G.s0 + w - G.nstrip);
 }
 
 // the solve of runs that are zero before their element 64 j0 (and stay so)
@@ -537,7 +540,7 @@ hipError_t block_inverses(const PanelGroup& grp, int wg, int nbmax, hipStream_t 
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        (int)trsm_smem(1024));
     if (attr) return attr;
-    k_block_inv<<<wg, ST_THREADS, trsm_smem(nbmax), s>>>(grp);
+    k_block_inv<<<wg, ST_THREADS, trsm_smem(nbmax, wg), s>>>(grp);
     return hipGetLastError();
 }
 
@@ -675,21 +678,30 @@ __global__ __launch_bounds__(256) void k_pair_upper(int64_t n, int nb, const typ
     }
 }
 
-// the full FP32 inverses of the preconditioner's diagonal blocks (after the
-// factorisation): every factor block's, then the off-diagonal blocks of the
-// pairs.  W: scratch of ceil(n / 2nb) nb^2 floats.
-// Block step k solves its strips through the block inverses (16-bit storage)
-// while the trailing part is at least MXP_PANEL_MIN blocks: there the
+// The strips of block step k.  While they are no more than the CUs, one launch
+// solves them all, a CU each.  Above, the first ones -- the next block's rows and
+// columns, all that the next diagonal block waits for -- are solved on their own
+// by substitution (44 to 48 us at nb = 512 where all strips of a step take 70 to
+// 75 us and more beside the merged update), the others after them.
+static int strip_count(const FactorPlan& p, int64_t k) {
+    const int64_t m = p.n - k - p.nb;
+    return m > 0 ? (int)(rup(m, 256) / SR) : 0;
+}
+static int first_strips(const FactorPlan& p, int64_t k) {
+    return 2 * strip_count(p, k) <= NUM_CU ? strip_count(p, k) : (int)(p.nb / SR);
+}
+
+// Block step k solves its other strips through the block inverses (16-bit
+// storage) while the trailing part is at least MXP_PANEL_MIN blocks: there the
 // products free the compute units the substitution would hold beside the
-// merged update; the last steps, bound by the chain of panel solves, keep the
-// substitution, whose latency is lower.  Depends on (n, nb, k) alone, so that
-// grouped and single factorisations take the same path.
+// merged update.  Depends on (n, nb, k) alone, so that grouped and single
+// factorisations take the same path.
 #ifndef MXP_PANEL_MIN
 #define MXP_PANEL_MIN 16
 #endif
 static bool inverse_path(const FactorPlan& p, int64_t k) {
-    const int64_t kb = p.n - k < p.nb ? p.n - k : p.nb;
-    return panel_path(p.store) && p.n - k - kb >= MXP_PANEL_MIN * p.nb;
+    return panel_path(p.store) && strip_count(p, k) > first_strips(p, k) &&
+           p.n - k - p.nb >= MXP_PANEL_MIN * p.nb;
 }
 // the first block whose inverses are formed after the factorisation
 static int64_t inv_first_after(const FactorPlan& p) {
@@ -699,6 +711,9 @@ static int64_t inv_first_after(const FactorPlan& p) {
     return b;
 }
 
+// the full FP32 inverses of the preconditioner's diagonal blocks (after the
+// factorisation): every factor block's, then the off-diagonal blocks of the
+// pairs.  W: scratch of ceil(n / 2nb) nb^2 floats.
 template <int ST>
 static hipError_t prec_inverses(const FactorPlan& p, float* W, hipStream_t s) {
     const int64_t n = p.n, nb = p.nb;
@@ -708,8 +723,9 @@ static hipError_t prec_inverses(const FactorPlan& p, float* W, hipStream_t s) {
     dim3 g((unsigned)(nb / SR), (unsigned)(nblk - blk0));
     hipEvent_t pt = prof::begin(prof::DIAG, s);
     if (blk0 < nblk) {
-        k_inv_upper<<<g, ST_THREADS, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.T, p.uinv, p.uinv_full);
-        k_inv_lower<<<g, ST_THREADS, trsm_smem((int)nb), s>>>(n, (int)nb, blk0, p.Trm, p.linv, p.linv_full);
+        const size_t lds = trsm_smem((int)nb, (int)(g.x * g.y));
+        k_inv_upper<<<g, ST_THREADS, lds, s>>>(n, (int)nb, blk0, p.T, p.uinv, p.uinv_full);
+        k_inv_lower<<<g, ST_THREADS, lds, s>>>(n, (int)nb, blk0, p.Trm, p.linv, p.linv_full);
     }
     double fl = 2.0 / 3.0 * (double)n * nb * nb;
     if (prec_block(nb) == 2 * nb && n > nb) {
@@ -733,17 +749,16 @@ static hipError_t prec_inverses(const FactorPlan& p, float* W, hipStream_t s) {
 hipError_t lookahead_create(Lookahead* la) {
     hipError_t e;
     if ((e = hipStreamCreateWithFlags(&la->side, hipStreamNonBlocking))) return e;
-    if ((e = hipEventCreateWithFlags(&la->ev_upd, hipEventDisableTiming))) return e;
-    if ((e = hipEventCreateWithFlags(&la->ev_cross, hipEventDisableTiming))) return e;
-    if ((e = hipEventCreateWithFlags(&la->ev_next, hipEventDisableTiming))) return e;
-    return hipEventCreateWithFlags(&la->ev_panel, hipEventDisableTiming);
+    if ((e = hipStreamCreateWithFlags(&la->chain, hipStreamNonBlocking))) return e;
+    for (hipEvent_t* ev : {&la->ev_upd, &la->ev_cross, &la->ev_diag, &la->ev_first, &la->ev_panel, &la->ev_side})
+        if ((e = hipEventCreateWithFlags(ev, hipEventDisableTiming))) return e;
+    return hipSuccess;
 }
 
 void lookahead_destroy(Lookahead* la) {
-    if (la->ev_panel) (void)hipEventDestroy(la->ev_panel);
-    if (la->ev_next) (void)hipEventDestroy(la->ev_next);
-    if (la->ev_cross) (void)hipEventDestroy(la->ev_cross);
-    if (la->ev_upd) (void)hipEventDestroy(la->ev_upd);
+    for (hipEvent_t ev : {la->ev_upd, la->ev_cross, la->ev_diag, la->ev_first, la->ev_panel, la->ev_side})
+        if (ev) (void)hipEventDestroy(ev);
+    if (la->chain) (void)hipStreamDestroy(la->chain);
     if (la->side) (void)hipStreamDestroy(la->side);
     *la = Lookahead();
 }
@@ -751,7 +766,7 @@ void lookahead_destroy(Lookahead* la) {
 // Look-ahead contexts of callers that bring none: a pool per device
 // (default stream priority).  A call takes a context for the time it
 // enqueues its work and returns it afterwards; work still in flight on the
-// context's side stream is no hazard for the next user, whose waits and
+// context's own streams is no hazard for the next user, whose waits and
 // records are enqueued after it (a wait on an event refers to the event's
 // latest record at the time of the wait call).  Two calls never enqueue on
 // one context at the same time.
@@ -783,21 +798,17 @@ static void lookahead_release(int dev, Lookahead* L) {
     g_la_free[dev].push_back(L);
 }
 
-// the strip-TRSM descriptor of block step k of a factorisation; wg_begin: the
-// work-groups of the group before it
+// the strip-TRSM descriptor of strips [s0, s0 + count) per side of block step k
+// of a factorisation; wg_begin: the work-groups of the group before it
 template <int ST, int OP>
-static void trsm_desc(const FactorPlan& p, int64_t k, TrsmOne& g, int wg_begin) {
+static void trsm_desc(const FactorPlan& p, int64_t k, int s0, int count, TrsmOne& g, int wg_begin) {
     typedef typename Operand<OP>::T OP_T;
     const int nb = (int)p.nb;
-    const int kb = (int)(p.n - k < nb ? p.n - k : nb);
-    const int64_t m = p.n - k - kb;
     const int64_t blk = k / nb;
     const int set = (int)(blk & 3);
     const int64_t opset = p.op_rows * nb, scset = p.op_rows / 32;
-    const int nstrip = (int)(rup(m, 256) / SR);
-    g.A = p.A; g.lda = p.lda; g.n = p.n; g.k = k; g.nb = nb; g.nstrip = nstrip;
-    g.wg_end = wg_begin + 2 * nstrip;
-    g.pad = 0;
+    g.A = p.A; g.lda = p.lda; g.n = p.n; g.k = k; g.nb = nb; g.s0 = s0; g.nstrip = count;
+    g.wg_end = wg_begin + 2 * count;
     g.Trm = p.Trm + blk * nb * nb;
     g.uinv = p.uinv + blk * nb * 64;
     g.T = p.T + blk * nb * nb;
@@ -824,8 +835,9 @@ static void panel_desc(const FactorPlan& p, int64_t k, int tr, PanelOne& g, cons
     const int64_t D = prec_block(nb), gsz = D / nb, o = (blk % gsz) * nb;
     g.A = p.A; g.lda = p.lda; g.n = p.n; g.k = k; g.ldi = D;
     g.nb = nb; g.kbp = (int)rup(kb, 64);
-    g.ntile = m > 0 ? (int)(rup(m, 256) / tr) : 0;
-    g.pad = g.pad2 = 0;
+    g.tile0 = first_strips(p, k) * SR / tr;
+    g.ntile = m > 0 ? (int)(rup(m, 256) / tr) - g.tile0 : 0;
+    g.pad = 0;
     g.wg_inv = wg0[0] + 2 * (g.kbp / SR);
     g.wg_split = wg0[1] + (m > 0 ? 2 * (nb / 16) : 0);
     g.wg_trsm = wg0[2] + 2 * g.ntile;
@@ -895,18 +907,28 @@ static int cross_calls(const FactorPlan& p, int64_t j, bool pair, int64_t b, Gem
     return c;
 }
 
-// Right-looking blocked LU with look-ahead, the updates taken in pairs (see
-// above).  With the pair (k, k1), k1 = k + nb, and k2, k3 the next two
-// blocks, the caller's stream runs the pair's update in two launches -- the
-// rest of block column and row k2 (the diagonal block k2 is updated on the
-// side stream) with block column and row k3, then everything beyond -- while
-// the side stream runs the chain that sets the pace of the late steps: the
-// diagonal block k2, its LU, the strip TRSMs of step k2 and the update of
-// block column and row k3 by step k2 alone (after the first launch), the LU
-// and TRSMs of block k3.  One event per hand-over; in the late steps each
-// has fired before its wait is reached.  The operand sets of the pair are
-// rewritten by the TRSMs two pairs later, which the side stream enqueues
-// after it has seen the pair's last update end.
+// Right-looking blocked LU with look-ahead on three streams, the updates taken
+// in pairs (see above).
+//   chain: what the next diagonal block waits for, and nothing else: with (a, b)
+//   a pair of blocks, the diagonal block a's update by the pair before, its LU,
+//   the strips of step a in block b, the diagonal block b's update by step a, its
+//   LU, the strips of step b in the block after it.
+//   side: the other strips of step a, the rest of block column and row b by step
+//   a, the other strips of step b.
+//   the caller's stream: the update by the pair before of the rest of block column
+//   and row a and of block column and row b in one launch, then of everything
+//   beyond.
+// With every strip and the whole of block column and row b on the chain (which
+// is still the order where one launch solves a step's strips) the factorisation at
+// n = 12013 nb = 512 BF16 took 6.65 ms where it takes 6.17, the solve at n = 20001
+// with FP8 operands 16.9 against 15.6: there a step's 300 us and more of chain (LU
+// 150, inverses, their parts and products 160, update 20) became 270 (LU 175 beside
+// the products, strips 60 to 85, update 17).
+// One event per hand-over, waited for before its next record is enqueued.  The
+// operand sets of a pair are rewritten by the strips two pairs later, which
+// both streams enqueue after they have seen the pair's last update end.  The
+// diagonal blocks' updates read whole tiles of operand rows: those past the block
+// may be strips just being written, whose products are not stored.
 template <int ST, int OP>
 static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la) {
     typedef typename Store<ST>::T ST_T;
@@ -941,44 +963,38 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
                                 p.dsync + blk * diag_sync_words(nb), p.info, st);
         if (e2) return e2;
         prof::end(pt, prof::DIAG, st, 2.0 / 3.0 * kb * (double)kb * kb, 2.0 * kb * (double)kb * sizeof(ST_T));
-        if ((e2 = hipGetLastError())) return e2;
-        if (NP && inverse_path(p, k)) {
-            // the block's inverses and their 16-bit parts (the strip products' B operands)
-            PanelGroup pg;
-            const int wg0[3] = {0, 0, 0};
-            panel_desc(p, k, panel_rows(ST, nb), pg.g[0], wg0);
-            pg.count = 1;
-            hipEvent_t pi = prof::begin(prof::TRSM, st);
-            if ((e2 = block_inverses(pg, pg.g[0].wg_inv, nb, st))) return e2;
-            if (pg.g[0].wg_split > 0 && (e2 = panel_split(ST, pg, pg.g[0].wg_split, nb, st))) return e2;
-            prof::end(pi, prof::TRSM, st, 4.0 / 3.0 * kb * (double)kb * kb, 8.0 * kb * (double)kb);
-        }
-        return hipSuccess;
-    };
-    // strip TRSMs of block k (wide grids: all CUs)
-    auto trsm = [&](int64_t k, hipStream_t st) -> hipError_t {
-        const int kb = (int)(n - k < nb ? n - k : nb);
-        const int64_t m = n - k - kb;
-        if (m <= 0) return hipSuccess;
-        if (NP && inverse_path(p, k)) {
-            PanelGroup pg;
-            const int wg0[3] = {0, 0, 0};
-            panel_desc(p, k, panel_rows(ST, nb), pg.g[0], wg0);
-            pg.count = 1;
-            hipEvent_t pt = prof::begin(prof::TRSM, st);
-            hipError_t e2 = panel_trsm(ST, OP, pg, pg.g[0].wg_trsm, nb, st);
-            prof::end(pt, prof::TRSM, st, 4.0 * m * (double)nb * nb,
-                      4.0 * m * (double)nb * sizeof(ST_T) + 2.0 * m * (double)nb * sizeof(OP_T));
-            return e2;
-        }
-        TrsmGroup grp;
-        trsm_desc<ST, OP>(p, k, grp.g[0], 0);
-        grp.count = 1;
-        hipEvent_t pt = prof::begin(prof::TRSM, st);
-        k_trsm<ST, OP><<<grp.g[0].wg_end, ST_THREADS, trsm_smem(nb), st>>>(grp);
-        prof::end(pt, prof::TRSM, st, 2.0 * m * (double)nb * nb,
-                  4.0 * m * (double)nb * sizeof(ST_T) + 2.0 * m * (double)nb * sizeof(OP_T));
         return hipGetLastError();
+    };
+    // strips [s0, s0 + count) of each side of block step k by substitution
+    auto strips = [&](int64_t k, int s0, int count, hipStream_t st) -> hipError_t {
+        if (count <= 0) return hipSuccess;
+        TrsmGroup grp;
+        trsm_desc<ST, OP>(p, k, s0, count, grp.g[0], 0);
+        grp.count = 1;
+        const double m = (double)count * SR;
+        hipEvent_t pt = prof::begin(prof::TRSM, st);
+        k_trsm<ST, OP><<<grp.g[0].wg_end, ST_THREADS, trsm_smem(nb, grp.g[0].wg_end), st>>>(grp);
+        prof::end(pt, prof::TRSM, st, 2.0 * m * nb * nb, 4.0 * m * nb * sizeof(ST_T) + 2.0 * m * nb * sizeof(OP_T));
+        return hipGetLastError();
+    };
+    // the strips beyond the first (wide grids: all CUs)
+    auto other_strips = [&](int64_t k, hipStream_t st) -> hipError_t {
+        const int s0 = first_strips(p, k);
+        if (!(NP && inverse_path(p, k))) return strips(k, s0, strip_count(p, k) - s0, st);
+        // the block's inverses, their 16-bit parts (the strip products' B
+        // operands) and the products
+        PanelGroup pg;
+        const int wg0[3] = {0, 0, 0};
+        panel_desc(p, k, panel_rows(ST, nb), pg.g[0], wg0);
+        pg.count = 1;
+        const double m = (double)(n - k - nb);
+        hipEvent_t pt = prof::begin(prof::TRSM, st);
+        hipError_t e2 = block_inverses(pg, pg.g[0].wg_inv, nb, st);
+        if (!e2) e2 = panel_split(ST, pg, pg.g[0].wg_split, nb, st);
+        if (!e2) e2 = panel_trsm(ST, OP, pg, pg.g[0].wg_trsm, nb, st);
+        prof::end(pt, prof::TRSM, st, 4.0 * m * nb * nb + 4.0 / 3.0 * nb * (double)nb * nb,
+                  4.0 * m * nb * sizeof(ST_T) + 2.0 * m * nb * sizeof(OP_T) + 8.0 * nb * (double)nb);
+        return e2;
     };
     // one trailing-update launch of up to two descriptors, timed on its own
     auto gemm = [&](const GemmCall* c, int cnt, hipStream_t st) -> hipError_t {
@@ -1001,15 +1017,10 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         prof::end(pt, prof::GEMM, st, fl, by);
         return e2;
     };
-    // block column and row b by step j (pair: by steps j and j + nb)
-    auto cross = [&](int64_t j, bool pair, int64_t b, hipStream_t st) -> hipError_t {
-        GemmCall c[2];
-        const int cnt = cross_calls<ST, OP>(p, j, pair, b, c);
-        return gemm(c, cnt, st);
-    };
-    // the square [b, n) x [b, n) by the pair (j, j + nb)
-    auto square = [&](int64_t j, int64_t b, int64_t w, hipStream_t st) -> hipError_t {
-        GemmCall c = pair_call<ST, OP>(p, j, true, b, b, w, w);
+    // the diagonal block b by step j (pair: by steps j and j + nb)
+    auto diag_update = [&](int64_t j, bool pair, int64_t b, hipStream_t st) -> hipError_t {
+        const int64_t w = n - b < nb ? n - b : nb;
+        GemmCall c = pair_call<ST, OP>(p, j, pair, b, b, w, w);
         return gemm(&c, 1, st);
     };
 
@@ -1018,60 +1029,96 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         const int64_t words = ((n + nb - 1) / nb) * (int64_t)diag_sync_words(nb);
         if ((e = fill_u64(p.dsync, (words + 1) / 2, 0ull, s))) return e;
     }
-    // panels 0 and 1 (block column and row 1 updated by step 0 alone)
-    if ((e = diag(0, s))) return e;
-    if ((e = trsm(0, s))) return e;
-    if (nb < n) {
-        if ((e = cross(0, false, nb, s))) return e;
-        if ((e = diag(nb, s))) return e;
-        if ((e = trsm(nb, s))) return e;
+    if (n <= nb) {
+        if ((e = diag(0, s))) return e;
+        return prec_inverses<ST>(p, p.pairw, s);
     }
-    if ((e = hipEventRecord(LA->ev_upd, s))) return e;
+    // the first pair of a matrix whose strips are solved in one launch has nothing
+    // to overlap with: it stays on the caller's stream
+    const hipStream_t side = LA->side;
+    const bool lone = first_strips(p, 0) == strip_count(p, 0);
+    hipStream_t chain = lone ? s : LA->chain;
     bool side_used = false;
-    for (int64_t k = 0; k + 2 * nb < n; k += 2 * nb) {
-        // panels k and k1 = k + nb are formed; the pair (k, k1) updates [k2, n)
-        const int64_t k2 = k + 2 * nb, k3 = k2 + nb;
-        const int64_t w2 = n - k2 < nb ? n - k2 : nb;
-        // side: diagonal block k2 (needs the previous pair's last update), its LU
-        if ((e = hipStreamWaitEvent(LA->side, LA->ev_upd, 0))) return e;
-        if ((e = square(k, k2, w2, LA->side))) return e;
-        if ((e = diag(k2, LA->side))) return e;
-        // main: the rest of block column and row k2 (needs panel k1) and
-        // block column and row k3, in one launch (the side stream's diagonal
-        // LU of k2 outlasts both), then everything beyond
-        if (side_used && (e = hipStreamWaitEvent(s, LA->ev_panel, 0))) return e;
-        {
+    // the strips of step j: the first (or all); the others behind them, through
+    // the inverses, which start with a launch of few work-groups, beside them
+    auto panel = [&](int64_t j) -> hipError_t {
+        const int first = first_strips(p, j);
+        if (first == strip_count(p, j)) return strips(j, 0, first, chain);
+        const bool inv = NP && inverse_path(p, j);
+        side_used = true;
+        hipError_t e2;
+        if (inv) {
+            if ((e2 = hipEventRecord(LA->ev_diag, chain))) return e2;
+            if ((e2 = hipStreamWaitEvent(side, LA->ev_diag, 0))) return e2;
+        }
+        if ((e2 = strips(j, 0, first, chain))) return e2;
+        if ((e2 = hipEventRecord(LA->ev_first, chain))) return e2;
+        if (!inv && (e2 = hipStreamWaitEvent(side, LA->ev_first, 0))) return e2;
+        if ((e2 = other_strips(j, side))) return e2;
+        return inv ? hipStreamWaitEvent(side, LA->ev_first, 0) : hipSuccess;
+    };
+    for (int64_t a = 0; a < n; a += 2 * nb) {
+        const int64_t b = a + nb, k = a - 2 * nb;        // (k, k + nb): the pair before
+        const int64_t wa = n - a < nb ? n - a : nb;
+        if (a == 0 || (a == 2 * nb && lone)) {
+            if ((e = hipEventRecord(LA->ev_upd, s))) return e;
+            if (a > 0) chain = LA->chain;
+        }
+        // chain: diagonal block a (the pair before's predecessor has updated it)
+        if (chain != s && (e = hipStreamWaitEvent(chain, LA->ev_upd, 0))) return e;
+        if (a > 0 && (e = diag_update(k, true, a, chain))) return e;
+        if ((e = diag(a, chain))) return e;
+        if (b >= n) break;
+        if (a > 0) {
+            // the caller's stream: the pair before's panels are formed
+            if ((k > 0 || !lone) && (e = hipStreamWaitEvent(s, LA->ev_panel, 0))) return e;
+            if (side_used && (e = hipStreamWaitEvent(s, LA->ev_side, 0))) return e;
             GemmCall c[4];
             int cnt = 0;
-            if (n - k2 - w2 > 0) {
-                c[cnt++] = pair_call<ST, OP>(p, k, true, k2 + w2, k2, n - k2 - w2, w2);
-                c[cnt++] = pair_call<ST, OP>(p, k, true, k2, k2 + w2, w2, n - k2 - w2);
-            }
-            if (k3 < n) cnt += cross_calls<ST, OP>(p, k, true, k3, c + cnt);
-            if (cnt && (e = gemm(c, cnt, s))) return e;
-        }
-        if ((e = hipEventRecord(LA->ev_cross, s))) return e;
-        if (k3 < n) {
-            const int64_t w3 = n - k3 < nb ? n - k3 : nb;
-            if ((e = hipEventRecord(LA->ev_next, s))) return e;
-            if (n - k3 - w3 > 0) {
-                GemmCall c = pair_call<ST, OP>(p, k, true, k3 + w3, k3 + w3, n - k3 - w3, n - k3 - w3);
-                if ((e = gemm(&c, 1, s))) return e;
+            c[cnt++] = pair_call<ST, OP>(p, k, true, b, a, n - b, wa);
+            c[cnt++] = pair_call<ST, OP>(p, k, true, a, b, wa, n - b);
+            cnt += cross_calls<ST, OP>(p, k, true, b, c + cnt);
+            if ((e = gemm(c, cnt, s))) return e;
+            if ((e = hipEventRecord(LA->ev_cross, s))) return e;
+            if (n - b > nb) {
+                GemmCall d = pair_call<ST, OP>(p, k, true, b + nb, b + nb, n - b - nb, n - b - nb);
+                if ((e = gemm(&d, 1, s))) return e;
             }
             if ((e = hipEventRecord(LA->ev_upd, s))) return e;
-            // side: panel k2, block column and row k3 by step k2, panel k3
-            if ((e = hipStreamWaitEvent(LA->side, LA->ev_cross, 0))) return e;
-            if ((e = trsm(k2, LA->side))) return e;
-            if ((e = hipStreamWaitEvent(LA->side, LA->ev_next, 0))) return e;
-            if ((e = cross(k2, false, k3, LA->side))) return e;
-            if ((e = diag(k3, LA->side))) return e;
-            if ((e = trsm(k3, LA->side))) return e;
+            if ((e = hipStreamWaitEvent(chain, LA->ev_cross, 0))) return e;
         }
-        if ((e = hipEventRecord(LA->ev_panel, LA->side))) return e;
-        side_used = true;
+        const int64_t wb = n - b < nb ? n - b : nb, c0 = b + wb;
+        const bool whole = first_strips(p, a) == strip_count(p, a);
+        if ((e = panel(a))) return e;
+        GemmCall c[2];
+        if (whole) {
+            // block column and row b by step a
+            const int cnt = cross_calls<ST, OP>(p, a, false, b, c);
+            if ((e = gemm(c, cnt, chain))) return e;
+        } else if ((e = diag_update(a, false, b, chain))) {
+            return e;
+        }
+        if ((e = diag(b, chain))) return e;
+        if (c0 < n) {
+            if (!whole) {
+                // side: the rest of block column and row b by step a
+                c[0] = pair_call<ST, OP>(p, a, false, c0, b, n - c0, wb);
+                c[1] = pair_call<ST, OP>(p, a, false, b, c0, wb, n - c0);
+                if ((e = gemm(c, 2, side))) return e;
+                if ((e = hipEventRecord(LA->ev_side, side))) return e;
+                if ((e = hipStreamWaitEvent(chain, LA->ev_side, 0))) return e;
+            }
+            if ((e = panel(b))) return e;
+        }
+        if (chain != s && (e = hipEventRecord(LA->ev_panel, chain))) return e;
+        if (side_used && (e = hipEventRecord(LA->ev_side, side))) return e;
     }
-    // the caller's stream ends after every side-stream kernel
-    if (side_used && (e = hipStreamWaitEvent(s, LA->ev_panel, 0))) return e;
+    // the caller's stream ends after every kernel of the other two
+    if (chain != s) {
+        if ((e = hipEventRecord(LA->ev_panel, chain))) return e;
+        if ((e = hipStreamWaitEvent(s, LA->ev_panel, 0))) return e;
+    }
+    if (side_used && (e = hipStreamWaitEvent(s, LA->ev_side, 0))) return e;
     // full FP32 inverses of the preconditioner's diagonal blocks
     return prec_inverses<ST>(p, p.pairw, s);
 }
@@ -1128,13 +1175,13 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
             dc[nd++] = DiagCall{p.A, p.lda, k, kb, (int)rup(kb, 64), nb, p.T + blk * nb * nb, p.Trm + blk * nb * nb,
                                 p.linv + blk * nb * 64, p.uinv + blk * nb * 64, p.dsync + blk * diag_sync_words(nb),
                                 p.info};
-            if (NP && inverse_path(p, k)) {
+            const bool inv = NP && inverse_path(p, k);
+            if (inv) {
                 pg.g[np++].nb = nb;                       // descriptors filled below (tile rows need nbmax)
                 pnbmax = nb > pnbmax ? nb : pnbmax;
-                continue;
             }
             if (m <= 0) continue;
-            trsm_desc<ST, OP>(p, k, tg.g[nt], wg);
+            trsm_desc<ST, OP>(p, k, 0, inv ? first_strips(p, k) : strip_count(p, k), tg.g[nt], wg);
             wg = tg.g[nt++].wg_end;
             nbmax = nb > nbmax ? nb : nbmax;
         }
@@ -1162,7 +1209,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
         if (!nt) return hipSuccess;
         tg.count = nt;
         hipEvent_t pt = prof::begin(prof::TRSM, s);
-        k_trsm<ST, OP><<<wg, ST_THREADS, trsm_smem(nbmax), s>>>(tg);
+        k_trsm<ST, OP><<<wg, ST_THREADS, trsm_smem(nbmax, wg), s>>>(tg);
         prof::end(pt, prof::TRSM, s, 0.0, 0.0);
         return hipGetLastError();
     };

@@ -155,7 +155,7 @@ hipError_t panel_split(int store, const PanelGroup& grp, int wg, int nbmax, hipS
 }
 
 // ------------------------------------------------------------------ strip products
-// One work-group: TR = 32 RB rows of L21 (work-groups [0, ntile)) or TR
+// One work-group: TR = 32 RB rows of L21 (the first ntile work-groups) or TR
 // columns of U12 (the rest), all nb output columns.  The panel tile goes to
 // LDS once: the rows of A21 as stored (column-major: K runs over the LDS
 // rows, [kk][row]), the columns of A12 with K contiguous ([row][kk]).  The
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_trsm_inv(const PanelGroup g
     const PanelOne& G = grp.g[d];
     const int w0 = (int)blockIdx.x - (d > 0 ? grp.g[d - 1].wg_trsm : 0);
     const bool lside = w0 < G.ntile;                      // work-group uniform
-    const int tile = lside ? w0 : w0 - G.ntile;
+    const int tile = G.tile0 + (lside ? w0 : w0 - G.ntile);
     const int nb = G.nb, PU = nb + 8;
     const int64_t n = G.n, k = G.k, lda = G.lda;
     STT* A = (STT*)G.A;

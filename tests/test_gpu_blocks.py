@@ -13,6 +13,7 @@ import torch
 
 import paper_2509_19618_amd as mxp
 from test_gpu_factor import _dense_prec
+from test_gpu_factor import test_factor_backward_and_forward_error as _factor_error
 
 pytestmark = pytest.mark.gpu
 EPS = 2.0 ** -53
@@ -153,3 +154,18 @@ def test_many_right_hand_sides(n):
     for r in (0, 15, 16, 19):
         one = mxp.mxp_solve_ir(prob, fac, B=prob.B[r:r + 1].contiguous())
         assert float((res.X[r] - one.X[0]).abs().max()) <= 1e-12 * float(one.X[0].abs().max())
+
+
+# more strips than CUs (a trailing part of more than 4096): the first strips of a
+# step on their own, the others by substitution (FP32 storage, few blocks) or
+# through the block inverses, against the definition; then in a group bit for bit
+@pytest.mark.parametrize("n,nb,update,store", [(4300, 64, "bf16", "bf16"), (4500, 128, "f8", "f16"),
+                                               (4900, 512, "f32", "f32"), (4400, 256, "f16", "f16")])
+def test_factor_of_more_strips_than_cus(n, nb, update, store):
+    _factor_error(n, nb, update, store)
+    probs = [mxp.mxp_generate(n - 100 * i, 1, 6 + i, store=store) for i in range(2)]
+    facs = mxp.mxp_factor_group(probs, [nb, nb], update)
+    for i, fac in enumerate(facs):
+        one = mxp.mxp_factor(mxp.mxp_generate(n - 100 * i, 1, 6 + i, store=store), nb, update)
+        m = n - 100 * i                              # (the columns' padding is nobody's)
+        assert fac.info == 0 and torch.equal(fac.LU[:, :m], one.LU[:, :m])
