@@ -594,16 +594,60 @@ __global__ __launch_bounds__(256) void k_panel64_pp(double* A, int64_t lda, int6
 // barrier instead of a round over the whole device: every wave proposes its
 // largest magnitude with that row's W values in LDS, and after the barrier
 // every thread has the winner, its row and the row it trades places with.
-// Measured: about 0.6 us per column, against 12 us with a device-wide barrier
-// (5 us with the cheaper one above).  The swaps and the update of the panel's
+// Measured (n = 3000, rocprofv3): 29.5 us per 16 columns and 18.4 per 8, 1.9 to
+// 2.3 us per column (48 and 26 us with the reductions through LDS and a division
+// per row), against 12 us per column with a device-wide barrier (5 us with the
+// cheaper one above).  Eight waves with twice the rows each, or the columns in a
+// loop that moves them through the same registers, were not faster (20.4 and 42 us
+// per 8 columns).  The swaps and the update of the panel's
 // other columns follow per W columns (k_panel64_rest).
 constexpr int PW_T = 1024;
 
-// the larger value over the wave (all lanes get it)
+// the largest of v (no NaN) over the 16 lanes of a row / over the wave, in all of
+// its lanes: exchanges by DPP and lane swaps (through LDS, as __shfl does it, the
+// reductions were two thirds of a column's time)
+MXP_DEV double max64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+template <int CTRL> MXP_DEV double dpp_max64(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+    return max64(v, __hiloint2double(hi, lo));
+}
+MXP_DEV double row_max64(double v) {
+    v = dpp_max64<0xB1>(v);                                // quad_perm [1,0,3,2]
+    v = dpp_max64<0x4E>(v);                                // quad_perm [2,3,0,1]
+    v = dpp_max64<0x141>(v);                               // row_half_mirror
+    return dpp_max64<0x140>(v);                            // row_mirror
+}
 MXP_DEV double wave_max64(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    v = row_max64(v);
+    {
+        const auto a = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        v = max64(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
+    }
+    const auto a = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+    return max64(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
+}
+// the smallest row over the lanes of mask (a wave-uniform result; one lane as a rule)
+MXP_DEV int least_row(unsigned long long mask, int row) {
+    int r = __builtin_amdgcn_readlane(row, __builtin_ctzll(mask));
+    for (mask &= mask - 1; mask; mask &= mask - 1) {
+        const int t = __builtin_amdgcn_readlane(row, __builtin_ctzll(mask));
+        r = t < r ? t : r;
+    }
+    return r;
+}
+// 1 / x to within an ulp or so, finite and normal where it is used; the quotients
+// taken with it are corrected by their residual
+MXP_DEV double recip64(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
 }
 
 template <int J, int W, int R>
@@ -622,10 +666,7 @@ MXP_DEV void panel_step(double (&x)[R][W], int64_t k0, int m, int tid, int lane,
             if (r >= J && r < m && a > v) { v = a; row = r; }
         }
         const double wm = wave_max64(v);
-        int cr = v == wm ? row : 0x7FFFFFFF;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(cr, o, 64); cr = t < cr ? t : cr; }
-        cr = __builtin_amdgcn_readfirstlane(cr);
+        const int cr = wm < 0.0 ? 0x7FFFFFFF : least_row(__ballot(v == wm), row);
         if (cr != 0x7FFFFFFF) {
             const int ci = cr / PW_T;
 #pragma unroll
@@ -641,14 +682,8 @@ MXP_DEV void panel_step(double (&x)[R][W], int64_t k0, int m, int tid, int lane,
         __syncthreads();
         // the winner, the same in every thread
         const double cv = swave[par][lane & 15];
-        int wr = srow[par][lane & 15];
-        double bm = cv;
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) bm = fmax(bm, __shfl_xor(bm, o, 64));
-        wr = cv == bm ? wr : 0x7FFFFFFF;
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) { const int t = __shfl_xor(wr, o, 64); wr = t < wr ? t : wr; }
-        const int p = __builtin_amdgcn_readfirstlane(wr);
+        const int wr = srow[par][lane & 15];
+        const int p = least_row(__ballot(cv == row_max64(cv)) & 0xFFFFull, wr);
         const int pw = (p % PW_T) / 64;
         double pr[W];
 #pragma unroll
@@ -669,22 +704,38 @@ MXP_DEV void panel_step(double (&x)[R][W], int64_t k0, int m, int tid, int lane,
                 for (int c = 0; c < W; ++c) x[0][c] = pr[c];
         }
         const double piv = pr[J];
-        const bool ok = piv != 0.0 && isfinite(piv);
-        if (!ok && bad < 0) bad = J;
-        if (ok) {
+        if (__builtin_amdgcn_readfirstlane(piv != 0.0 && isfinite(piv))) {
             // the quotient as a product with the reciprocal and one residual
-            // correction (a true quotient where the reciprocal overflows)
-            const double rp = 1.0 / piv;
-            const bool fast = isfinite(rp);
+            // correction (a true quotient where the reciprocal leaves the range)
+            double l[R];
+            const double rp = recip64(piv);
+            if (__builtin_amdgcn_readfirstlane(fabs(rp) >= 0x1p-1000 && fabs(rp) <= 0x1p1000)) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    l[i] = x[i][J] * rp;
+                    l[i] = fma(fma(-piv, l[i], x[i][J]), rp, l[i]);
+                }
+            } else {
+#pragma unroll 1
+                for (int i = 0; i < R; ++i) {
+                    double a = x[0][J];
+#pragma unroll
+                    for (int k = 1; k < R; ++k) a = k == i ? x[k][J] : a;
+                    a = a / piv;
+#pragma unroll
+                    for (int k = 0; k < R; ++k) l[k] = k == i ? a : l[k];
+                }
+            }
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                double l = x[i][J] * rp;
-                l = fast ? fma(fma(-piv, l, x[i][J]), rp, l) : x[i][J] / piv;
-                l = (i > 0 || tid > J) ? l : 0.0;
-                if (i > 0 || tid > J) x[i][J] = l;
+                const bool below = i > 0 || tid > J;
+                x[i][J] = below ? l[i] : x[i][J];
+                l[i] = below ? l[i] : 0.0;
 #pragma unroll
-                for (int c = J + 1; c < W; ++c) x[i][c] = fma(-l, pr[c], x[i][c]);
+                for (int c = J + 1; c < W; ++c) x[i][c] = fma(-l[i], pr[c], x[i][c]);
             }
+        } else if (bad < 0) {
+            bad = J;
         }
         panel_step<J + 1, W, R>(x, k0, m, tid, lane, wave, ipiv, swave, srow, sval, stop, bad);
     }
