@@ -960,32 +960,65 @@ __global__ __launch_bounds__(256) void k_laswp64(double* A, int64_t lda, int64_t
 // chain bound it (about 7 us per block); blocks of 64 with the triangle solved
 // by one lane per right-hand side from memory took 80 us per block.
 
-// the n swaps in order, one work-group per right-hand side: x in LDS when it
-// fits (lds_n = n), the swap rows read ahead 64 at a time
-__global__ __launch_bounds__(256) void k_apply_pivots(double* x, int64_t ldx, const int64_t* __restrict__ ipiv,
-                                                      int64_t n, int lds_n) {
+// The n swaps in order, one work-group per right-hand side: x in LDS when it fits
+// (lds_n = n).  Sixteen waves form the net exchange of 64 swaps each -- at most 128
+// slots: slot j < 64 is row k0 + j, slot 64 + j row ipiv[k0 + j] where that lies
+// outside and no earlier swap names it -- then one wave moves the values, 64 swaps
+// at a time.  (Swap after swap on the values, each a round trip to LDS: 316 us at
+// n = 3000 against 46.)
+constexpr int AP_T = 1024, AP_W = AP_T / 64;
+__global__ __launch_bounds__(AP_T) void k_apply_pivots(double* x, int64_t ldx, const int64_t* __restrict__ ipiv,
+                                                       int64_t n, int lds_n) {
     extern __shared__ __attribute__((aligned(16))) double gsm[];
+    __shared__ int row[AP_W][128];
+    __shared__ int src[AP_W][128];
     double* g = x + (int64_t)blockIdx.x * ldx;
-    const int tid = threadIdx.x;
-    for (int i = tid; i < lds_n; i += 256) gsm[i] = g[i];
-    __syncthreads();
-    if (tid < 64) {
-        for (int64_t k0 = 0; k0 < n; k0 += 64) {
-            const int m = (int)(n - k0 < 64 ? n - k0 : 64);
-            const int pv = tid < m ? (int)ipiv[k0 + tid] : 0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < lds_n; i += AP_T) gsm[i] = g[i];
+    double* const v = lds_n ? gsm : g;
+    for (int64_t r0 = 0; r0 < n; r0 += 64 * AP_W) {
+        const int64_t k0 = r0 + 64 * wave;
+        const int m = (int)(n - k0 < 64 ? n - k0 : 64);
+        if (m > 0) {
+            const int p = lane < m ? (int)ipiv[k0 + lane] : (int)k0 + lane;
+            int slot = p - (int)k0;
+            if (slot >= 64) {
+                slot = 64 + lane;
+            }
+#pragma unroll 8
+            for (int j = 62; j >= 0; --j)                 // the first swap that names the row
+                if (slot >= 64 && j < lane && __builtin_amdgcn_readlane(p, j) == p) slot = 64 + j;
+            row[wave][lane] = lane < m ? (int)k0 + lane : -1;
+            row[wave][64 + lane] = lane < m && slot == 64 + lane ? p : -1;
+            src[wave][lane] = lane;
+            src[wave][64 + lane] = 64 + lane;
+            __builtin_amdgcn_wave_barrier();
             for (int j = 0; j < m; ++j) {
-                const int64_t k = k0 + j, p = __builtin_amdgcn_readlane(pv, j);
-                if (p != k && tid == 0) {
-                    double* v = lds_n ? gsm : g;
-                    const double a = v[k];
-                    v[k] = v[p];
-                    v[p] = a;
+                const int s = __builtin_amdgcn_readlane(slot, j);
+                if (lane == 0) {
+                    const int a = src[wave][j], b = src[wave][s];
+                    src[wave][j] = b;
+                    src[wave][s] = a;
                 }
             }
         }
+        __syncthreads();
+        if (wave == 0) {
+            for (int c = 0; c < AP_W && r0 + 64 * c < n; ++c) {
+                const int ra = row[c][lane], rb = row[c][64 + lane];
+                const double a = ra >= 0 ? v[row[c][src[c][lane]]] : 0.0;
+                const double b = rb >= 0 ? v[row[c][src[c][64 + lane]]] : 0.0;
+                __threadfence_block();
+                __builtin_amdgcn_wave_barrier();
+                if (ra >= 0) v[ra] = a;
+                if (rb >= 0) v[rb] = b;
+                __threadfence_block();
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int i = tid; i < lds_n; i += 256) g[i] = gsm[i];
+    for (int i = tid; i < lds_n; i += AP_T) g[i] = gsm[i];
 }
 
 constexpr int SVB = 128;     // rows of a block step
@@ -1278,12 +1311,12 @@ hipError_t lu64_solve(int64_t n, const double* A, int64_t lda, const int64_t* ip
                       hipStream_t s) {
     hipError_t e;
     if (ipiv) {
-        constexpr int LDS_N = 20000;                  // 160 KB of LDS
+        constexpr int LDS_N = 18000;                  // of 160 KB of LDS, 16 for the exchanges
         static const hipError_t attr = hipFuncSetAttribute((const void*)k_apply_pivots,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS_N * 8);
         if (attr) return attr;
         const int lds_n = n <= LDS_N ? (int)n : 0;
-        k_apply_pivots<<<nr, 256, (size_t)lds_n * 8, s>>>(X, ldx, ipiv, n, lds_n);
+        k_apply_pivots<<<nr, AP_T, (size_t)lds_n * 8, s>>>(X, ldx, ipiv, n, lds_n);
         if ((e = hipGetLastError())) return e;
     }
     for (int r = 0; r < nr;) {

@@ -169,3 +169,20 @@ def test_factor_of_more_strips_than_cus(n, nb, update, store):
         one = mxp.mxp_factor(mxp.mxp_generate(n - 100 * i, 1, 6 + i, store=store), nb, update)
         m = n - 100 * i                              # (the columns' padding is nobody's)
         assert fac.info == 0 and torch.equal(fac.LU[:, :m], one.LU[:, :m])
+
+
+# the swaps alone (identity factor), in order: chunks of 64 whole and ragged, rows
+# named by several swaps, and a vector past what LDS holds
+@pytest.mark.parametrize("n", [1, 64, 65, 1087, 2500, 18400])
+def test_lu64_solve_applies_the_swaps_in_order(n):
+    print("swaps", n, flush=True)
+    gen = torch.Generator().manual_seed(n)
+    k = torch.arange(n)
+    piv = k + (torch.rand(n, generator=gen) * torch.minimum(n - k, torch.tensor(n if n % 2 else 70))).long()
+    want = torch.arange(2.0 * n, dtype=torch.float64).reshape(2, n)
+    B = want.clone().cuda()
+    order = list(range(n))
+    for i, p in enumerate(piv.tolist()):
+        order[i], order[p] = order[p], order[i]
+    fac = mxp.Factor64(n, torch.eye(n, dtype=torch.float64, device="cuda"), n, piv.cuda(), 0, 0)
+    assert torch.equal(mxp.mxp_lu64_solve(fac, B).cpu(), want[:, order])
