@@ -66,12 +66,16 @@ MXP_DEV int g64_boff(int k, int col) { return col * G64_K + (((k >> 1) ^ g64_key
 
 __global__ __launch_bounds__(256, 2) void k_gemm64(double* __restrict__ C, int64_t ldc, const double* __restrict__ A,
                                                    int64_t lda, const double* __restrict__ B, int64_t ldb, int64_t M,
-                                                   int64_t N, int K, int aligned) {
+                                                   int64_t N, int K, int aligned, int tm, int ne) {
     extern __shared__ __attribute__((aligned(16))) double gsm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 15, lk = lane >> 4;
-    const int64_t row0 = (int64_t)blockIdx.x * G64_T, col0 = (int64_t)blockIdx.y * G64_T;
+    // tiles: the first ne tile columns whole (tm tile rows each), the first ne tile
+    // rows of the columns after them
+    const int t = (int)blockIdx.x, u = t - tm * ne;
+    const int64_t row0 = (int64_t)(u < 0 ? t % tm : u % ne) * G64_T;
+    const int64_t col0 = (int64_t)(u < 0 ? t / tm : ne + u / ne) * G64_T;
     const bool inside = aligned && row0 + G64_T <= M && col0 + G64_T <= N;
     auto stage = [&](int k0, int buf) {
         double* sA = gsm + buf * (G64_SA + G64_SB);
@@ -154,20 +158,33 @@ __global__ __launch_bounds__(256, 2) void k_gemm64(double* __restrict__ C, int64
         }
 }
 
-hipError_t gemm64(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M,
-                  int64_t N, int K, hipStream_t s) {
+// edge < 0: all of C; otherwise its first edge columns and the rest of its first
+// edge rows (edge a multiple of the tile)
+static hipError_t gemm64_part(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb,
+                              int64_t M, int64_t N, int K, int64_t edge, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-    if (K % 4) return hipErrorInvalidValue;
-    dim3 g((unsigned)((M + G64_T - 1) / G64_T), (unsigned)((N + G64_T - 1) / G64_T));
+    if (K % 4 || edge % G64_T > 0) return hipErrorInvalidValue;
+    const int64_t tm = (M + G64_T - 1) / G64_T, tn = (N + G64_T - 1) / G64_T;
+    const int64_t ne = edge < 0 || edge / G64_T > tn ? tn : edge / G64_T;
+    const int64_t nr = ne < tm ? ne : tm;
+    if (ne == 0) return hipSuccess;
+    if (ne < tn && nr < ne) return hipErrorInvalidValue;
     static const hipError_t attr =
         hipFuncSetAttribute((const void*)k_gemm64, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G64_LDS);
     if (attr) return attr;
     hipEvent_t pt = prof::begin(prof::GEMM64, s);
     // 16-byte copies need even leading dimensions and 16-byte aligned operands
     const int aligned = lda % 2 == 0 && ldb % 2 == 0 && ((uintptr_t)A | (uintptr_t)B) % 16 == 0;
-    k_gemm64<<<g, 256, G64_LDS, s>>>(C, ldc, A, lda, B, ldb, M, N, K, aligned);
-    prof::end(pt, prof::GEMM64, s, 2.0 * M * (double)N * K, 16.0 * M * (double)N + 8.0 * (M + N) * K);
+    k_gemm64<<<(unsigned)(tm * ne + nr * (tn - ne)), 256, G64_LDS, s>>>(C, ldc, A, lda, B, ldb, M, N, K, aligned,
+                                                                        (int)tm, (int)ne);
+    const double mn = ne == tn ? M * (double)N : (double)edge * (M + N - edge);
+    prof::end(pt, prof::GEMM64, s, 2.0 * mn * K, 16.0 * mn + 8.0 * (M + N) * K);
     return hipGetLastError();
+}
+
+hipError_t gemm64(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M,
+                  int64_t N, int K, hipStream_t s) {
+    return gemm64_part(C, ldc, A, lda, B, ldb, M, N, K, -1, s);
 }
 
 // The same update by rocBLAS's dgemm (a plain library GEMM), for the FP64
@@ -1242,7 +1259,21 @@ hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* w
     hipError_t e;
     if ((e = fill_u64(info_dev, 1, ~0ull, s))) return e;
     if ((e = fill_u64(bar, 2, 0ull, s))) return e;   // bar[0..1] and err
+    // Without pivoting, while at least GROUP_MIN columns are left, blocks are taken
+    // four at a time: inside such a group an update covers what the group still
+    // factors, its columns and its rows, and the rest follows once per group with
+    // K = 512 (one pass over C instead of four: the update alone runs at 42 TFLOP/s
+    // with K = 128, 52 with 256).  Factorisation 13.63 -> 12.09 ms at n = 8192, 9.88
+    // -> 9.20 at 6500, 5.66 -> 5.56 at 5000; with groups down to 2048 columns 3.02 ->
+    // 3.06 at n = 3000, down to 6144 only 12.39 at 8192.  (Pivoting brings rows of
+    // the rest, which lag, into the group.)
+    constexpr int64_t GROUP_MIN = 4096;
+    int64_t g0 = 0, ge = 0;                              // the group's columns [g0, ge)
     for (int64_t k = 0; k < n; k += nb) {
+        if (k == ge) {
+            g0 = k;
+            ge = k + (nb == G64_T && !ipiv && n - k >= GROUP_MIN ? 4 * nb : nb);
+        }
         const int kb = (int)(n - k < nb ? n - k : nb);
         const int64_t m = n - k;
         if (ipiv) {
@@ -1275,10 +1306,16 @@ hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* w
             if (kb == 128) k_trsm64<8><<<wg + wgr, 256, 0, s>>>(A, lda, n, k, wgr, PL, PU);
             else k_trsm64<4><<<wg + wgr, 256, 0, s>>>(A, lda, n, k, wgr, PL, PU);
             if ((e = hipGetLastError())) return e;
-            auto g64 = use_rocblas ? gemm64_rocblas : gemm64;
-            if ((e = g64(A + (k + kb) + (k + kb) * lda, lda, A + (k + kb) + k * lda, lda, A + k + (k + kb) * lda, lda,
-                         m - kb, m - kb, kb, s)))
-                return e;
+            const int64_t k1 = k + kb;
+            double* C = A + k1 + k1 * lda;
+            if (use_rocblas)
+                e = gemm64_rocblas(C, lda, A + k1 + k * lda, lda, A + k + k1 * lda, lda, m - kb, m - kb, kb, s);
+            else if (k1 < ge)
+                e = gemm64_part(C, lda, A + k1 + k * lda, lda, A + k + k1 * lda, lda, m - kb, m - kb, kb,
+                                ge < n ? ge - k1 : -1, s);
+            else
+                e = gemm64(C, lda, A + k1 + g0 * lda, lda, A + g0 + k1 * lda, lda, m - kb, m - kb, (int)(k1 - g0), s);
+            if (e) return e;
         }
     }
     return hipSuccess;

@@ -186,3 +186,10 @@ def test_lu64_solve_applies_the_swaps_in_order(n):
         order[i], order[p] = order[p], order[i]
     fac = mxp.Factor64(n, torch.eye(n, dtype=torch.float64, device="cuda"), n, piv.cuda(), 0, 0)
     assert torch.equal(mxp.mxp_lu64_solve(fac, B).cpu(), want[:, order])
+
+
+# four blocks per update: one group and a ragged rest, a rest of one row, a group
+# whose successor is taken block by block
+@pytest.mark.parametrize("n", [4097, 4224, 4609, 5000])
+def test_lu64_in_groups_of_blocks(n):
+    test_lu64_and_solve(n, False, 1)
