@@ -691,17 +691,16 @@ static int first_strips(const FactorPlan& p, int64_t k) {
     return 2 * strip_count(p, k) <= NUM_CU ? strip_count(p, k) : (int)(p.nb / SR);
 }
 
-// Block step k solves its other strips through the block inverses (16-bit
-// storage) while the trailing part is at least MXP_PANEL_MIN blocks: there the
-// products free the compute units the substitution would hold beside the
-// merged update.  Depends on (n, nb, k) alone, so that grouped and single
-// factorisations take the same path.
-#ifndef MXP_PANEL_MIN
-#define MXP_PANEL_MIN 16
-#endif
+// Block step k solves its other strips, where there are any, through the block
+// inverses (16-bit storage): the products take less than the substitution beside
+// the next diagonal LU and free the compute units it would hold beside the merged
+// update.  With the substitution while fewer than 16 blocks are left (the rule when
+// every strip was on the chain): n = 12013 nb = 512 BF16 6.14 against 6.00 ms,
+// n = 16000 nb = 1024 BF16 12.1 against 9.8, n = 9000 nb = 1024 FP16 5.3 against
+// 4.6.  Depends on (n, nb, k) alone, so that grouped and single factorisations take
+// the same path.
 static bool inverse_path(const FactorPlan& p, int64_t k) {
-    return panel_path(p.store) && strip_count(p, k) > first_strips(p, k) &&
-           p.n - k - p.nb >= MXP_PANEL_MIN * p.nb;
+    return panel_path(p.store) && strip_count(p, k) > first_strips(p, k);
 }
 // the first block whose inverses are formed after the factorisation
 static int64_t inv_first_after(const FactorPlan& p) {

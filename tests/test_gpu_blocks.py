@@ -157,10 +157,11 @@ def test_many_right_hand_sides(n):
 
 
 # more strips than CUs (a trailing part of more than 4096): the first strips of a
-# step on their own, the others by substitution (FP32 storage, few blocks) or
-# through the block inverses, against the definition; then in a group bit for bit
+# step on their own, the others by substitution (FP32 storage) or through the
+# block inverses, against the definition; then in a group bit for bit
 @pytest.mark.parametrize("n,nb,update,store", [(4300, 64, "bf16", "bf16"), (4500, 128, "f8", "f16"),
-                                               (4900, 512, "f32", "f32"), (4400, 256, "f16", "f16")])
+                                               (4900, 512, "f32", "f32"), (4400, 256, "f16", "f16"),
+                                               (5400, 1024, "bf16", "bf16")])
 def test_factor_of_more_strips_than_cus(n, nb, update, store):
     _factor_error(n, nb, update, store)
     probs = [mxp.mxp_generate(n - 100 * i, 1, 6 + i, store=store) for i in range(2)]
