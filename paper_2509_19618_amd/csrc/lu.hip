@@ -10,7 +10,9 @@
 //      diagonal sub-blocks of L11 and U11 kept;
 //   2. L21 = A21 U11^-1 and U12 = L11^-1 A12 by blocked substitution in
 //      FP32, one workgroup per 32-row (32-column) strip, fused with the
-//      rounding to the update format under a power-of-two strip scale;
+//      rounding to the update format under a power-of-two strip scale (the
+//      strips beyond the next block's, while they are many, as products with
+//      the block's inverses: panel.hip);
 //   3. A22 <- A22 - L21 U12 on the matrix cores (MFMA), FP32 accumulation,
 //      result rounded to the storage format.
 #include <mutex>

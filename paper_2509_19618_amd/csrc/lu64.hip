@@ -12,15 +12,17 @@
 //   without pivoting: the nb x nb diagonal block is factored by one
 //     work-group in LDS (k_diag64); L21 = A21 U11^-1 and U12 = L11^-1 A12 by
 //     substitution over 16 x 16 blocks on the matrix cores (k_trsm64);
-//   with pivoting: the m x nb panel is factored by one cooperative launch
-//     (k_panel64_pp): every work-group holds a slice of the panel's rows in
-//     LDS; per column each proposes its largest-magnitude candidate, a grid
+//   with pivoting: a panel of up to 8192 rows is factored a few columns at a
+//     time by one work-group (k_panel64_wg, k_panel64_rest), a larger one by
+//     one cooperative launch (k_panel64_pp): every work-group holds a slice of
+//     the panel's rows in LDS; per column each proposes its largest-magnitude candidate, a grid
 //     barrier, every work-group picks the same winner (largest magnitude,
 //     smallest row among equals -- the rule of LAPACK's getrf), the two rows
 //     trade places and every work-group eliminates its rows.  The swaps are
 //     then applied to the columns left and right of the panel (k_laswp64)
 //     and U12 formed as above;
-//   both: A22 <- A22 - L21 U12 with v_mfma_f64_16x16x4f64 (k_gemm64).
+//   both: A22 <- A22 - L21 U12 with v_mfma_f64_16x16x4f64 (k_gemm64), without
+//     pivoting for four blocks at a time while the matrix is large.
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
@@ -1263,7 +1265,7 @@ hipError_t lu64_factor(int64_t n, double* A, int64_t lda, int64_t* ipiv, void* w
     // four at a time: inside such a group an update covers what the group still
     // factors, its columns and its rows, and the rest follows once per group with
     // K = 512 (one pass over C instead of four: the update alone runs at 42 TFLOP/s
-    // with K = 128, 52 with 256).  Factorisation 13.63 -> 12.09 ms at n = 8192, 9.88
+    // with K = 128, 52 with 256, 63 with 512).  Factorisation 13.63 -> 12.09 ms at n = 8192, 9.88
     // -> 9.20 at 6500, 5.66 -> 5.56 at 5000; with groups down to 2048 columns 3.02 ->
     // 3.06 at n = 3000, down to 6144 only 12.39 at 8192.  (Pivoting brings rows of
     // the rest, which lag, into the group.)
