@@ -49,7 +49,6 @@ struct FactorPlan {
     void* Uq;        // 4 sets of op_rows x nb operands (K-major)
     float* inv_sa;   // 4 sets of op_rows/32
     float* inv_sb;   // 4 sets of op_rows/32
-    float* pairw;    // ceil(n / 2nb) x nb x nb: scratch of the pair inverses (D = 2 nb only)
     void* binv;      // 2 x 3 x nb x nb 16-bit parts of the current block's inverses (U11^-1, L11^-1)
     float* binv_sc;  // 2 x nb reciprocal line scales of those parts
     unsigned long long* info;  // 1
@@ -61,7 +60,7 @@ struct AuxLayout {
     size_t T, Trm, linv, uinv, lsc, rowscale, linv_full, uinv_full, total;
 };
 struct WorkLayout {
-    size_t Lq, Uq, inv_sa, inv_sb, info, dsync, pairw, binv, binv_sc, total;
+    size_t Lq, Uq, inv_sa, inv_sb, info, dsync, binv, binv_sc, total;
 };
 AuxLayout aux_layout(int64_t n, int64_t nb);
 // diagonal-block size of the preconditioner's substitution: pairs of factor

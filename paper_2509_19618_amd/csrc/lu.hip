@@ -69,8 +69,6 @@ WorkLayout work_layout(int64_t n, int64_t nb, int update) {
     W.inv_sb = off; off = al256(off + 4 * (size_t)(rows / 32) * 4);
     W.info = off; off = al256(off + 8);
     W.dsync = off; off = al256(off + (size_t)((n + nb - 1) / nb) * diag_sync_words(nb) * 4);
-    W.pairw = off;
-    if (prec_block(nb) == 2 * nb) off = al256(off + (size_t)((n + 2 * nb - 1) / (2 * nb)) * nb * nb * 4);
     W.binv = off; off = al256(off + (size_t)2 * 3 * nb * nb * 2);
     W.binv_sc = off; off = al256(off + (size_t)2 * nb * 4);
     W.total = off;
@@ -489,37 +487,43 @@ MXP_DEV void inv_lower_strip(int kbp, const float* __restrict__ Trm, int ld, con
     }
 }
 
-// the inverses of diagonal blocks blk0.. in one launch (after the
-// factorisation: every block with FP32 storage, the blocks whose strips were
-// solved by substitution otherwise); blockIdx.y = block - blk0, blockIdx.x = strip.  Block blk is
-// diagonal block blk % g of the preconditioner's group blk / g
-// (column-major, ld D).
-__global__ __launch_bounds__(ST_THREADS) void k_inv_upper(int64_t n, int nb, int64_t blk0, const float* __restrict__ Tall,
-                                                   const float* __restrict__ uinv_all, float* __restrict__ out_all) {
+// The inverses formed after the factorisation, up to GEMM_GROUP_MAX of them in a
+// launch (work-groups numbered one after another): the full inverses of the diagonal
+// blocks blk0 .. blk0 + nblk (every block with FP32 storage, the blocks whose strips
+// were all solved by substitution otherwise; the strips of U11^-1, then those of
+// L11^-1), then the off-diagonal blocks of the pairs (k_pair).  Block blk is diagonal
+// block blk % g of the preconditioner's group blk / g (column-major, ld D).  The two
+// triangles of all members are independent: one launch for both and for all of a
+// group, then two for the pairs (one after the other, six launches a member, most of
+// a few dozen work-groups: a group of n = 520 to 5003 at nb = 256 3.41 against
+// 2.99 ms, the solve at n = 600 991 against 963 us).
+struct InvOne {
+    const void* A;
+    int64_t lda, n, blk0;
+    int nb, nblk, npair, wg_inv, wg_pair, pad;
+    const float *T, *Trm, *linv, *uinv, *lsc;
+    float *Li, *Ui;
+};
+struct InvGroup {
+    InvOne g[GEMM_GROUP_MAX];
+    int count;
+};
+__global__ __launch_bounds__(ST_THREADS) void k_inv(const InvGroup grp) {
     extern __shared__ float smem[];
-    const int64_t blk = blk0 + blockIdx.y;
+    int d = 0;
+    while ((int)blockIdx.x >= grp.g[d].wg_inv) ++d;
+    const InvOne& G = grp.g[d];
+    const int w = (int)blockIdx.x - (d > 0 ? grp.g[d - 1].wg_inv : 0);
+    const int nb = G.nb, per = nb / SR, side = w / (per * G.nblk), v = w - side * per * G.nblk;
+    const int64_t blk = G.blk0 + v / per;
     const int64_t k = blk * nb;
-    const int kb = (int)(n - k < nb ? n - k : nb);
+    const int kb = (int)(G.n - k < nb ? G.n - k : nb);
     const int kbp = (kb + 63) / 64 * 64;
-    const int r0 = SR * blockIdx.x;
+    const int r0 = SR * (v % per);
     if (r0 >= kbp) return;
-    const int64_t D = prec_block(nb), g = D / nb, o = (blk % g) * nb;
-    inv_upper_strip(kbp, Tall + blk * nb * nb, nb, uinv_all + blk * nb * 64,
-                    out_all + (blk / g) * D * D + o + o * D, D, r0, smem);
-}
-
-__global__ __launch_bounds__(ST_THREADS) void k_inv_lower(int64_t n, int nb, int64_t blk0, const float* __restrict__ Trm_all,
-                                                   const float* __restrict__ linv_all, float* __restrict__ out_all) {
-    extern __shared__ float smem[];
-    const int64_t blk = blk0 + blockIdx.y;
-    const int64_t k = blk * nb;
-    const int kb = (int)(n - k < nb ? n - k : nb);
-    const int kbp = (kb + 63) / 64 * 64;
-    const int c0 = SR * blockIdx.x;
-    if (c0 >= kbp) return;
-    const int64_t D = prec_block(nb), g = D / nb, o = (blk % g) * nb;
-    inv_lower_strip(kbp, Trm_all + blk * nb * nb, nb, linv_all + blk * nb * 64,
-                    out_all + (blk / g) * D * D + o + o * D, D, c0, smem);
+    const int64_t D = prec_block(nb), g = D / nb, o = (blk % g) * nb, out = (blk / g) * D * D + o + o * D;
+    if (side == 0) inv_upper_strip(kbp, G.T + blk * nb * nb, nb, G.uinv + blk * nb * 64, G.Ui + out, D, r0, smem);
+    else inv_lower_strip(kbp, G.Trm + blk * nb * nb, nb, G.linv + blk * nb * 64, G.Li + out, D, r0, smem);
 }
 
 // the inverses of one block step's diagonal blocks (16-bit storage: formed
@@ -551,9 +555,9 @@ hipError_t block_inverses(const PanelGroup& grp, int wg, int nbmax, hipStream_t 
 //   [[L0, 0], [B, L1]]^-1 = [[L0^-1, 0], [-L1^-1 B L0^-1, L1^-1]],
 //   [[U0, B'], [0, U1]]^-1 = [[U0^-1, -U0^-1 B' U1^-1], [0, U1^-1]],
 // with B and B' the stored panels of the factor (B with its strip factors
-// undone) and the diagonal inverses from k_inv_lower / k_inv_upper.  Each
-// product is one launch over all pairs (blockIdx.z = pair) of 64 x 64
-// output tiles on the FP32 matrix cores; the K range of a tile skips the
+// undone) and the diagonal inverses from k_inv.  Two launches over both
+// triangles of all pairs, a 64 x 64 output tile per work-group on the FP32
+// matrix cores; the K range of a tile skips the
 // zero triangle of its triangular operand.
 // LDS pitches of the staged operands (64 banks): A is written with the rows
 // running over the lanes and read two k rows at a time (pitch 96: the two
@@ -620,19 +624,20 @@ MXP_DEV void pair_store(const f16v_t& acc, float alpha, int M, int N, int i0, in
     }
 }
 
-// phase 0: W = B L0^-1 (kb1 x nb, ld nb, into W), phase 1: X = -L1^-1 W
+// phase 0: W = B L0^-1 (kb1 x nb), phase 1: X = -L1^-1 W.  W stands in the pair's
+// upper right block, which is zero in the inverse and never read.
 template <int ST>
-__global__ __launch_bounds__(256) void k_pair_lower(int64_t n, int nb, const typename Store<ST>::T* __restrict__ A,
-                                                    int64_t lda, const float* __restrict__ lsc, int64_t nstrips32,
-                                                    float* __restrict__ inv_all, float* __restrict__ W, int phase) {
-    __shared__ float sA[32 * PP_SP], sB[32 * PP_SPB];
-    const int64_t p = blockIdx.z, D = 2 * (int64_t)nb;
-    const int64_t k0 = p * D, k1 = k0 + nb;
+MXP_DEV void pair_lower(const InvOne& G, int64_t p, int i0, int j0, int phase, float* sA, float* sB) {
+    typedef typename Store<ST>::T T;
+    const T* A = (const T*)G.A;
+    const int nb = G.nb;
+    const int64_t n = G.n, lda = G.lda, D = 2 * (int64_t)nb;
+    const int64_t k0 = p * D, k1 = k0 + nb, nstrips32 = (n + 31) / 32;
     if (k1 >= n) return;
     const int kb1 = (int)(n - k1 < nb ? n - k1 : nb);
-    float* inv = inv_all + p * D * D;
-    float* Wp = W + p * (int64_t)nb * nb;
-    const int i0 = 64 * blockIdx.y, j0 = 64 * blockIdx.x;
+    float* inv = G.Li + p * D * D;
+    float* Wp = inv + nb * D;
+    const float* lsc = G.lsc;
     if (phase == 0) {
         if (i0 >= kb1) return;
         const float* srow = lsc + (2 * p) * nstrips32;
@@ -641,43 +646,55 @@ __global__ __launch_bounds__(256) void k_pair_lower(int64_t n, int nb, const typ
         };
         auto fb = [&](int k, int j) { return inv[k + (int64_t)j * D]; };
         const f16v_t acc = pair_tile(fa, fb, kb1, nb, i0, j0, j0, nb, sA, sB);   // L0^-1[k][j] = 0 for k < j
-        pair_store(acc, 1.0f, kb1, nb, i0, j0, [&](int i, int j, float v) { Wp[i + (int64_t)j * nb] = v; });
+        pair_store(acc, 1.0f, kb1, nb, i0, j0, [&](int i, int j, float v) { Wp[i + (int64_t)j * D] = v; });
     } else {
         if (i0 >= kb1) return;
         auto fa = [&](int i, int k) { return inv[(nb + i) + (int64_t)(nb + k) * D]; };
-        auto fb = [&](int k, int j) { return Wp[k + (int64_t)j * nb]; };
+        auto fb = [&](int k, int j) { return Wp[k + (int64_t)j * D]; };
         const int kh = i0 + 64 < kb1 ? i0 + 64 : kb1;                             // L1^-1[i][k] = 0 for k > i
         const f16v_t acc = pair_tile(fa, fb, kb1, nb, i0, j0, 0, kh, sA, sB);
         pair_store(acc, -1.0f, kb1, nb, i0, j0, [&](int i, int j, float v) { inv[(nb + i) + (int64_t)j * D] = v; });
     }
 }
 
-// phase 0: W = U0^-1 B' (nb x kb1, ld nb, into W), phase 1: Y = -W U1^-1
+// phase 0: W = U0^-1 B' (nb x kb1, in the pair's lower left block), phase 1:
+// Y = -W U1^-1
 template <int ST>
-__global__ __launch_bounds__(256) void k_pair_upper(int64_t n, int nb, const typename Store<ST>::T* __restrict__ A,
-                                                    int64_t lda, float* __restrict__ inv_all, float* __restrict__ W,
-                                                    int phase) {
-    __shared__ float sA[32 * PP_SP], sB[32 * PP_SPB];
-    const int64_t p = blockIdx.z, D = 2 * (int64_t)nb;
+MXP_DEV void pair_upper(const InvOne& G, int64_t p, int i0, int j0, int phase, float* sA, float* sB) {
+    typedef typename Store<ST>::T T;
+    const T* A = (const T*)G.A;
+    const int nb = G.nb;
+    const int64_t n = G.n, lda = G.lda, D = 2 * (int64_t)nb;
     const int64_t k0 = p * D, k1 = k0 + nb;
     if (k1 >= n) return;
     const int kb1 = (int)(n - k1 < nb ? n - k1 : nb);
-    float* inv = inv_all + p * D * D;
-    float* Wp = W + p * (int64_t)nb * nb;
-    const int i0 = 64 * blockIdx.y, j0 = 64 * blockIdx.x;
+    float* inv = G.Ui + p * D * D;
+    float* Wp = inv + nb;
     if (j0 >= kb1) return;
     if (phase == 0) {
         auto fa = [&](int i, int k) { return inv[i + (int64_t)k * D]; };
         auto fb = [&](int k, int j) { return Store<ST>::load(A, (k0 + k) + (k1 + j) * lda); };
         const f16v_t acc = pair_tile(fa, fb, nb, kb1, i0, j0, i0, nb, sA, sB);   // U0^-1[i][k] = 0 for k < i
-        pair_store(acc, 1.0f, nb, kb1, i0, j0, [&](int i, int j, float v) { Wp[i + (int64_t)j * nb] = v; });
+        pair_store(acc, 1.0f, nb, kb1, i0, j0, [&](int i, int j, float v) { Wp[i + (int64_t)j * D] = v; });
     } else {
-        auto fa = [&](int i, int k) { return Wp[i + (int64_t)k * nb]; };
+        auto fa = [&](int i, int k) { return Wp[i + (int64_t)k * D]; };
         auto fb = [&](int k, int j) { return inv[(nb + k) + (int64_t)(nb + j) * D]; };
         const int kh = j0 + 64 < kb1 ? j0 + 64 : kb1;                             // U1^-1[k][j] = 0 for k > j
         const f16v_t acc = pair_tile(fa, fb, nb, kb1, i0, j0, 0, kh, sA, sB);
         pair_store(acc, -1.0f, nb, kb1, i0, j0, [&](int i, int j, float v) { inv[i + (int64_t)(nb + j) * D] = v; });
     }
+}
+
+template <int ST> __global__ __launch_bounds__(256) void k_pair(const InvGroup grp, int phase) {
+    __shared__ float sA[32 * PP_SP], sB[32 * PP_SPB];
+    int d = 0;
+    while ((int)blockIdx.x >= grp.g[d].wg_pair) ++d;
+    const InvOne& G = grp.g[d];
+    const int w = (int)blockIdx.x - (d > 0 ? grp.g[d - 1].wg_pair : 0);
+    const int t = G.nb / 64, q = w / (t * t), e = w - q * t * t;         // q: triangle and pair
+    const int j0 = 64 * (e % t), i0 = 64 * (e / t);
+    if (q < G.npair) pair_lower<ST>(G, q, i0, j0, phase, sA, sB);
+    else pair_upper<ST>(G, q - G.npair, i0, j0, phase, sA, sB);
 }
 
 // The strips of block step k.  While they are no more than the CUs, one launch
@@ -713,35 +730,36 @@ static int64_t inv_first_after(const FactorPlan& p) {
 }
 
 // the full FP32 inverses of the preconditioner's diagonal blocks (after the
-// factorisation): every factor block's, then the off-diagonal blocks of the
-// pairs.  W: scratch of ceil(n / 2nb) nb^2 floats.
+// factorisations): every factor block's, then the off-diagonal blocks of the
+// pairs
 template <int ST>
-static hipError_t prec_inverses(const FactorPlan& p, float* W, hipStream_t s) {
-    const int64_t n = p.n, nb = p.nb;
-    const int64_t nblk = (n + nb - 1) / nb;
-    // blocks before blk0 got their inverses during the factorisation
-    const int64_t blk0 = inv_first_after(p);
-    dim3 g((unsigned)(nb / SR), (unsigned)(nblk - blk0));
+static hipError_t prec_inverses(const FactorPlan* P, int count, hipStream_t s) {
+    InvGroup grp;
+    grp.count = count;
+    int wi = 0, wp = 0, nbmax = 64;
+    double fl = 0, by = 0;
+    for (int i = 0; i < count; ++i) {
+        const FactorPlan& p = P[i];
+        InvOne& g = grp.g[i];
+        const int64_t n = p.n, nb = p.nb;
+        g.A = p.A; g.lda = p.lda; g.n = n; g.nb = (int)nb; g.pad = 0;
+        // blocks before blk0 got their inverses during the factorisation
+        g.blk0 = inv_first_after(p);
+        g.nblk = (int)((n + nb - 1) / nb - g.blk0);
+        g.npair = prec_block(nb) == 2 * nb && n > nb ? (int)((n + 2 * nb - 1) / (2 * nb)) : 0;
+        g.wg_inv = wi += 2 * g.nblk * (int)(nb / SR);
+        g.wg_pair = wp += 2 * g.npair * (int)((nb / 64) * (nb / 64));
+        g.T = p.T; g.Trm = p.Trm; g.linv = p.linv; g.uinv = p.uinv; g.lsc = p.lsc;
+        g.Li = p.linv_full; g.Ui = p.uinv_full;
+        nbmax = (int)nb > nbmax ? (int)nb : nbmax;
+        fl += (2.0 / 3.0 + (g.npair ? 4.0 : 0.0)) * (double)n * nb * nb;
+        by += 16.0 * (double)n * nb;
+    }
     hipEvent_t pt = prof::begin(prof::DIAG, s);
-    if (blk0 < nblk) {
-        const size_t lds = trsm_smem((int)nb, (int)(g.x * g.y));
-        k_inv_upper<<<g, ST_THREADS, lds, s>>>(n, (int)nb, blk0, p.T, p.uinv, p.uinv_full);
-        k_inv_lower<<<g, ST_THREADS, lds, s>>>(n, (int)nb, blk0, p.Trm, p.linv, p.linv_full);
-    }
-    double fl = 2.0 / 3.0 * (double)n * nb * nb;
-    if (prec_block(nb) == 2 * nb && n > nb) {
-        const int64_t npair = (n + 2 * nb - 1) / (2 * nb);
-        const dim3 gp((unsigned)(nb / 64), (unsigned)(nb / 64), (unsigned)npair);
-        typedef typename Store<ST>::T T;
-        // the lower and then the upper products, each pair of launches through W
-        for (int ph = 0; ph < 2; ++ph)
-            k_pair_lower<ST><<<gp, 256, 0, s>>>(n, (int)nb, (const T*)p.A, p.lda, p.lsc, (n + 31) / 32, p.linv_full,
-                                                W, ph);
-        for (int ph = 0; ph < 2; ++ph)
-            k_pair_upper<ST><<<gp, 256, 0, s>>>(n, (int)nb, (const T*)p.A, p.lda, p.uinv_full, W, ph);
-        fl += 4.0 * (double)n * nb * nb;
-    }
-    prof::end(pt, prof::DIAG, s, fl, 16.0 * (double)n * nb);
+    if (wi) k_inv<<<wi, ST_THREADS, trsm_smem(nbmax, wi), s>>>(grp);
+    if (wp)
+        for (int ph = 0; ph < 2; ++ph) k_pair<ST><<<wp, 256, 0, s>>>(grp, ph);
+    prof::end(pt, prof::DIAG, s, fl, by);
     return hipGetLastError();
 }
 
@@ -938,9 +956,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         hipError_t e2;
         if ((e2 = hipFuncSetAttribute((const void*)k_trsm<ST, OP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)trsm_smem(1024)))) return e2;
-        if ((e2 = hipFuncSetAttribute((const void*)k_inv_upper, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)trsm_smem(1024)))) return e2;
-        return hipFuncSetAttribute((const void*)k_inv_lower, hipFuncAttributeMaxDynamicSharedMemorySize,
+        return hipFuncSetAttribute((const void*)k_inv, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)trsm_smem(1024));
     }();
     if (attr) return attr;
@@ -1032,7 +1048,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
     }
     if (n <= nb) {
         if ((e = diag(0, s))) return e;
-        return prec_inverses<ST>(p, p.pairw, s);
+        return prec_inverses<ST>(&p, 1, s);
     }
     // the first pair of a matrix whose strips are solved in one launch has nothing
     // to overlap with: it stays on the caller's stream
@@ -1121,7 +1137,7 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
     }
     if (side_used && (e = hipStreamWaitEvent(s, LA->ev_side, 0))) return e;
     // full FP32 inverses of the preconditioner's diagonal blocks
-    return prec_inverses<ST>(p, p.pairw, s);
+    return prec_inverses<ST>(&p, 1, s);
 }
 
 static hipError_t factor_dispatch(const FactorPlan& p, hipStream_t s, Lookahead* la) {
@@ -1145,10 +1161,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
     if ((e = hipFuncSetAttribute((const void*)k_trsm<ST, OP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)trsm_smem(1024))))
         return e;
-    if ((e = hipFuncSetAttribute((const void*)k_inv_upper, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)trsm_smem(1024))))
-        return e;
-    if ((e = hipFuncSetAttribute((const void*)k_inv_lower, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if ((e = hipFuncSetAttribute((const void*)k_inv, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)trsm_smem(1024))))
         return e;
     int64_t steps = 0;
@@ -1249,9 +1262,7 @@ static hipError_t factor_group_typed(const FactorPlan* P, int count, hipStream_t
         }
         if ((e = gemms(gc, ng))) return e;
     }
-    for (int g = 0; g < count; ++g)
-        if ((e = prec_inverses<ST>(P[g], P[g].pairw, s))) return e;
-    return hipSuccess;
+    return prec_inverses<ST>(P, count, s);
 }
 
 hipError_t factor_group(const FactorPlan* P, int count, hipStream_t s) {
