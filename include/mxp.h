@@ -226,7 +226,7 @@ int mxp_factor_group(int count, const mxp_factor_item *items, int update, int st
  *         inv_sa/inv_sb four sets of op_rows/32 FP32 factors 1/s per
  *                   32-row strip of Lq / Uq
  *         info      unsigned 64-bit: first failing pivot column, ~0 if none
- *         (then scratch of the preconditioner's inverses)
+ *         (then flags of the diagonal LU and the split inverses of a block)
  * Returns MXP_EINVAL for sizes mxp_factor would reject.
  */
 typedef struct {
