@@ -11,7 +11,7 @@
 // Right-looking, block size nb (64 or 128).  Per block step k, m = n - k:
 //   without pivoting: the nb x nb diagonal block is factored by one
 //     work-group in LDS (k_diag64); L21 = A21 U11^-1 and U12 = L11^-1 A12 by
-//     substitution over 16 x 16 blocks on the matrix cores (k_trsm64);
+//     blocked substitution, its products on the matrix cores (k_trsm64);
 //   with pivoting: a panel of up to 8192 rows is factored a few columns at a
 //     time by one work-group (k_panel64_wg, k_panel64_rest), a larger one by
 //     one cooperative launch (k_panel64_pp): every work-group holds a slice of
@@ -27,6 +27,7 @@
 #include <rocblas/rocblas.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/mxp.h"
 #include "common.hpp"
@@ -216,14 +217,89 @@ hipError_t gemm64_rocblas(double* C, int64_t ldc, const double* A, int64_t lda, 
 }
 
 // ============================================================== block triangles
-// The triangular solves of a block step run on the matrix cores: the nb x nb
-// triangle is cut into 16 x 16 blocks, its diagonal blocks replaced by their
-// inverses, and the blocks of the lower triangle (of L11, and of U11
-// transposed) kept as MFMA operands: block (i, j), i >= j, k-step ks of lane l
-// at 256 (i (i + 1) / 2 + j) + 64 ks + l = M[16 i + l % 16][16 j + 4 ks + l / 16].
+// The triangular solves of a block step cut the nb x nb triangle into 16 x 16
+// blocks: the blocks below its diagonal (of L11, and of U11 transposed) are
+// MFMA operands, block (i, j), i > j, k-step ks of lane l at
+// 256 (i (i + 1) / 2 + j) + 64 ks + l = M[16 i + l % 16][16 j + 4 ks + l / 16];
+// the diagonal blocks are solved by substitution (tri_solve16), their entry
+// M[r][e], r >= e, at 256 (i (i + 3) / 2) + tri_pos(r, e), with the reciprocals of
+// U11's diagonal in places of the other triangle (tri_rp).
 constexpr int TB = 16;                              // triangle block
 constexpr int TRI_MAX = 8 * 9 / 2 * 256;            // doubles of one packed triangle (nb = 128)
 MXP_DEV int tri_off(int i, int j) { return (i * (i + 1) / 2 + j) * 256; }
+MXP_DEV int tri_pos(int r, int e) { return 16 * e + 4 * (r & 3) + (r >> 2); }
+MXP_DEV int tri_rp(int e) { return e ? tri_pos(e - 1, e) : tri_pos(0, 15); }
+
+// lane row G (of four) of the wave to all of them
+MXP_DEV int rows_bcast32(int v, int G) {
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const int r = (G & 1) ? p[1] : p[0];
+    const auto o = __builtin_amdgcn_permlane32_swap(r, r, false, false);
+    return (G & 2) ? o[1] : o[0];
+}
+MXP_DEV double rows_bcast(double v, int G) {
+    return __hiloint2double(rows_bcast32(__double2hiint(v), G), rows_bcast32(__double2loint(v), G));
+}
+
+// M^-1 x0 for a lower 16 x 16 triangle and sixteen lines at once: entry 4 q + g of
+// line c in register q of lane 16 g + c (the layout of the MFMA's result and of
+// its next operand).  coef(e): this lane's M[4 q + g][e], q = 0 ..
+// 3 (not used where not below the diagonal); DIV: diagonal diag(e) with
+// reciprocal rp(e), else 1.  A step's quotient is the product with the
+// reciprocal and one residual correction; where any result is not finite -- a
+// zero, subnormal or infinite diagonal entry, an infinite entry, an overflow --
+// the solve is made again with true quotients.  All coefficients are loaded
+// first: loaded step by step, each step waits for its own.
+// (Substitution, not the product with the block's inverse: without pivoting these
+// blocks are badly conditioned as a rule on uniform entries, and the product then
+// loses the accuracy that its conditioning takes: largest |LU - A| / (eps |L||U|)
+// 363 against 2.4 at n = 4600, scaled residual of the solve 33 against 7 at
+// n = 2000.)
+template <bool DIV, class FC, class FD, class FR>
+MXP_DEV d4v tri_solve16(const d4v x0, FC coef, FD diag, FR rp) {
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    d4v m[TB];
+    double d[TB], r[TB];
+#pragma unroll
+    for (int e = 0; e < TB; ++e) {
+        m[e] = coef(e);
+        if constexpr (DIV) { d[e] = diag(e); r[e] = rp(e); }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    d4v x = x0, y;
+#pragma unroll
+    for (int e = 0; e < TB; ++e) {
+        double t = x[e >> 2];
+        if constexpr (DIV) {
+            const double q = t * r[e];
+            t = fma(fma(-d[e], q, t), r[e], q);
+        }
+        const double b = rows_bcast(t, e & 3);
+        y[e >> 2] = g == (e & 3) ? b : y[e >> 2];
+        // (rows at or above e are done: their part of x is no longer read)
+#pragma unroll
+        for (int q = e >> 2; q < 4; ++q) x[q] = fma(-m[e][q], b, x[q]);
+    }
+    if constexpr (DIV) {
+        if (!__all(isfinite(y[0]) && isfinite(y[1]) && isfinite(y[2]) && isfinite(y[3]))) {
+            x = x0;
+#pragma unroll 1
+            for (int e = 0; e < TB; ++e) {
+                const d4v me = coef(e);
+                const int q0 = e >> 2;
+                double t = q0 == 0 ? x[0] : q0 == 1 ? x[1] : q0 == 2 ? x[2] : x[3];
+                t = t / diag(e);
+                const double b = __shfl(t, 16 * (e & 3) + (lane & 15), 64);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (4 * q + g > e) x[q] -= me[q] * b;
+                    y[q] = 4 * q + g == e ? b : y[q];
+                }
+            }
+        }
+    }
+    return y;
+}
 
 // lane J of each 16-lane row to the whole row
 template <int J> MXP_DEV double row_bcast(double v) {
@@ -249,60 +325,24 @@ template <int J> MXP_DEV void leaf64(double (&x)[TB], int r, int& bad) {
     }
 }
 
-// step S of the inverse of a lower triangle, row r in lane r: m its row
-// (diagonal not read), dinv the reciprocal of its diagonal entry
-template <int S> MXP_DEV void tinv64(double (&X)[TB], const double (&m)[TB], double dinv, int r) {
-    if constexpr (S < TB) {
-        const double sc = r == S ? dinv : 1.0, w = r > S ? m[S] : 0.0;
-#pragma unroll
-        for (int c = 0; c <= S; ++c) {
-            X[c] *= sc;
-            X[c] = fma(-w, row_bcast<S>(X[c]), X[c]);
-        }
-        tinv64<S + 1>(X, m, dinv, r);
-    }
-}
-
-// inverse of the lower triangle M of one 16 x 16 block (lane row r; one wave,
-// groups of 16 lanes independent): m(c) = M[r][c] for c < r, dinv = 1 / M[r][r];
-// written as MFMA operand into dst (lanes of one group: w set) and to s
-// (s[c * 18 + r])
-MXP_DEV void tri_inverse(const double (&m)[TB], double dinv, int r, bool w, double* dst, double* s) {
-    double X[TB];
-#pragma unroll
-    for (int c = 0; c < TB; ++c) X[c] = c == r ? 1.0 : 0.0;
-    tinv64<0>(X, m, dinv, r);
-    if (w) {
-#pragma unroll
-        for (int c = 0; c < TB; ++c) {
-            dst[64 * (c >> 2) + 16 * (c & 3) + r] = X[c];
-            if (s) s[c * 18 + r] = X[c];
-        }
-    }
-}
-
 // ============================================================== diagonal block (no pivoting)
 // LU of the kb x kb block at A[k, k] (kb <= 128) by one work-group: the block
 // in LDS (padded with the identity to a multiple of 16, pitch D64P), right-
 // looking over 16 x 16 blocks.  Per step, wave 0 factors the diagonal block
 // in registers (one row per lane, the pivot row broadcast along a 16-lane row
-// by DPP) and forms both triangles' inverses in the same instructions (L in
-// one 16-lane row, U transposed in another); the waves then form the strips
-// as products with the inverses and update the rest on the FP64 matrix cores,
-// wave 0 taking the next diagonal block first and going on to its LU.  The
-// chain is what bounds it: about 3 us per step, where the column-by-column
-// elimination took two work-group barriers and an LDS pass per column.
-// A zero / non-finite pivot sets *info; the packed triangles of L11 and
-// U11^T go to PL and PU.
+// by DPP); the waves then solve the strips against it (tri_solve16, sixteen rows
+// or columns each) and update the rest on the FP64 matrix cores, wave 0 taking
+// the next diagonal block first and going on to its LU.  The chain of leaf and
+// strip is what bounds it.  A zero / non-finite pivot sets *info; the packed
+// triangles of L11 and U11^T go to PL and PU.
 constexpr int D64P = 130;
-constexpr size_t D64_LDS = (size_t)(128 * D64P + 2 * TB * 18) * 8;
+constexpr size_t D64_LDS = (size_t)(128 * D64P + TB) * 8;
 
 __global__ __launch_bounds__(512) void k_diag64(double* A, int64_t lda, int64_t k, int kb, double* PL, double* PU,
                                                 unsigned long long* info) {
     extern __shared__ __attribute__((aligned(16))) double gsm[];
     double* D = gsm;                                  // D[c * D64P + r]
-    double* sIL = gsm + 128 * D64P;                   // L^-1 of the step's block
-    double* sIU = sIL + TB * 18;                      // U^-T
+    double* sR = gsm + 128 * D64P;                    // reciprocals of the step's pivots
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int P = (kb + TB - 1) / TB, kp = P * TB;
@@ -322,31 +362,23 @@ __global__ __launch_bounds__(512) void k_diag64(double* A, int64_t lda, int64_t 
         for (int q = 0; q < 4; ++q) D[(TB * j + li) * D64P + TB * i + lk + 4 * q] -= acc[q];
     };
     for (int t = 0; t < P; ++t) {
+        const int o = TB * t;
         if (wave == 0) {
             if (t > 0) update(t, t, t - 1);
-            const int o = TB * t;
             asm volatile("" ::: "memory");
-            double x[TB], m[TB];
+            double x[TB];
 #pragma unroll
             for (int c = 0; c < TB; ++c) x[c] = D[(o + c) * D64P + o + li];
             int bad = -1;
             leaf64<0>(x, li, bad);
             if (bad >= 0 && lane == 0) atomicMin(info, (unsigned long long)(k + o + bad + 1));
-            if (lk == 0) {
-#pragma unroll
-                for (int c = 0; c < TB; ++c) D[(o + c) * D64P + o + li] = x[c];
-            }
-            asm volatile("" ::: "memory");
-            // lanes 0-15: L^-1; lanes 16-31: U^-T (row li of U^T is column li of U)
             double dg = 1.0;
 #pragma unroll
             for (int c = 0; c < TB; ++c) {
-                const double u = D[(o + li) * D64P + o + c];
-                m[c] = (lk & 1) ? u : x[c];
-                if (c == li) dg = u;
+                if (c == li) dg = x[c];
+                if (lk == 0) D[(o + c) * D64P + o + li] = x[c];
             }
-            const double dinv = (lk & 1) ? 1.0 / dg : 1.0;
-            tri_inverse(m, dinv, li, lk < 2, ((lk & 1) ? PU : PL) + tri_off(t, t), sIL + (lk & 1) * TB * 18);
+            if (lk == 0) sR[li] = 1.0 / dg;
         } else if (t > 0) {
             // the rest of update t - 1
             const int w = P - t;
@@ -355,26 +387,34 @@ __global__ __launch_bounds__(512) void k_diag64(double* A, int64_t lda, int64_t 
         __syncthreads();
         const int w = P - 1 - t;
         for (int u = wave; u < 2 * w; u += 8) {
-            d4v acc = {0.0, 0.0, 0.0, 0.0};
             if (u < w) {
-                // block (i,t) transposed: U_tt^-T block^T
-                const int i = t + 1 + u;
+                // rows of block (i,t), against U_tt^T
+                double* p = D + (o + lk) * D64P + TB * (t + 1 + u) + li;
+                const d4v x = tri_solve16<true>(
+                    d4v{p[0], p[4 * D64P], p[8 * D64P], p[12 * D64P]},
+                    [&](int e) {
+                        d4v m;
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sIU[(4 * ks + lk) * 18 + li],
-                                                               D[(TB * t + 4 * ks + lk) * D64P + TB * i + li], acc, 0,
-                                                               0, 0);
+                        for (int q = 0; q < 4; ++q) m[q] = D[(o + 4 * q + lk) * D64P + o + e];
+                        return m;
+                    },
+                    [&](int e) { return D[(o + e) * D64P + o + e]; }, [&](int e) { return sR[e]; });
 #pragma unroll
-                for (int q = 0; q < 4; ++q) D[(TB * t + lk + 4 * q) * D64P + TB * i + li] = acc[q];
+                for (int q = 0; q < 4; ++q) p[4 * q * D64P] = x[q];
             } else {
-                const int j = t + 1 + u - w;
+                // columns of block (t,j), against L_tt
+                double* p = D + (TB * (t + 1 + u - w) + li) * D64P + o + lk;
+                const d4v x = tri_solve16<false>(
+                    d4v{p[0], p[4], p[8], p[12]},
+                    [&](int e) {
+                        d4v m;
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sIL[(4 * ks + lk) * 18 + li],
-                                                               D[(TB * j + li) * D64P + TB * t + 4 * ks + lk], acc, 0,
-                                                               0, 0);
+                        for (int q = 0; q < 4; ++q) m[q] = D[(o + e) * D64P + o + 4 * q + lk];
+                        return m;
+                    },
+                    [](int) { return 1.0; }, [](int) { return 1.0; });
 #pragma unroll
-                for (int q = 0; q < 4; ++q) D[(TB * j + li) * D64P + TB * t + lk + 4 * q] = acc[q];
+                for (int q = 0; q < 4; ++q) p[4 * q] = x[q];
             }
         }
         __syncthreads();
@@ -383,39 +423,45 @@ __global__ __launch_bounds__(512) void k_diag64(double* A, int64_t lda, int64_t 
         const int r = e & 127, c = e >> 7;
         if (r < kb) A[(k + r) + (k + c) * lda] = D[c * D64P + r];
     }
-    // the blocks below the diagonal as operands
-    for (int u = wave; u < P * (P - 1) / 2; u += 8) {
-        int i = 1, v = u;
-        while (v >= i) v -= i++;
+    // the packed triangles: the blocks below the diagonal as operands, the
+    // diagonal blocks for the substitution (entry f = tri_pos(r, e))
+    for (int u = wave; u < P * (P + 1) / 2; u += 8) {
+        int i = 0, v = u;
+        while (v > i) v -= ++i;
+        double *pl = PL + tri_off(i, v), *pu = PU + tri_off(i, v);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            PL[tri_off(i, v) + 64 * ks + lane] = D[(TB * v + 4 * ks + lk) * D64P + TB * i + li];
-            PU[tri_off(i, v) + 64 * ks + lane] = D[(TB * i + li) * D64P + TB * v + 4 * ks + lk];
+            const int f = 64 * ks + lane;
+            if (v < i) {
+                pl[f] = D[(TB * v + 4 * ks + lk) * D64P + TB * i + li];
+                pu[f] = D[(TB * i + li) * D64P + TB * v + 4 * ks + lk];
+            } else {
+                const int e = f >> 4, r = (f >> 2 & 3) + 4 * (f & 3), b = TB * i;
+                const int d = r == e - 1 ? e : r == 0 && e == 15 ? 0 : -1;      // the reciprocal kept here
+                pl[f] = r > e ? D[(b + e) * D64P + b + r] : 0.0;
+                pu[f] = r >= e ? D[(b + r) * D64P + b + e] : d >= 0 ? 1.0 / D[(b + d) * D64P + b + d] : 0.0;
+            }
         }
     }
 }
 
-// the packed triangle of L11 from a factored nb x nb block (pivoted panels):
-// wave t the inverse of diagonal block t, then every wave its share of the
-// blocks below
+// the packed triangle of L11 from a factored nb x nb block (pivoted panels)
 __global__ __launch_bounds__(512) void k_pack64(const double* __restrict__ A, int64_t lda, int64_t k, int nb,
                                                 double* __restrict__ PL) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int P = nb / TB;
     const double* B = A + k + k * lda;
-    if (wave < P) {
-        double m[TB];
+    for (int u = wave; u < P * (P + 1) / 2; u += 8) {
+        int i = 0, v = u;
+        while (v > i) v -= ++i;
+        double* pl = PL + tri_off(i, v);
 #pragma unroll
-        for (int c = 0; c < TB; ++c) m[c] = B[TB * wave + li + (int64_t)(TB * wave + c) * lda];
-        tri_inverse(m, 1.0, li, lk == 0, PL + tri_off(wave, wave), nullptr);
-    }
-    for (int u = wave; u < P * (P - 1) / 2; u += 8) {
-        int i = 1, v = u;
-        while (v >= i) v -= i++;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            PL[tri_off(i, v) + 64 * ks + lane] = B[TB * i + li + (int64_t)(TB * v + 4 * ks + lk) * lda];
+        for (int ks = 0; ks < 4; ++ks) {
+            const int f = 64 * ks + lane, e = f >> 4, r = (f >> 2 & 3) + 4 * (f & 3);
+            if (v < i) pl[f] = B[TB * i + li + (int64_t)(TB * v + 4 * ks + lk) * lda];
+            else pl[f] = r > e ? B[TB * i + r + (int64_t)(TB * i + e) * lda] : 0.0;
+        }
     }
 }
 
@@ -424,10 +470,13 @@ __global__ __launch_bounds__(512) void k_pack64(const double* __restrict__ A, in
 // a wave takes 16 rows of A21 (work-groups [0, wgr)) or 16 columns of A12 (the
 // rest) and holds all nb entries of each in registers, in the MFMA result
 // layout, whose registers are also the operands of the next product.  Per
-// 16-block i: acc = M(i, 0..i-1) X(0..i-1) - X(i), X(i) = -M(i,i)^-1 acc, the
-// packed triangle's operands read as whole 512-byte lines.  A wave is a chain
-// of 144 MFMAs of 64 cycles (nb = 128: 3.8 us); one thread per row or column
-// with its entries in LDS was a chain of nb^2/2 dependent LDS reads.
+// 16-block i: X(i) <- M(i,i)^-1 X(i) by substitution (tri_solve16), then X(j) -=
+// M(j,i) X(i) for the blocks after it on the matrix cores (the packed triangle's
+// operands read as whole 512-byte lines).  The chain of a wave bounds it; one
+// thread per row or column with its entries in LDS was a chain of nb^2/2 dependent
+// LDS reads.  The blocks move one place through the registers per step, so that
+// the loop is one copy of its code: eight copies, each run once, were bound by
+// fetching them (43 us per launch at n = 8192).
 template <int P>
 __global__ __launch_bounds__(256) void k_trsm64(double* A, int64_t lda, int64_t n, int64_t k, int wgr,
                                                 const double* __restrict__ PL, const double* __restrict__ PU) {
@@ -435,6 +484,13 @@ __global__ __launch_bounds__(256) void k_trsm64(double* A, int64_t lda, int64_t 
     const int li = lane & 15, lk = lane >> 4;
     const bool right = (int)blockIdx.x < wgr;              // rows of A21
     const int64_t wg = right ? blockIdx.x : blockIdx.x - wgr;
+    const double* __restrict__ M = right ? PU : PL;
+    // the diagonal blocks in LDS: a substitution step that takes its coefficients
+    // from memory waits for them (24 us more per launch at n = 8192)
+    __shared__ __attribute__((aligned(32))) double sT[P][256];
+#pragma unroll
+    for (int i = 0; i < P; ++i) sT[i][threadIdx.x] = M[tri_off(i, i) + threadIdx.x];
+    __syncthreads();
     const int64_t o0 = k + TB * P + (wg * 4 + wave) * TB;  // first row / column of the wave
     if (o0 >= n) return;
     const bool in = o0 + li < n;
@@ -442,32 +498,43 @@ __global__ __launch_bounds__(256) void k_trsm64(double* A, int64_t lda, int64_t 
     // entry e of this lane's row / column: base + (4 q + 16 i) step
     double* base = right ? A + o + (k + lk) * lda : A + (k + lk) + o * lda;
     const int64_t step = right ? lda : 1;
-    const double* __restrict__ M = right ? PU : PL;
     d4v X[P];
 #pragma unroll
     for (int i = 0; i < P; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q) X[i][q] = base[(int64_t)(TB * i + 4 * q) * step];
+    auto solve = [&](auto DIV) {
+#pragma unroll 1
+        for (int i = 0; i < P; ++i) {
+            // the operands of the blocks (i + j, i); X holds the blocks from i on
+            d4v m[P];
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
-        d4v acc = -X[i];
+            for (int j = 1; j < P; ++j) {
+                const double* __restrict__ Mj = M + tri_off(i + j < P ? i + j : P - 1, i);
 #pragma unroll
-        for (int j = 0; j < i; ++j)
+                for (int ks = 0; ks < 4; ++ks) m[j][ks] = Mj[64 * ks + lane];
+            }
+            const double* T = sT[i];
+            const d4v y = tri_solve16<decltype(DIV)::value>(
+                X[0], [&](int e) { return *(const d4v*)(T + tri_pos(lk, e)); },
+                [&](int e) { return T[tri_pos(e, e)]; }, [&](int e) { return T[tri_rp(e)]; });
+            if (in) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(M[tri_off(i, j) + 64 * ks + lane], X[j][ks], acc, 0, 0, 0);
-        d4v y = {0.0, 0.0, 0.0, 0.0};
+                for (int q = 0; q < 4; ++q) base[(int64_t)(TB * i + 4 * q) * step] = y[q];
+            }
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            y = __builtin_amdgcn_mfma_f64_16x16x4f64(M[tri_off(i, i) + 64 * ks + lane], -acc[ks], y, 0, 0, 0);
-        X[i] = y;
-    }
-    if (in) {
+            for (int j = 1; j < P; ++j) {
+                if (i + j >= P) break;
+                d4v acc = X[j];
 #pragma unroll
-        for (int i = 0; i < P; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) base[(int64_t)(TB * i + 4 * q) * step] = X[i][q];
-    }
+                for (int ks = 0; ks < 4; ++ks)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(m[j][ks], -y[ks], acc, 0, 0, 0);
+                X[j - 1] = acc;
+            }
+        }
+    };
+    if (right) solve(std::true_type{});
+    else solve(std::false_type{});
 }
 
 // ============================================================== pivoted panel
