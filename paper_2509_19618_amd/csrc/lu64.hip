@@ -1115,12 +1115,21 @@ MXP_DEV double rl64(double v, int l) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// One wave solves a 64 x 64 triangle, row r in lane r: d[s] = T[r][s], zero
-// outside the strict triangle, dg its diagonal (1 for the unit-lower); NR
-// right-hand sides side by side.  The quotient by the diagonal is the product
-// with its reciprocal and one residual correction.
-template <bool LOWER, int NR> MXP_DEV void tri_solve64(double (&x)[NR], const double (&d)[64], double dg) {
+// One wave solves a 64 x 64 triangle (its first m rows), row r in lane r: d[s] =
+// T[r][s], zero outside the strict triangle, dg its diagonal (1 for the unit-
+// lower); NR right-hand sides side by side.  The quotient by the diagonal is the
+// product with its reciprocal and one residual correction.  Where any result is
+// not finite -- a zero, subnormal or infinite diagonal entry, an infinite entry,
+// an overflow -- that right-hand side is solved again with true quotients and only
+// the rows that a solved one reaches (T[r][s] again from memory, at T + s ld).
+template <bool LOWER, int NR>
+MXP_DEV void tri_solve64(double (&x)[NR], const double (&d)[64], double dg, const double* T, int64_t ld, int m) {
+    const int lane = threadIdx.x & 63;
     const double ri = LOWER ? 1.0 : 1.0 / dg;
+    double x0[NR], y[NR];
+    bool fin[NR], all = true;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x0[r] = x[r];
 #pragma unroll
     for (int s2 = 0; s2 < 64; ++s2) {
         const int s = LOWER ? s2 : 63 - s2;
@@ -1134,12 +1143,35 @@ template <bool LOWER, int NR> MXP_DEV void tri_solve64(double (&x)[NR], const do
             x[r] = fma(-d[s], rl64(q, s), x[r]);
         }
     }
-    if (!LOWER)
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+    for (int r = 0; r < NR; ++r) {
+        if (!LOWER) {
             const double q = x[r] * ri;
             x[r] = fma(fma(-dg, q, x[r]), ri, q);
         }
+        fin[r] = __all(isfinite(x[r]));
+        all = all && fin[r];
+    }
+    if (all) return;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        y[r] = x[r];
+        x[r] = x0[r];
+    }
+#pragma unroll 1
+    for (int s2 = 0; s2 < m; ++s2) {
+        const int s = LOWER ? s2 : m - 1 - s2;
+        const bool reach = lane < m && (LOWER ? s < lane : s > lane);
+        const double t = T[reach ? s * ld : 0];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const double q = LOWER ? x[r] : x[r] / dg;
+            const double b = rl64(q, s);
+            if (reach) x[r] -= t * b;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x[r] = fin[r] ? y[r] : LOWER ? x[r] : x[r] / dg;
 }
 
 // Block step: the block [b0, b0 + kb) and the rows beyond it (above it for
@@ -1223,7 +1255,8 @@ __global__ __launch_bounds__(512) void k_trsv64_step(const double* __restrict__ 
             double v[NR];
 #pragma unroll
             for (int r = 0; r < NR; ++r) v[r] = lane < m ? sx[r][64 * w + lane] : 0.0;
-            tri_solve64<LOWER, NR>(v, d, dg);
+            const int64_t o = b0 + 64 * w;
+            tri_solve64<LOWER, NR>(v, d, dg, A + o + (lane < m ? lane : 0) + o * lda, lda, m);
 #pragma unroll
             for (int r = 0; r < NR; ++r)
                 if (lane < m) {

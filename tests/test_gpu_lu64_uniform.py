@@ -58,3 +58,52 @@ def test_blocks_whose_inverses_overflow(lower):
     assert fac.info == 0
     Lg, Ug = _split(fac, n)
     assert torch.equal(Lg.cpu(), L) and torch.equal(Ug.cpu(), U)
+
+
+def _substitution(LU, B):
+    """L y = b, U x = y row by row and with true quotients, on the CPU"""
+    n = LU.shape[0]
+    x = B.clone()
+    for s in range(n):
+        x[:, s + 1:] -= LU[s + 1:, s] * x[:, s:s + 1]
+    for s in range(n - 1, -1, -1):
+        x[:, s] /= LU[s, s]
+        x[:, :s] -= LU[:s, s] * x[:, s:s + 1]
+    return x
+
+
+# diagonal entries whose reciprocal overflows, is zero or subnormal, a singular
+# factor, infinite entries of a right-hand side: finite, infinite or NaN as a
+# substitution with true quotients has it (row by row 2 n eps of the sums, entries
+# of one sign)
+@pytest.mark.parametrize("what", ["subnormal", "zero", "infinite", "huge", "rhs_first", "rhs_last", "overflow"])
+@pytest.mark.parametrize("n,nrhs", [(40, 1), (130, 2), (300, 7)])
+def test_solve_at_the_ends_of_the_range(what, n, nrhs):
+    print("lu64 solve range", what, n, nrhs, flush=True)
+    gen = torch.Generator().manual_seed(n)
+    LU = -torch.rand((n, n), generator=gen, dtype=torch.float64) / n
+    LU.diagonal().copy_(1 + torch.rand(n, generator=gen, dtype=torch.float64))
+    B = 1 + torch.rand((nrhs, n), generator=gen, dtype=torch.float64)
+    for s in (n // 3, n - 2):
+        if what == "subnormal":                       # a row that stands alone, as small as its pivot
+            LU[s, :], LU[:, s], LU[s, s] = 0.0, 0.0, 2.0 ** -1070
+            B[:, s] = 3 * 2.0 ** -1071
+        elif what == "huge":
+            LU[s, :], LU[:, s], LU[s, s] = 0.0, 0.0, 1.5 * 2.0 ** 1023
+            B[:, s] = 1.25 * 2.0 ** 1023
+        elif what == "overflow":
+            LU[s, s] = 2.0 ** -1000
+            B[:, s] = 2.0 ** 1000
+        elif what in ("zero", "infinite"):
+            LU[s, s] = 0.0 if what == "zero" else float("inf")
+    if what.startswith("rhs"):
+        B[0, 1 if what == "rhs_first" else n - 1] = float("inf")
+    want = _substitution(LU, B)
+    got = mxp.mxp_lu64_solve(mxp.Factor64(n, LU.t().contiguous().cuda(), n, None, 0, 0), B.cuda()).cpu()
+    for r in range(nrhs):                             # whatever stands beside it
+        one = mxp.mxp_lu64_solve(mxp.Factor64(n, LU.t().contiguous().cuda(), n, None, 0, 0), B[r:r + 1].cuda()).cpu()
+        assert torch.equal(one[0].nan_to_num(nan=7.0), got[r].nan_to_num(nan=7.0))
+    fin = want.isfinite()
+    assert torch.equal(got.isfinite(), fin) and torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got[~fin & ~want.isnan()], want[~fin & ~want.isnan()])
+    assert bool(((got - want)[fin].abs() <= 2 * n * EPS * want[fin].abs()).all())
