@@ -347,8 +347,9 @@ int mxp_hpl_eta(int64_t n, uint64_t seed, int kind, const double *diag, const do
  * on the FP64 matrix cores.
  * ipiv (device, n int64 entries, may be NULL): NULL factors without
  *   pivoting; otherwise partial pivoting (largest magnitude in the column,
- *   the first among equals, as LAPACK getrf) with ipiv[k] = the 0-based row
- *   swapped with row k; the swaps are applied to the whole matrix.
+ *   the first among equals, as LAPACK getrf; a NaN counts as zero) with
+ *   ipiv[k] = the 0-based row swapped with row k, k <= ipiv[k] < n whatever the
+ *   entries; the swaps are applied to the whole matrix.
  *   Pivoting needs n <= 65536.
  * gemm: the trailing update, MXP_GEMM64_OWN (this library's FP64 matrix-core
  *   kernel, mxp_trailing_update64) or MXP_GEMM64_ROCBLAS (rocBLAS dgemm, a

@@ -579,6 +579,13 @@ __device__ bool grid_sync(unsigned* bar, unsigned nwg, int* err) {
 MXP_DEV void put64(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 MXP_DEV double get64(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// What a pivot search goes by: the magnitude, a NaN counting as zero.  A row on
+// or below the pivot position then always is a candidate, and ipiv always names
+// one of them: the swaps' kernels index with it.  (A NaN compares false with
+// everything; held by the lane that the others are compared with it hid them, and
+// with one in every work-group there was no candidate at all.)
+MXP_DEV double pivot_size(double a) { return fmax(fabs(a), 0.0); }
+
 // the better of two pivot candidates: larger magnitude, smaller row among equals
 MXP_DEV void better(double& v, int64_t& r, double ov, int64_t orr) {
     if (ov > v || (ov == v && orr < r)) { v = ov; r = orr; }
@@ -614,6 +621,11 @@ __global__ __launch_bounds__(256) void k_panel64_pp(double* A, int64_t lda, int6
     const int64_t rbase = k + (int64_t)w * rpw;                 // global row of local row 0
     const int nrows = (int)(n - rbase < rpw ? n - rbase : rpw);
     const int slot = nb + 2;
+    // after a wait that expired, here or in a panel before: no swaps from column j on
+    auto leave = [&](int j) {
+        if (w == 0 && t >= j && t < nb) ipiv[k + t] = k + t;
+    };
+    if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return leave(0);
     for (int c = 0; c < nb; ++c)
         if (t < nrows) P[c * rpw + t] = A[(rbase + t) + (k + c) * lda];
     __syncthreads();
@@ -624,7 +636,7 @@ __global__ __launch_bounds__(256) void k_panel64_pp(double* A, int64_t lda, int6
         double bv = -1.0;
         int64_t br = INT64_MAX;
         if (t < nrows && rbase + t >= gtop) {
-            bv = fabs(P[j * rpw + t]);
+            bv = pivot_size(P[j * rpw + t]);
             br = rbase + t;
         }
         wg_argmax(bv, br, redv, redr);
@@ -636,7 +648,7 @@ __global__ __launch_bounds__(256) void k_panel64_pp(double* A, int64_t lda, int6
         if (bv >= 0.0 && t < nb) put64(&my[2 + t], P[t * rpw + (int)(br - rbase)]);
         if (gtop >= rbase && gtop < rbase + nrows && t < nb) put64(&top[par * nb + t], P[t * rpw + (int)(gtop - rbase)]);
         // (b) every candidate and the top row are published
-        if (!grid_sync(bar, nwg, err)) return;
+        if (!grid_sync(bar, nwg, err)) return leave(j);
         // (c) the winner, the same in every work-group: one candidate per thread
         double cv = -1.0;
         int64_t cr = INT64_MAX;
@@ -742,13 +754,13 @@ MXP_DEV void panel_step(double (&x)[R][W], int64_t k0, int m, int tid, int lane,
     if constexpr (J < W) {
         constexpr int par = J & 1;
         // this wave's candidate: the largest |x[.][J]| on or below the pivot
-        // position, the smallest row among equals (a NaN counts as zero)
+        // position, the smallest row among equals
         double v = -1.0;
         int row = 0x7FFFFFFF;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int r = tid + PW_T * i;
-            const double a = fmax(fabs(x[i][J]), 0.0);
+            const double a = pivot_size(x[i][J]);
             if (r >= J && r < m && a > v) { v = a; row = r; }
         }
         const double wm = wave_max64(v);
@@ -864,7 +876,7 @@ __global__ __launch_bounds__(PW_T) void k_panel64_wg(double* A, int64_t lda, int
                 int p = j;
                 double best = -1.0;
                 for (int r = j; r < m; ++r) {
-                    const double a = fmax(fabs(sval[0][r][j]), 0.0);
+                    const double a = pivot_size(sval[0][r][j]);
                     if (a > best) { best = a; p = r; }
                 }
                 ipiv[k0 + j] = k0 + p;
