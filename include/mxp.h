@@ -122,10 +122,11 @@ int mxp_generate(int64_t n, int64_t nrhs, uint64_t seed, int kind, double gamma,
  * Right-looking blocked LU without pivoting with block size nb.  Per block
  * step: the diagonal block is factored in FP32; the block column
  * L21 = A21 U11^-1 and block row U12 = L11^-1 A12 are formed at FP32
- * quality -- while the trailing part has more than 4096 rows and `store`
- * is 16-bit, beyond the next block as products with the diagonal block's
- * FP32 inverses split into 16-bit parts (matrix cores, FP32 accumulation),
- * otherwise by blocked FP32 substitution; both are rounded to the update format `update`
+ * quality -- while the trailing part has more than 4096 rows and at least 16
+ * blocks and `store` is 16-bit, beyond the next block as products with the
+ * diagonal block's FP32 inverses split into 16-bit parts (matrix cores, FP32
+ * accumulation), otherwise by blocked FP32 substitution; both are rounded to the
+ * update format `update`
  * (MXP_F16, MXP_BF16, MXP_F8E4M3 with a power-of-two scale per strip of
  * rows of L21 / columns of U12; MXP_F32 for an all-FP32 factorisation);
  * the trailing matrix is updated A22 <- A22 - L21 U12 on the matrix cores

@@ -710,16 +710,21 @@ static int first_strips(const FactorPlan& p, int64_t k) {
     return 2 * strip_count(p, k) <= NUM_CU ? strip_count(p, k) : (int)(p.nb / SR);
 }
 
-// Block step k solves its other strips, where there are any, through the block
-// inverses (16-bit storage): the products take less than the substitution beside
-// the next diagonal LU and free the compute units it would hold beside the merged
-// update.  With the substitution while fewer than 16 blocks are left (the rule when
-// every strip was on the chain): n = 12013 nb = 512 BF16 6.14 against 6.00 ms,
-// n = 16000 nb = 1024 BF16 12.1 against 9.8, n = 9000 nb = 1024 FP16 5.3 against
-// 4.6.  Depends on (n, nb, k) alone, so that grouped and single factorisations take
-// the same path.
+// Block step k solves its other strips through the block inverses (16-bit storage)
+// while at least 16 blocks are left: the products free the compute units that the
+// substitution would hold beside the merged update.  With fewer left they are
+// solved by substitution too: the inverses' 16-bit parts are not as accurate.
+// Against FP64 from the FP32 factor of the block, in units of 2^-24 of a column's
+// largest (a model with these roundings, nb = 512, dominant and sqrt(n) matrices):
+// substitution 0.35-0.45, two FP16 parts 3.9-4.5, three BF16 parts 0.58-0.60.
+// (Products wherever there are other strips would be the faster: n = 12013
+// nb = 512 BF16 5.82 against 5.95 ms, n = 16000 nb = 1024 BF16 9.7 against 12.0,
+// n = 20001 nb = 512 FP8 on FP16 10.68 against 10.74.)
+// Depends on (n, nb, k) alone, so that grouped and single factorisations take the
+// same path.
+constexpr int INV_BLOCKS = 16;
 static bool inverse_path(const FactorPlan& p, int64_t k) {
-    return panel_path(p.store) && strip_count(p, k) > first_strips(p, k);
+    return panel_path(p.store) && strip_count(p, k) > first_strips(p, k) && p.n - k - p.nb >= INV_BLOCKS * p.nb;
 }
 // the first block whose inverses are formed after the factorisation
 static int64_t inv_first_after(const FactorPlan& p) {
