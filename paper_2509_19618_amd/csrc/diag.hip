@@ -30,17 +30,21 @@
 // each the operand the other's update needs.  (With 32 x 32 x 2 MFMAs, whose
 // results take twice as long, the leaf took 3.1 us.)
 //
-// Work-group 0 carries the chain that bounds the block: wave 0 the diagonal
+// One work-group carries the chain that bounds the block: wave 0 the diagonal
 // tiles, four waves the tiles at distance one and two from the diagonal (both
 // sides), exchanging through LDS; two waves publish their tiles.  A chain tile
 // of step t only takes its last update (by step t - 1; the diagonal tile its
 // last two) there.  All other
 // tiles, the earlier updates of the chain's tiles, the copies of its tiles that
 // later kernels read and the inverses of the 64 x 64 diagonal sub-blocks are
-// tasks taken in order from a device counter by the remaining waves (one of
-// work-group 0, so that one resident work-group suffices, and all of the
+// tasks taken in order from a device counter by the remaining waves (one of the
+// chain's work-group, so that one resident work-group suffices, and all of the
 // others).  A task only waits for tiles of earlier tasks and of the chain's
-// earlier steps.  Tiles between work-groups go through device-scope accesses
+// earlier steps.  The chain's work-group is the first of the block to start, by a
+// device counter, not one index: the hardware deals the indices out to the XCDs,
+// each dispatching its share in order, and the helpers of several launches on
+// several streams could hold the places that the work-groups they wait for need.
+// So every wait is for work-groups that have started.  Tiles between work-groups go through device-scope accesses
 // with one flag per tile; a flag is raised after the tile's stores are
 // acknowledged (sync_release in common.hpp).  Every wait is bounded: on expiry
 // it records an error in *info and the wave exits.
@@ -68,15 +72,15 @@ constexpr int SP = 36;              // LDS pitch of a tile
 constexpr int TILE_F = 32 * SP;     // floats of a tile in LDS
 constexpr int FAC_F = TILE_F + 32;  // a triangle and its diagonal's reciprocals
 constexpr int NR = 2;               // ring slots per side and distance
-// LDS of work-group 0 (floats): two leaf slots (L, U with reciprocals), the
+// LDS of the chain's work-group (floats): two leaf slots (L, U with reciprocals), the
 // rings of distance one and two, and the triangle of its task wave; the other
 // work-groups: one triangle per wave
 constexpr int O_FAC = 0;                            // [slot][L, U]
 constexpr int O_RING = 4 * FAC_F;                   // [distance - 1][side][slot]
 constexpr int O_TASK = O_RING + 4 * NR * TILE_F;
 constexpr int O_END = O_TASK + FAC_F;
-constexpr unsigned LIMIT_G = 1u << 22;              // polls of a device flag
-constexpr unsigned LIMIT_L = 1u << 25;              // polls of an LDS word
+constexpr unsigned LIMIT_G = 1u << 26;              // polls of a device flag
+constexpr unsigned LIMIT_L = 1u << 29;              // polls of an LDS word
 
 MXP_DEV float rl(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
 MXP_DEV int ild(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -312,7 +316,8 @@ struct DiagGroup {
     int count;
 };
 
-// device words of one block: the task counter, then a flag per side and tile:
+// device words of one block: the task counter, the count of work-groups that have
+// started, then (from SYNC_FLAGS on) a flag per side and tile:
 // 1 = the early part of a chain tile is stored, 2 = the tile is final; the
 // diagonal tile's final flag is side 0's, its early flag side 1's
 constexpr int SYNC_FLAGS = 16;
@@ -338,6 +343,7 @@ __global__ __launch_bounds__(DT, 4) void k_diag_lu(const DiagGroup grp) {
     typedef typename Store<ST>::T STT;
     extern __shared__ __attribute__((aligned(16))) float dsm[];
     __shared__ int s_w[16];            // progress of the chain, in steps (see W_*)
+    __shared__ int s_order;            // work-groups of the block that started before
     const DiagOne& G = grp.g[blockIdx.y];
     if ((int)blockIdx.x >= G.wgs) return;
     STT* A = (STT*)G.A;
@@ -614,19 +620,19 @@ __global__ __launch_bounds__(DT, 4) void k_diag_lu(const DiagGroup grp) {
     // whose distance-one and -two tiles are published, leaves done, leaves
     // published, and steps solved per distance and side
     constexpr int W_UPD = 0, W_PUB = 5, W_LEAF = 7, W_PUBLEAF = 8, W_DONE = 9;
-    if (blockIdx.x == 0) {
-        if (tid < 16) s_w[tid] = 0;
-        __syncthreads();
-    }
-    // roles of work-group 0's waves: 0 the diagonal, 1 and 2 distance one, 3
-    // and 7 distance two, 4 and 5 publish (they run no MFMA beside waves 0 and
-    // 1 on their SIMDs), 6 takes tasks
-    if (blockIdx.x != 0 || wave == 6) {
-        task_loop(dsm + (blockIdx.x ? wave * FAC_F : O_TASK));
+    if (tid < 16) s_w[tid] = 0;
+    if (tid == 0) s_order = __hip_atomic_fetch_add(G.sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool helper = __builtin_amdgcn_readfirstlane(s_order) != 0;
+    // roles of the waves of the first work-group: 0 the diagonal, 1 and 2 distance
+    // one, 3 and 7 distance two, 4 and 5 publish (they run no MFMA beside waves 0
+    // and 1 on their SIMDs), 6 takes tasks
+    if (helper || wave == 6) {
+        task_loop(dsm + (helper ? wave * FAC_F : O_TASK));
         return;
     }
 
-    // ---- the chain (work-group 0)
+    // ---- the chain (the block's first work-group)
     auto fac = [&](int t, int side) -> float* { return dsm + O_FAC + ((t & 1) * 2 + side) * FAC_F; };
     auto ring = [&](int dist, int side, int t) -> float* {
         return dsm + O_RING + (((dist - 1) * 2 + side) * NR + t % NR) * TILE_F;
