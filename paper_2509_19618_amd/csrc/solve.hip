@@ -254,8 +254,7 @@ __global__ __launch_bounds__(512, 4) void k_trsv(int64_t n, int nb, int db, cons
     // Loads carry no condition (a column past the range re-reads the first and
     // has the weight zero): a load under a branch ends in a wait for every load
     // in flight, which would serialise them.  A uniform base and 32-bit byte
-    // offsets (a block of 1024 columns spans less than 4 GB for any matrix that
-    // fits the card).
+    // offsets: VEC only where the 128 columns of a wave span at most 4 GB.
     u32x4v pre[PF];
     double acc[RPL] = {};
     float us = 1.0f;
@@ -451,7 +450,9 @@ static hipError_t prec_typed(const PrecPlan& p, const double* V, int64_t ldv, do
     double *Y = W, *Tf = Y + n * nr, *Xb = Tf + n * nr, *Tb = Xb + n * nr;
     unsigned* tk = prec_words(W, n, nr);
     int* err = (int*)(tk + 2);
-    const bool vec = ((p.lda * (int64_t)sizeof(T)) % 16 == 0 && ((uintptr_t)p.A) % 16 == 0);
+    // 16-byte loads: aligned columns, and a wave's 128 of them within 32-bit offsets
+    const int64_t colb = p.lda * (int64_t)sizeof(T);
+    const bool vec = colb % 16 == 0 && ((uintptr_t)p.A) % 16 == 0 && colb <= (1ll << 32) / 128;
     const int db = (int)prec_block(nb);
     const dim3 grid((unsigned)S, (unsigned)nr);
     hipEvent_t pt = prof::begin(prof::PREC, s);
