@@ -28,19 +28,23 @@ hipError_t fill_u64(void* p, int64_t count, uint64_t v, hipStream_t s) {
 // ---------------------------------------------------------------- generation
 // Thread: GEN_R consecutive rows by a run of column quads; one Philox call
 // gives A[i, 4q..4q+3].  Each thread also accumulates sum_j |k(i,j) - 2^31|
-// exactly in 64-bit integers; the per-row sums are combined with integer
-// atomics, which are exact and order independent.  Entries are s 2^-32 (s = k -
-// 2^31) for the matrices with entries in [-1/2, 1/2), s 2^-31 for those in
+// exactly in 64-bit integers; the work-group's four waves take the same rows and
+// every fourth quad, and add their sums in LDS; the work-groups' are combined with
+// integer atomics, which are exact and order independent.  Entries are s 2^-32 (s
+// = k - 2^31) for the matrices with entries in [-1/2, 1/2), s 2^-31 for those in
 // [-1, 1).
 //
-// Bound: the stores at large n (16-bit: 2 n^2 bytes) and the Philox rounds
-// (shared with the regenerating product, 0.36 ms at n = 32768).  Each entry was
-// rounded through FP64 bits (about 40 integer instructions) and stored alone:
-// 1.61 ms at n = 32768 FP16, 72 us at n = 600, where 64 quads per thread left
-// 9 work-groups.  Four rows per thread make the stores 8 bytes (16-bit
-// formats), the rounding below is a few instructions, and the quads per thread
-// follow from n.
-constexpr int GEN_R = 4;       // rows per thread
+// Bound: the stores at large n (2 to 8 n^2 bytes) and the Philox rounds (shared with
+// the regenerating product, 0.36 ms at n = 32768), below that the atomics, one per
+// row and work-group.  A lane's rows of a column are one store of 8 (16-bit formats)
+// or 16 bytes: with four rows in FP64 too, each of its two stores wrote half of
+// every 32 bytes.  The whole generation, n = 600 / 5000 / 8192 / 20001, FP16 14 / 33
+// / 57 / 273 us, FP32 14 / 28 / 52 / 328, FP64 14 / 42 / 114 / 601 (n = 32768 FP16
+// 680).  With each thread on rows of its own, atomics and all, and four to 64
+// quads: FP16 17 / 71 / 149 / 278, FP32 16 / 71 / 149 / 335, FP64 16 / 77 / 178 / 685;
+// one row and 64 quads per thread, each entry rounded through FP64 bits and stored
+// alone: FP16 83 / 101 / 141 / 620, FP32 38 / 48 / 67 / 353, FP64 38 / 47 / 131 / 611.
+template <int ST> constexpr int GEN_R = ST == F64 ? 2 : 4;       // rows per thread
 
 // s unit (unit a power of two) rounded once to the storage format.  Beyond 24
 // bits the draw is first rounded to a multiple of 256 by rounding to odd (its
@@ -61,44 +65,49 @@ template <int ST>
 __global__ __launch_bounds__(256) void k_gen_matrix(int64_t n, uint64_t seed, float unit, typename Store<ST>::T* A,
                                                     int64_t lda, int vec, int64_t quads,
                                                     unsigned long long* rowsum) {
+    constexpr int R = GEN_R<ST>;
     typedef typename Store<ST>::T T;
-    typedef T TV __attribute__((ext_vector_type(GEN_R)));
+    typedef T TV __attribute__((ext_vector_type(R)));
+    __shared__ unsigned long long part[4][64 * R];
     uint32_t k0[10], k1[10];
     philox_keys(seed, k0, k1);
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * GEN_R;
-    if (i >= n) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = (int64_t)blockIdx.x * (64 * R), i = r0 + lane * R;
     const int64_t nq = (n + 3) / 4;
-    const int64_t q0 = (int64_t)blockIdx.y * quads, q1 = q0 + quads < nq ? q0 + quads : nq;
-    unsigned long long acc[GEN_R] = {};
-    const bool whole = vec && i + GEN_R <= n;
-    for (int64_t q = q0; q < q1; ++q) {
-        uint32_t w[GEN_R][4];
+    const int64_t q0 = (int64_t)blockIdx.y * 4 * quads, q1 = q0 + 4 * quads < nq ? q0 + 4 * quads : nq;
+    unsigned long long acc[R] = {};
+    const bool whole = vec && i + R <= n;
+    if (i < n)
+        for (int64_t q = q0 + wave; q < q1; q += 4) {
+            uint32_t w[R][4];
 #pragma unroll
-        for (int r = 0; r < GEN_R; ++r) philox4((uint32_t)(i + r), (uint32_t)q, 0u, k0, k1, w[r]);
+            for (int r = 0; r < R; ++r) philox4((uint32_t)(i + r), (uint32_t)q, 0u, k0, k1, w[r]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int64_t j = 4 * q + t;
-            if (j >= n) break;
-            TV v;
+            for (int t = 0; t < 4; ++t) {
+                const int64_t j = 4 * q + t;
+                if (j >= n) break;
+                TV v;
 #pragma unroll
-            for (int r = 0; r < GEN_R; ++r) {
-                const int32_t s = draw_offset(w[r][t]);
-                acc[r] += (uint32_t)(s < 0 ? 0u - (uint32_t)s : (uint32_t)s);
-                v[r] = gen_value<ST>(s, unit);
-            }
-            if (!A) continue;
-            if (whole) {
-                *(TV*)(A + i + j * lda) = v;
-            } else {
+                for (int r = 0; r < R; ++r) {
+                    const int32_t s = draw_offset(w[r][t]);
+                    acc[r] += (uint32_t)(s < 0 ? 0u - (uint32_t)s : (uint32_t)s);
+                    v[r] = gen_value<ST>(s, unit);
+                }
+                if (!A) continue;
+                if (whole) {
+                    *(TV*)(A + i + j * lda) = v;
+                } else {
 #pragma unroll
-                for (int r = 0; r < GEN_R; ++r)
-                    if (i + r < n) A[i + r + j * lda] = v[r];
+                    for (int r = 0; r < R; ++r)
+                        if (i + r < n) A[i + r + j * lda] = v[r];
+                }
             }
         }
-    }
 #pragma unroll
-    for (int r = 0; r < GEN_R; ++r)
-        if (i + r < n) atomicAdd(&rowsum[i + r], acc[r]);
+    for (int r = 0; r < R; ++r) part[wave][R * lane + r] = acc[r];
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 64 * R && r0 + t < n) atomicAdd(&rowsum[r0 + t], part[0][t] + part[1][t] + part[2][t] + part[3][t]);
 }
 
 // row sums and the norm cleared
@@ -173,12 +182,15 @@ static hipError_t gen_launch(int64_t n, int64_t nrhs, uint64_t seed, int kind, d
     const unsigned rows = (unsigned)((n + 255) / 256);
     k_gen_clear<<<rows, 256, 0, s>>>((unsigned long long*)diag, n, (unsigned long long*)a_inf);
     if ((e = hipGetLastError())) return e;
-    // about 4096 work-groups, 4 to 64 column quads per thread
-    const int64_t nq = (n + 3) / 4, gx = (n + 256 * GEN_R - 1) / (256 * GEN_R);
-    int64_t quads = nq * gx / 4096;
-    quads = quads < 4 ? 4 : quads > 64 ? 64 : quads;
-    const int vec = lda % GEN_R == 0 && (uintptr_t)A % (GEN_R * sizeof(T)) == 0;
-    k_gen_matrix<ST><<<dim3((unsigned)gx, (unsigned)((nq + quads - 1) / quads)), 256, 0, s>>>(
+    // 2 to 16 column quads per wave, 2048 work-groups if that gives them: with up to 64
+    // too few are left (n = 10000 FP16 90 against 138 us), with at least 4 the small
+    // orders take no less
+    constexpr int R = GEN_R<ST>;
+    const int64_t nq = (n + 3) / 4, gx = (n + 64 * R - 1) / (64 * R);
+    int64_t quads = nq * gx / (4 * 2048);
+    quads = quads < 2 ? 2 : quads > 16 ? 16 : quads;
+    const int vec = lda % R == 0 && (uintptr_t)A % (R * sizeof(T)) == 0;
+    k_gen_matrix<ST><<<dim3((unsigned)gx, (unsigned)((nq + 4 * quads - 1) / (4 * quads))), 256, 0, s>>>(
         n, seed, (float)gen_offscale(kind), (T*)A, lda, vec, quads, (unsigned long long*)diag);
     if ((e = hipGetLastError())) return e;
     k_gen_finalize<ST><<<rows, 256, 0, s>>>(n, seed, kind, shift, (T*)A, lda, diag, row_l1,
