@@ -107,3 +107,16 @@ def test_solve_at_the_ends_of_the_range(what, n, nrhs):
     assert torch.equal(got.isfinite(), fin) and torch.equal(got.isnan(), want.isnan())
     assert torch.equal(got[~fin & ~want.isnan()], want[~fin & ~want.isnan()])
     assert bool(((got - want)[fin].abs() <= 2 * n * EPS * want[fin].abs()).all())
+
+
+# groups of one, two and four right-hand sides, the last one with one to four: each
+# solution as if alone
+@pytest.mark.parametrize("n", [16, 129, 700])
+@pytest.mark.parametrize("nrhs", [2, 3, 4, 5, 63, 64])
+def test_right_hand_sides_are_independent(n, nrhs):
+    print("lu64 right-hand sides", n, nrhs, flush=True)
+    prob = mxp.mxp_generate(n, nrhs, 9, store="f64", kind=mxp.GEN_UNIFORM)
+    fac = mxp.mxp_lu64_factor(prob.A, n, prob.lda, True)
+    X = mxp.mxp_lu64_solve(fac, prob.B)
+    for r in {0, nrhs // 2, nrhs - 1}:
+        assert torch.equal(mxp.mxp_lu64_solve(fac, prob.B[r:r + 1].contiguous())[0], X[r])
