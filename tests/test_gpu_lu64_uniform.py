@@ -37,6 +37,24 @@ def test_unpivoted_uniform_is_backward_stable(n, seed):
     assert ratio <= 8
 
 
+# blocks of 64 (orders above 32768), on a sample of the rows
+def test_unpivoted_uniform_with_blocks_of_64():
+    n = 32900
+    print("lu64 unpivoted uniform", n, flush=True)
+    prob = mxp.mxp_generate(n, 1, 2, store="f64", kind=mxp.GEN_UNIFORM)
+    rows = torch.cat([torch.arange(r, r + 70, device="cuda") for r in (0, 60, 5000, 20000, n - 70)])
+    A = mxp.as_matrix(prob.A, n)[rows].clone()
+    fac = mxp.mxp_lu64_factor(prob.A, n, prob.lda, False)
+    assert fac.info == 0
+    LU = mxp.as_matrix(fac.LU, n)
+    L = torch.where(torch.arange(n, device="cuda")[None, :] < rows[:, None], LU[rows], 0.0)
+    L[torch.arange(len(rows), device="cuda"), rows] = 1.0
+    U = torch.triu(LU)
+    ratio = float(((L @ U - A).abs() / (L.abs() @ U.abs_())).max()) / EPS
+    print("  |LU - A| / (eps |L||U|): %.2f" % ratio, flush=True)
+    assert ratio <= 8
+
+
 # Diagonal blocks with 2^100 beside the diagonal: the inverse of such a 16 x 16
 # block overflows, the substitution for the right-hand sides here is exact.  In
 # the block's own 128 rows and in the strips beyond.

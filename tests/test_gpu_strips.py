@@ -6,12 +6,14 @@ import pytest
 import torch
 
 import paper_2509_19618_amd as mxp
+from test_gpu_factor import test_factor_backward_and_forward_error as _factor_error
 
 pytestmark = pytest.mark.gpu
 
 
 def _first_step(n, nb, update, store, seed=6, kind=mxp.GEN_DOMINANT):
-    """(stored, exact) of both sides, lines of the solve as rows, in the stored scale"""
+    """Of both sides, lines of the solve as rows: the stored panel, the exact one in
+    its scale, the scale, the right-hand sides and the triangle's inverse."""
     prob = mxp.mxp_generate(n, 1, seed, store=store, kind=kind, gamma=1.0)
     A = mxp.as_matrix(prob.A, n)
     A21, A12 = A[nb:, :nb].double(), A[:nb, nb:].double()
@@ -26,7 +28,10 @@ def _first_step(n, nb, update, store, seed=6, kind=mxp.GEN_DOMINANT):
     L = torch.tril(T, -1) + torch.eye(nb, dtype=torch.float64, device="cuda")
     l = torch.linalg.solve_triangular(U, A21, upper=True, left=False)
     u = torch.linalg.solve_triangular(L, A12, upper=False, unitriangular=True).t()
-    return (F[nb:, :nb], l * s), (F[:nb, nb:].t(), u)
+    eye = torch.eye(nb, dtype=torch.float64, device="cuda")
+    Ui = torch.linalg.solve_triangular(U, eye, upper=True)
+    Li = torch.linalg.solve_triangular(L, eye, upper=False, unitriangular=True)
+    return (F[nb:, :nb], l * s, s, A21, Ui), (F[:nb, nb:].t(), u, torch.ones_like(s), A12.t(), Li.t())
 
 
 # The strips next to the diagonal block are solved by FP32 substitution.  Where
@@ -41,7 +46,7 @@ def _first_step(n, nb, update, store, seed=6, kind=mxp.GEN_DOMINANT):
 def test_every_strip_is_as_accurate_as_the_first(n, nb, update, kind):
     print("strips", n, nb, update, kind, flush=True)
     assert 4096 < n - nb < 16 * nb
-    for got, want in _first_step(n, nb, update, "f16", kind=kind):
+    for got, want, *_ in _first_step(n, nb, update, "f16", kind=kind):
         off = got != want.to(torch.float16)
         first, rest = off[:nb], off[nb:]
         a, b = int(first.sum()), int(rest.sum())
@@ -49,3 +54,53 @@ def test_every_strip_is_as_accurate_as_the_first(n, nb, update, kind):
         print("  not the exact rounding: first %d of %d, others %d of %d" % (a, first.numel(), b, rest.numel()),
               flush=True)
         assert b <= expect * (2 * a + 5 * max(a, 1) ** 0.5)
+
+
+def _on_inverse_path(n, nb):
+    # more strips than one launch takes, at least 16 blocks left
+    return n - nb > 4096 and n - nb >= 16 * nb
+
+
+INVERSE = [(4300, 64, "f16", "f16"), (4500, 128, "f8", "bf16"), (4700, 256, "f8", "f16"), (4700, 256, "bf16", "bf16"),
+           (8800, 512, "f16", "f16"), (17500, 1024, "f16", "f16"), (17500, 1024, "bf16", "bf16")]
+
+
+# The strips through the block's inverses: 64-row tiles (FP16, nb <= 512; waves
+# without a column block at nb = 64), 32-row tiles, every number of parts and
+# operand format.  Within the rounding to storage, FP32 products (4 nb 2^-24 |A|
+# |U^-1|: the inverse and the sum) and the parts' last place (2^-24 of a line's
+# largest, doubled).
+@pytest.mark.parametrize("n,nb,update,store", INVERSE)
+def test_strips_through_the_inverses(n, nb, update, store):
+    print("inverse strips", n, nb, update, store, flush=True)
+    assert _on_inverse_path(n, nb)
+    for side, (got, want, s, rhs, inv) in enumerate(_first_step(n, nb, update, store)):
+        rhs, inv = rhs.abs(), inv.abs()
+        err = 4 * nb * 2.0 ** -24 * (rhs @ inv) + 2.0 ** -23 * rhs.sum(1)[:, None] * inv.amax(0)[None, :]
+        u = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[store]
+        bound = u * want.abs() + (1 + u) * s * err + (2.0 ** -25 if store == "f16" else 0.0)
+        ratio = float(((got.double() - want).abs() / bound).max())
+        print("  side %d error / bound %.3g" % (side, ratio), flush=True)
+        assert ratio <= 1.0
+
+
+@pytest.mark.parametrize("n,nb,update,store", [(4300, 64, "f16", "f16"), (4500, 128, "f8", "bf16")])
+def test_whole_factor_with_inverse_strips(n, nb, update, store):
+    assert _on_inverse_path(n, nb)
+    _factor_error(n, nb, update, store)
+
+
+# members on and off the inverse path, of different block sizes on it (the launch's
+# tiles follow its largest), in one group: bit for bit the single factorisations
+@pytest.mark.parametrize("store,group", [("f16", [(4400, 64), (8800, 512), (700, 128), (4500, 256), (4700, 512)]),
+                                         ("bf16", [(4400, 64), (8800, 512), (700, 128), (4500, 256)]),
+                                         ("f16", [(17500, 1024), (4400, 64), (4500, 256)])])
+def test_group_of_members_on_and_off_the_inverse_path(store, group):
+    print("group", store, group, flush=True)
+    on = {nb for n, nb in group if _on_inverse_path(n, nb)}
+    assert len(on) >= 3 and (len(on) < len(group) or 1024 in on)
+    probs = [mxp.mxp_generate(n, 1, 60 + i, store=store) for i, (n, _) in enumerate(group)]
+    facs = mxp.mxp_factor_group(probs, [nb for _, nb in group], store)
+    for i, ((n, nb), fac) in enumerate(zip(group, facs)):
+        one = mxp.mxp_factor(mxp.mxp_generate(n, 1, 60 + i, store=store), nb, store)
+        assert fac.info == 0 and torch.equal(fac.LU[:, :n], one.LU[:, :n]), (n, nb)
