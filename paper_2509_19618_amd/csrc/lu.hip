@@ -177,13 +177,18 @@ MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M
 #pragma unroll
         for (int u = 0; u < 4; ++u) a[u] = *(const f4*)(ub + lo + 16 * u);
     };
-    auto ld_inv = [&](float (&v)[16], int J) {
+    // the step's inverse, lower triangular in (row, k): this wave's 16 rows, the
+    // sixteens of k left of its diagonal one (vi, k = 16 u + t + 4 g) and that (vd, k
+    // = 16 tj + 4 t + g)
+    auto ld_inv = [&](float (&vi)[12], float (&vd)[4], int J) {
         const float* ub = Minv + (int64_t)J * 4096 + 16 * tj;
         const int lo = c + 256 * g;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 3; ++u)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) v[4 * u + t] = ub[lo + (16 * u + t) * 64];
+            for (int t = 0; t < 4; ++t) vi[4 * u + t] = ub[lo + (16 * u + t) * 64];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) vd[t] = ub[c + 64 * g + (16 * tj + 4 * t) * 64];
     };
     float* const Sr = S + (16 * h + c) * SP + 4 * g;             // this lane's run, its k
     float* const Rr = R + (16 * h + c) * RP + 4 * g;
@@ -203,9 +208,9 @@ MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M
             acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3][t], b[3][t], acc1, 0, 0, 0);
         }
     };
-    float iv[16];
+    float iv[12], id[4];
     f4 m0[4], m1[4];
-    ld_inv(iv, 0);
+    ld_inv(iv, id, 0);
     for (int J = 0; J < nbk; ++J) {
         acc0 = acc1 = f4{0.0f, 0.0f, 0.0f, 0.0f};
         // m0 holds block (J, 0), m1 block (J, 1) (loaded during step J - 1); the
@@ -231,19 +236,26 @@ MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M
         const int o = J * 64 + 16 * tj;
         *(f4*)(Rr + 16 * tj) = *(const f4*)(Sr + o) - (acc0 + acc1);
         __syncthreads();
-        f4 b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = *(const f4*)(Rr + 16 * u);
+        // (the diagonal sixteen last and in the order of k: its diagonal entry, by far
+        // the largest as a rule, is then the last one added; with terms after it,
+        // each rounded at its magnitude, L21 and U12 were off by 0.60 and 0.46
+        // instead of 0.42 and 0.29 units of 2^-24 of the largest, rms)
         acc0 = acc1 = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        auto mul_inv = [&](int u, f4& a) {
+            const f4 b = *(const f4*)(Rr + 16 * u);
 #pragma unroll
-        for (int u = 0; u < 4; u += 2)
+            for (int t = 0; t < 4; ++t) a = __builtin_amdgcn_mfma_f32_16x16x4f32(iv[4 * u + t], b[t], a, 0, 0, 0);
+        };
+        float bd[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(iv[4 * u + t], b[u][t], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(iv[4 * u + 4 + t], b[u + 1][t], acc1, 0, 0, 0);
-            }
-        if (J + 1 < nbk) ld_inv(iv, J + 1);
-        const f4 y = acc0 + acc1;
+        for (int t = 0; t < 4; ++t) bd[t] = R[(16 * h + c) * RP + 16 * tj + 4 * t + g];
+        if (tj > 0) mul_inv(0, acc0);                    // (wave-uniform)
+        if (tj > 1) mul_inv(1, acc1);
+        if (tj > 2) mul_inv(2, acc0);
+        f4 y = acc0 + acc1;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y = __builtin_amdgcn_mfma_f32_16x16x4f32(id[t], bd[t], y, 0, 0, 0);
+        if (J + 1 < nbk) ld_inv(iv, id, J + 1);
         *(f4*)(Sr + o) = y;
 #pragma unroll
         for (int q = 0; q < 4; ++q) m = fmaxf(m, fabsf(y[q]));

@@ -104,3 +104,29 @@ def test_group_of_members_on_and_off_the_inverse_path(store, group):
     for i, ((n, nb), fac) in enumerate(zip(group, facs)):
         one = mxp.mxp_factor(mxp.mxp_generate(n, 1, 60 + i, store=store), nb, store)
         assert fac.info == 0 and torch.equal(fac.LU[:, :n], one.LU[:, :n]), (n, nb)
+
+
+# FP32 storage shows the solves' own roundings.  An entry of the size of the largest
+# is rounded in the right-hand side's last sum and in the result, L21 also in the
+# reciprocal of its pivot; entries spread evenly below the largest, a rounding is
+# 0.22 units of 2^-24 of it, rms: two of them 0.31 (U12: 0.36), with a reciprocal to
+# 1 ulp and the product's binade anywhere at most 0.5 (L21).  Terms added after the
+# diagonal one, by far the largest, each add such a rounding: 0.46 and 0.60.  The
+# sums themselves: j products of size p in two accumulators, each partial sum of
+# about p sqrt(k) rounded to 0.42 units of its own size, come to 0.21 p j, over the
+# columns j < nb 0.12 p nb (dominant: below 0.01; sqrt(n) kind: 0.42 at nb = 1024).
+@pytest.mark.parametrize("n,nb", [(3000, 512), (3000, 128), (2500, 1024)])
+@pytest.mark.parametrize("kind", [mxp.GEN_DOMINANT, mxp.GEN_SQRTN])
+def test_rounding_of_the_substitution(n, nb, kind):
+    print("fp32 strips", n, nb, kind, flush=True)
+    for side, (got, want, _, rhs, inv) in enumerate(_first_step(n, nb, "f32", "f32", kind=kind)):
+        top = want.abs().amax(0) if side == 0 else want.abs().max()
+        rms = float((((got.double() - want) / top) ** 2).mean() ** 0.5) * 2.0 ** 24
+        # a product: of a solution's entry and one beside the diagonal, about as large as
+        # one of the right-hand side over the pivot is; relative to the right-hand side
+        p = float(want.square().mean().sqrt() * (rhs.square().mean().sqrt() if side == 0 else
+                                                 inv.triu(1).square().sum().div(nb * (nb - 1) / 2).sqrt())) / \
+            float(rhs.abs().max())
+        bound = ((0.5, 0.36)[side] ** 2 + (0.12 * p * nb) ** 2) ** 0.5
+        print("  side %d rms %.3f (bound %.3f)" % (side, rms, bound), flush=True)
+        assert rms <= bound
