@@ -587,13 +587,19 @@ __global__ __launch_bounds__(DT, 4) void k_diag_lu(const DiagGroup grp) {
         solve_tile(x, F, side == 1, c, g);
         put(x, 0, 0);
         const Tile zero = {};
-        Tile z = neg(mma_tile(a, x, zero));
+        const Tile z = neg(mma_tile(a, x, zero));
         stage_tri(side, t, F);
-        solve_tile(z, F, side == 1, c, g);
-        put(z, 0, 32);
         x = id;
         solve_tile(x, F, side == 1, c, g);
         put(x, 32, 32);
+        // Y21 = Y22 z as a product (a solve rounds its 32 terms at the result's
+        // magnitude: the inverses were off by 0.61 instead of 0.51 units of 2^-24,
+        // rms of |L Y - I| / |L||Y|), Y22 by its rows through F
+        lds_st_tile(x, F, c, g);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x.x[r >> 2][r & 3] = F[kin(r, g) * SP + krun(r, c)];
+        put(mma_tile(x, z, zero), 0, 32);
         put(zero, 32, 0);
         return true;
     };

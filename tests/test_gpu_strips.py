@@ -130,3 +130,25 @@ def test_rounding_of_the_substitution(n, nb, kind):
         bound = ((0.5, 0.36)[side] ** 2 + (0.12 * p * nb) ** 2) ** 0.5
         print("  side %d rms %.3f (bound %.3f)" % (side, rms, bound), flush=True)
         assert rms <= bound
+
+
+# the 64 x 64 inverses, |M Y - I| / |M| |Y|: their lower left quarter as a product
+# (0.51, the right one 0.56) and not as a solve, whose 32 terms per entry are each
+# rounded at the result's size (0.61, 0.66)
+@pytest.mark.parametrize("nb", [512, 1024])
+def test_rounding_of_the_sub_block_inverses(nb):
+    print("64 x 64 inverses", nb, flush=True)
+    rms = [[], []]
+    eye = torch.eye(64, dtype=torch.float64, device="cuda")
+    for seed in range(1, 7):
+        fac = mxp.mxp_factor(mxp.mxp_generate(nb, 1, seed, store="f32"), nb, "f32")
+        lay = mxp.factor_layout(nb, nb, "f32")
+        T = fac.aux[lay.T:lay.T + 4 * nb * nb].view(torch.float32).view(nb, nb).t().double()[:64, :64]
+        for side, off in enumerate((lay.linv, lay.uinv)):
+            Y = fac.aux[off:off + 4 * 4096].view(torch.float32).view(64, 64).double()
+            M, Y = (torch.tril(T, -1) + eye, Y.t()) if side == 0 else (torch.triu(T), Y)
+            E = (M @ Y - eye).abs() / (M.abs() @ Y.abs()).clamp_min(1e-30)
+            rms[side].append(float((E ** 2).mean() ** 0.5) * 2.0 ** 24)
+    mean = [sum(r) / len(r) for r in rms]
+    print("  rms L %.3f U %.3f" % tuple(mean), flush=True)
+    assert mean[0] <= 0.55 and mean[1] <= 0.6
