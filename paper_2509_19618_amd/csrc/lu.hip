@@ -1069,9 +1069,18 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
     }
     // the first pair of a matrix whose strips are solved in one launch has nothing
     // to overlap with: it stays on the caller's stream
-    const hipStream_t side = LA->side;
     const bool lone = first_strips(p, 0) == strip_count(p, 0);
     hipStream_t chain = lone ? s : LA->chain;
+    // Under stream capture the side stream's work goes to the chain: a captured call
+    // only forks from the caller's stream and joins it (a capture in which two forked
+    // streams wait for each other's events ended the process).
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture)) {             // (no answer for the null stream beside a capture)
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusNone;
+    }
+    const bool apart = capture == hipStreamCaptureStatusNone;
+    const hipStream_t side = apart ? LA->side : LA->chain;
     bool side_used = false;
     // the strips of step j: the first (or all); the others behind them, through
     // the inverses, which start with a launch of few work-groups, beside them
@@ -1079,13 +1088,14 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
         const int first = first_strips(p, j);
         if (first == strip_count(p, j)) return strips(j, 0, first, chain);
         const bool inv = NP && inverse_path(p, j);
-        side_used = true;
+        side_used = apart;
         hipError_t e2;
-        if (inv) {
+        if (apart && inv) {
             if ((e2 = hipEventRecord(LA->ev_diag, chain))) return e2;
             if ((e2 = hipStreamWaitEvent(side, LA->ev_diag, 0))) return e2;
         }
         if ((e2 = strips(j, 0, first, chain))) return e2;
+        if (!apart) return other_strips(j, side);
         if ((e2 = hipEventRecord(LA->ev_first, chain))) return e2;
         if (!inv && (e2 = hipStreamWaitEvent(side, LA->ev_first, 0))) return e2;
         if ((e2 = other_strips(j, side))) return e2;
@@ -1139,8 +1149,8 @@ static hipError_t factor_typed(const FactorPlan& p, hipStream_t s, Lookahead* la
                 c[0] = pair_call<ST, OP>(p, a, false, c0, b, n - c0, wb);
                 c[1] = pair_call<ST, OP>(p, a, false, b, c0, wb, n - c0);
                 if ((e = gemm(c, 2, side))) return e;
-                if ((e = hipEventRecord(LA->ev_side, side))) return e;
-                if ((e = hipStreamWaitEvent(chain, LA->ev_side, 0))) return e;
+                if (apart && (e = hipEventRecord(LA->ev_side, side))) return e;
+                if (apart && (e = hipStreamWaitEvent(chain, LA->ev_side, 0))) return e;
             }
             if ((e = panel(b))) return e;
         }
