@@ -162,11 +162,11 @@ int mxp_generate(int64_t n, int64_t nrhs, uint64_t seed, int kind, double gamma,
  * asynchronous caller that needs the report reads the info word of `work`
  * (mxp_factor_get_layout: work offset `info`, an unsigned 64-bit value, all
  * ones when no pivot failed) after the stream has finished.
- * Concurrency: the factorisation runs on `stream` and on a side stream of
- * its own (look-ahead); each call takes a side stream and its events from a
- * per-device pool for the time of the call, so host threads may factor at
- * the same time on different streams.  Calls sharing `work`, `aux` or `A`
- * must be ordered by the caller.
+ * Concurrency: the factorisation runs on `stream` and on two streams of its
+ * own (look-ahead; under stream capture on one); each call takes them and
+ * their events from a per-device pool for the time of the call, so host
+ * threads may factor at the same time on different streams.  Calls sharing
+ * `work`, `aux` or `A` must be ordered by the caller.
  */
 size_t mxp_factor_aux_bytes(int64_t n, int64_t nb);
 size_t mxp_factor_work_bytes(int64_t n, int64_t nb, int update);

@@ -14,7 +14,11 @@
 // blocks of the 16 x 16 MFMA: lane l = 16 g + c has, in register 8 J + 4 I + q,
 // run 16 J + c at inner index 16 I + 4 g + q.  That is at once the A and the B
 // operand order of v_mfma_f32_16x16x4f32 (any order of K serves if both
-// operands share it) and the order of its result registers, so that a tile
+// operands share it; in that of K itself, which takes 4-byte loads, the
+// factorisation at n = 12013 took 6.75 against 6.10 ms for the same error on
+// dominant and sqrt(n) matrices; on uniform entries, where a small pivot's terms
+// cancel in the next one, |LU - A| / |L||U| was 0.12 against 0.20 units of 2^-24,
+// rms) and the order of its result registers, so that a tile
 // goes from accumulation through the solve to the next product without moving
 // between lanes.  Tiles of L are kept transposed, which makes L (solve with
 // U^T) and U (solve with L) one code path: side 0 = L(o,d), side 1 = U(d,o),
@@ -53,8 +57,9 @@
 // last update 0.9, the rest hand-overs and the round through the helpers: a
 // tile at distance three is back 5.7 us after its leaf).  With one phase per
 // kind of task, opened and closed through device counters, a step took 15 us.
-// Measured with rocprofv3 inside factorisations (BF16): nb = 512 252 -> 139 us
-// per block (n = 12013), nb = 256 122 -> 65 us, nb = 128 71 -> 35 us.
+// Measured with rocprofv3 inside factorisations (BF16): nb = 512 252 -> 148 us
+// per block (n = 12013, in part beside other strips' solves; 131 alone), nb = 256
+// 122 -> 65 us, nb = 128 71 -> 35 us.
 #include "common.hpp"
 #include "kernels.hpp"
 

@@ -162,7 +162,7 @@ template <class T> struct alignas(4 * sizeof(T)) Pack4 {
 // half of the sum in another wave, four barriers a step), rocprofv3, both sides'
 // strips in one launch: nb = 512 66 -> 64 us (two strips per CU), nb = 256 (a group
 // of six orders of 520 to 5003) 31 -> 24 us, nb = 256 FP32 (n = 2048)
-// 17.1 -> 15.7 us.
+// 17.1 -> 15.7 us; 64, 24.5 and 16.3 with the inverse's diagonal term added last.
 MXP_DEV float strip_solve(float* S, int SP, int nbk, const float* __restrict__ M, int ld,
                           const float* __restrict__ Minv, float* R) {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -956,8 +956,8 @@ static int cross_calls(const FactorPlan& p, int64_t j, bool pair, int64_t b, Gem
 //   beyond.
 // With every strip and the whole of block column and row b on the chain (which
 // is still the order where one launch solves a step's strips) the factorisation at
-// n = 12013 nb = 512 BF16 took 6.65 ms where it takes 6.17, the solve at n = 20001
-// with FP8 operands 16.9 against 15.6: there a step's 300 us and more of chain (LU
+// n = 12013 nb = 512 BF16 took 6.65 ms against 6.17, the solve at n = 20001 with FP8
+// operands 16.9 against 15.6 (6.15 and 15.3 now): there a step's 300 us and more of chain (LU
 // 150, inverses, their parts and products 160, update 20) became 270 (LU 175 beside
 // the products, strips 60 to 85, update 17).
 // One event per hand-over, waited for before its next record is enqueued.  The

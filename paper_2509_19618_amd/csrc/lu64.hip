@@ -855,8 +855,8 @@ __global__ __launch_bounds__(PW_T) void k_panel64_wg(double* A, int64_t lda, int
 #pragma unroll
         for (int c = 0; c < W; ++c) {
             const int r = tid + PW_T * i;
-            // past the edges: a zero row, and the identity in the columns past w
-            // (their pivots, taken last, are not written)
+            // past the edges zeros (the columns past w, those of the matrix's last
+            // sub-panel only, take no part in its elimination)
             const bool in = r < m && c < w;
             const double v = A[in ? (k0 + r) + (k0 + c) * lda : k0 + k0 * lda];
             x[i][c] = in ? v : 0.0;
@@ -1055,8 +1055,8 @@ __global__ __launch_bounds__(256) void k_laswp64(double* A, int64_t lda, int64_t
 // blocks of 128 rows, one launch per block: every work-group subtracts the
 // previous block's contribution from its 128 rows, and the one that holds
 // the next block solves it in the same launch.  Launches and the solve's
-// chain bound it (about 7 us per block); blocks of 64 with the triangle solved
-// by one lane per right-hand side from memory took 80 us per block.
+// chain bound it (14 to 16 us per block at n = 8192); blocks of 64 with the
+// triangle solved by one lane per right-hand side from memory took 80 us.
 
 // The n swaps in order, one work-group per right-hand side: x in LDS when it fits
 // (lds_n = n).  Sixteen waves form the net exchange of 64 swaps each -- at most 128

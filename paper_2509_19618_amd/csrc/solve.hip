@@ -44,10 +44,7 @@ __host__ __device__ static inline int64_t rup(int64_t a, int64_t b) { return (a 
 // Each wait is still bounded; on expiry it sets *err and the work-group goes
 // through its remaining steps without waiting.  All sums are taken in a fixed
 // order (deterministic results).
-#ifndef MXP_TRSV_TS
-#define MXP_TRSV_TS 64
-#endif
-constexpr int TS = MXP_TRSV_TS;
+constexpr int TS = 64;
 
 // Values exchanged between work-groups (block solutions, block right-hand
 // sides) are written and read with device-scope atomic accesses, which go to
